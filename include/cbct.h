@@ -307,8 +307,9 @@ int cbct_probe_fma_rate(int32_t fp64, double *tflops_host, void *stream);
  * height in pixels, [2] samples per box (the projector stages runs of
  * such pieces), [3] LDS box capacity in floats; [4..6] transpose brick in
  * cells (x, y, z), [7] LDS table capacity in pixels.  A piece whose box
- * exceeds [3], or a brick whose footprint on the detector exceeds [7]
- * pixels, reads global memory instead of LDS (same results).  Returns the number of entries written (8 when n >= 8),
+ * exceeds [3] reads global memory instead of LDS, and a brick whose
+ * footprint on the detector exceeds [7] pixels is staged in parts (same
+ * results).  Returns the number of entries written (8 when n >= 8),
  * EINVAL for a NULL array or negative n.  No GPU work. */
 int cbct_kernel_config(int32_t *out_host, int32_t n);
 

@@ -253,7 +253,7 @@ int validate_geom(const cbct_geom *g) {
     // some launches, all projector tiles form one linear grid
     if (g->n_views > 65535 || g->nz + 2 > 65535)
         return set_error(CBCT_EINVAL, "more than 65535 views or planes");
-    // the transpose stores cell indices and segment numbers as 16-bit integers
+    // the projector packs its boxes' cell indices into 16-bit integers
     if (g->nx > 32000 || g->ny > 32000 || g->nz > 32000)
         return set_error(CBCT_EINVAL, "grid dimension above 32000");
     if ((double)project_partials_count(*g) > 2147483647.0)
@@ -296,9 +296,8 @@ extern "C" int cbct_plan_create(const cbct_geom *gin, cbct_plan **out) {
         p->g = *gin;
         if (!(p->g.step > 0)) p->g.step = 0.5 * std::min(gin->hx, std::min(gin->hy, gin->hz));
         // sample indices n = t / step stay below (the source's distance to
-        // the grid centre + half the grid diagonal) / step; keep them well
-        // inside the 16-bit segment numbers of the transpose
-        // (n < 32767 * 256)
+        // the grid centre + half the grid diagonal) / step; the transpose
+        // counts them in float, from the grid centre's, up to 2^23
         const double reach =
             std::max(p->g.sdd, p->g.sad + sqrt(pow(p->g.x_off, 2) + pow(p->g.y_off, 2) +
                                                pow(p->g.z_off, 2))) +
@@ -341,6 +340,8 @@ extern "C" int cbct_plan_create(const cbct_geom *gin, cbct_plan **out) {
             v.sn = (float)sn;
             v.csd = cs;
             v.snd = sn;
+            v.nmid = (int)lround(sqrt(pow(src[0] - off[0], 2) + pow(src[1] - off[1], 2) +
+                                      off[2] * off[2]) / step);
         }
         DetConst &d = p->det;
         d.u0d = -0.5 * (g.nu - 1) * g.au + g.u_off;

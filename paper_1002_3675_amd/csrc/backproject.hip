@@ -6,37 +6,35 @@
 // interpolation cell rather than by voxel:
 //
 //   * a cell c = (cx, cy, cz), c_a in [-1, N_a - 1], is the box between
-//     voxel centres c and c + 1; every projector sample lies in exactly one
-//     cell, the one given by the projector's own cell arithmetic;
+//     voxel centres c and c + 1; every sample lies in exactly one cell;
 //   * preparation (geometry only, once per plan or workspace): the ray
-//     increment of every pixel of every view, and every brick's pixel
-//     rectangle per view (its footprint on the detector);
+//     increment of every pixel of every view, and every brick's footprint
+//     on the detector and map from cells to pixels per view;
 //   * pass 1 (one lane per cell, a workgroup per 16x16x1 brick of cells):
-//     for every view the workgroup stages, per pixel of its brick's
-//     footprint, the candidate-range terms, the segment origin of the ray
-//     in the brick and the residual in LDS; each lane then visits the
-//     pixels whose rays can cross its cell, enumerates the samples of each
-//     such ray that fall in the cell, and accumulates r * (trilinear
-//     corner weight), in xy-moment form, into eight register accumulators;
+//     for every view the workgroup stages the rays of its brick's footprint
+//     in LDS; each lane then visits the pixels whose rays can cross its
+//     cell and adds each ray's samples in the cell, r * (trilinear corner
+//     weight), to eight moments in registers.  In float the samples of one
+//     crossing are added in closed form (see crossing_sums); in double one
+//     by one;
 //   * pass 2 (one lane per voxel): sum the matching corner of the eight
 //     cells that share the voxel, optionally fused with Step 1 of
 //     Algorithm A1, g = f - tau * P^T r.
 //
-// Each (ray, sample) is visited once instead of eight times (once per
-// trilinear tap), every sum has a fixed order, and no lane writes memory
-// another lane writes.
-#include "ray.hpp"
+// Each (ray, cell) crossing is visited once, not once per trilinear tap,
+// every sum has a fixed order, and no lane writes memory another lane
+// writes.
+#include <type_traits>
 
-#ifndef CBCT_CELL_TABLE
-#define CBCT_CELL_TABLE 344
-#endif
+#include "ray.hpp"
 
 namespace cbct {
 
 namespace {
 
 constexpr int CB_X = 16, CB_Y = 16, CB_Z = 1;  // cells per workgroup: one z layer
-constexpr int TABLE = CBCT_CELL_TABLE;         // pixels staged per view (60 B each)
+constexpr int TABLE = 560;                     // rays staged at a time (40 B each)
+constexpr int PARTS = 6;                       // views staged at a time, at most
 constexpr int G_BX = 64, G_BY = 4;            // pass-2 block
 
 // Row pitch (in elements) of the cell corner-sum array: nx + 1 cells
@@ -48,65 +46,19 @@ __host__ __device__ __forceinline__ long long cell_pitch(int nx) {
 }
 
 // Ray table entry per pixel and view (prepared once): the ray increment D
-// in double (segment origins).  Readers form the reciprocals of its float
-// rounding for the range estimates themselves (ray_inv).  24 bytes.
+// in double.  Components below TINY_D are stored as TINY_D: such a ray then
+// crosses the faces of that axis far outside every sample, on the right
+// sides, and its samples' positions are unchanged to the last bit.  24 bytes.
+constexpr double TINY_D = 1e-20;
+
 struct PixelRay {
     double D[3];
 };
 
-// LDS entry per footprint pixel of the current view, in two parts.
-//
-// StagedRange serves the candidate test every cell of the brick makes for
-// this pixel.  Along axis a the samples with coordinate in [c_a, c_a + 1)
-// lie between (c_a - Q_a)/D_a and (c_a + 1 - Q_a)/D_a.  The float Q and D
-// differ from the double ones by at most ~1e-6 relative, which moves these
-// bounds by at most 1e-6 (|Q_a| + |c_a| + 1) |inv_a| (inv = 1/D_f); a
-// margin m_a = K_a |inv_a| + 1e-3 with K_a = 4e-6 (|Q_a| + max |c_a| over
-// the brick + 1) covers four times that plus the rounding of the float
-// estimate itself.  With the cell's cq_a = c_a - Q_a (float) the widened
-// bounds are
-//     lo_a = fma(cq_a, inv_a, min(0, inv_a) - m_a),
-//     hi_a = lo_a + |inv_a| (1 + 2 K_a) + 2e-3,
-// and lo[a] holds the additive term of lo_a (a = x, y).  Every cell of the
-// brick lies in the same z layer, so the z bounds are the same for all of
-// them: zlo, zhi.  24 bytes.
-//
-// StagedWalk serves the cells with candidates: the origin (I, f) of the
-// segment sq * SEG that holds the ray's first sample in the brick, as the
-// projector computes it; D_f = (float)D; the residual.  Cells whose
-// candidates start in another segment compute that segment's origin from
-// the ray table.  Grid dimensions below 32000 keep I (within SEG/2 + 2
-// cells of the brick) in a short.  36 bytes.
-struct StagedRange {
-    float inv[2];
-    float lo[2];
-    float zlo, zhi;
-};
-
-struct StagedWalk {
-    float f[3];
-    float Df[3];
-    float r;
-    short I[3];
-    short sq;
-};
-
-// Both parts of a pixel's entry, side by side: one pointer reaches both.
-struct StagedEntry {
-    StagedRange rg;
-    StagedWalk wk;
-};
-static_assert(sizeof(StagedEntry) == 60, "60-byte LDS entries");
-
-__device__ __forceinline__ float inv_or_huge(float d) {
-    return d != 0.0f ? __builtin_amdgcn_rcpf(d) : 1e30f;
-}
-
-// Reciprocals of the float rounding of a ray's increment (1e30 stands for
-// the reciprocal of an exactly zero component).
+// Reciprocals of the float rounding of a ray's increment.
 __device__ __forceinline__ void ray_inv(const PixelRay &g, float inv[3]) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) inv[a] = inv_or_huge((float)g.D[a]);
+    for (int a = 0; a < 3; ++a) inv[a] = __builtin_amdgcn_rcpf((float)g.D[a]);
 }
 
 // Per-lane, per-view constants of the candidate range of cell c: along
@@ -196,8 +148,9 @@ __device__ __forceinline__ void pixel_range(const DetConst &dc, int nu, int nv, 
 }
 
 // Accumulate r * corner weights of sample weights (wx, wy, wz).
-template <typename T>
-__device__ __forceinline__ void add_corners(T acc[8], T rv, T wx, T wy, T wz) {
+__device__ __forceinline__ void add_corners(double acc[8], double rv, double wx, double wy,
+                                            double wz) {
+    typedef double T;
     const T b1 = rv * wz, b0 = rv - b1;
     const T a01 = b0 * wy, a00 = b0 - a01;
     const T a11 = b1 * wy, a10 = b1 - a11;
@@ -208,127 +161,7 @@ __device__ __forceinline__ void add_corners(T acc[8], T rv, T wx, T wy, T wz) {
     t = a11 * wx; acc[6] += a11 - t; acc[7] += t;
 }
 
-// Float accumulation of r * corner weights in xy-moment form: for each z
-// corner oz the cell keeps S = sum b, X = sum b wx, Y = sum b wy and
-// XY = sum b wx wy, b = r * (z weight); the corners are (S - X) - (Y - XY),
-// X - XY, Y - XY and XY (moments_to_corners).  12 operations per sample
-// instead of 22.  The differences carry an absolute error of a few ulp of
-// S, the cell's mass on that z face, which is at most the sum over the
-// corners the voxel gather adds it to.
-__device__ __forceinline__ void add_moments(float acc[8], float rv, float wx, float wy,
-                                            float wz) {
-    const float b1 = rv * wz, b0 = rv - b1;
-    acc[0] += b0;
-    acc[1] = __builtin_fmaf(b0, wx, acc[1]);
-    acc[2] = __builtin_fmaf(b0, wy, acc[2]);
-    acc[3] = __builtin_fmaf(b0 * wx, wy, acc[3]);
-    acc[4] += b1;
-    acc[5] = __builtin_fmaf(b1, wx, acc[5]);
-    acc[6] = __builtin_fmaf(b1, wy, acc[6]);
-    acc[7] = __builtin_fmaf(b1 * wx, wy, acc[7]);
-}
-
-// Corner sums (index ox + 2 oy + 4 oz) from the xy-moments of add_moments.
-__device__ __forceinline__ void moments_to_corners(const float m[8], float c[8]) {
-#pragma unroll
-    for (int z = 0; z < 2; ++z) {
-        const float S = m[4 * z], X = m[4 * z + 1], Y = m[4 * z + 2], XY = m[4 * z + 3];
-        c[4 * z + 0] = (S - X) - (Y - XY);
-        c[4 * z + 1] = X - XY;
-        c[4 * z + 2] = Y - XY;
-        c[4 * z + 3] = XY;
-    }
-}
-
-// Where a pixel's ray-table entry is, computed only on the rare path that
-// needs the ray's double increment.  The pixel index passes through an
-// empty asm statement first, so the compiler cannot hoist the 64-bit
-// address arithmetic out of that path into every visit.
-struct RayRef {
-    const PixelRay *view;  // the view's table
-    int nu, i, j;
-    __device__ __forceinline__ const PixelRay *get() const {
-        int jj = j, ii = i;
-        asm volatile("" : "+v"(jj), "+v"(ii));
-        return view + ((long long)jj * nu + ii);
-    }
-};
-
-// Candidate samples of a ray in cell (cx, cy, cz), float data: sample
-// indices sf * SEG + m for m from m0 to mlast (integer-valued floats, sf the
-// segment number, m0 < SEG; mlast may run into later segments); o is the
-// origin of segment sf.  A later segment's origin is computed from the
-// ray's double increment in the ray table.  The projector's own cell
-// arithmetic decides membership; a candidate outside the cell adds zero (no
-// branch in the loop body).
-__device__ __forceinline__ void cell_samples_f(float acc[8], float rv, const double Qd[3],
-                                               const RayRef &ray, SegOrigin o, float sf,
-                                               const float Df[3], float m, float mlast, int cx,
-                                               int cy, int cz) {
-#pragma clang fp contract(off)
-    // The projector puts sample m of the segment in cell I + floor(l) with
-    // l = fma(m, Df, f), weight l - floor(l): the sample is in cell c when
-    // floor(l) == L = c - I on every axis, and its weight is then l - L.
-    // With L an integer, w = l - L rounds to itself except for l in
-    // [-2^-25, 0) with L = -1, where it rounds up to 1; rounding keeps w's
-    // sign and its order against 1.  So floor(l) == L exactly when w, read as
-    // an unsigned integer, is below that of 1.0f (a negative w has its sign
-    // bit set, l - L = 0 gives +0), except when some w is exactly 1: then
-    // floor decides, as in the projector, in a second pass over the
-    // segment's candidates.
-    float L[3];
-    auto bounds = [&]() {
-        L[0] = (float)(cx - o.I[0]);
-        L[1] = (float)(cy - o.I[1]);
-        L[2] = (float)(cz - o.I[2]);
-    };
-    bounds();
-    constexpr unsigned ONE = 0x3f800000u;  // 1.0f
-    for (;;) {
-        // samples up to the end of this segment (float counts are exact)
-        const float mend = __builtin_amdgcn_fmed3f(mlast, 0.0f, (float)(SEG - 1));  // mlast >= 0
-        const float mstart = m;
-        bool edge = false;  // some sample had a weight of exactly 1
-        for (; m <= mend; m += 1.0f) {
-            const float wx = __builtin_fmaf(m, Df[0], o.f[0]) - L[0];
-            const float wy = __builtin_fmaf(m, Df[1], o.f[1]) - L[1];
-            const float wz = __builtin_fmaf(m, Df[2], o.f[2]) - L[2];
-            const unsigned wmax = max(max(__builtin_bit_cast(unsigned, wx),
-                                          __builtin_bit_cast(unsigned, wy)),
-                                      __builtin_bit_cast(unsigned, wz));
-            add_moments(acc, wmax < ONE ? rv : 0.0f, wx, wy, wz);
-            edge |= wmax == ONE;
-        }
-        if (edge) {
-            // rare: add the samples with a weight of 1 that floor puts in
-            // the cell (after the others: the order of the sum changes, not
-            // its terms)
-            for (float mm = mstart; mm <= mend; mm += 1.0f) {
-                const float lx = __builtin_fmaf(mm, Df[0], o.f[0]);
-                const float ly = __builtin_fmaf(mm, Df[1], o.f[1]);
-                const float lz = __builtin_fmaf(mm, Df[2], o.f[2]);
-                const float wx = lx - L[0], wy = ly - L[1], wz = lz - L[2];
-                const unsigned wmax = max(max(__builtin_bit_cast(unsigned, wx),
-                                              __builtin_bit_cast(unsigned, wy)),
-                                          __builtin_bit_cast(unsigned, wz));
-                const bool in = (__builtin_floorf(lx) == L[0]) &
-                                (__builtin_floorf(ly) == L[1]) & (__builtin_floorf(lz) == L[2]);
-                if (wmax == ONE && in) add_moments(acc, rv, wx, wy, wz);
-            }
-        }
-        if (mlast <= (float)(SEG - 1)) return;
-        // rare: the cell's samples of this ray run into the next segment
-        sf += 1.0f;
-        m = 0.0f;
-        mlast -= (float)SEG;
-        const PixelRay *gray = ray.get();
-        const double D[3] = {gray->D[0], gray->D[1], gray->D[2]};
-        o = seg_origin(Qd, D, (int)sf * SEG);
-        bounds();
-    }
-}
-
-// The same for double data: every sample in double, no segments.
+// Samples n0 .. n1 of a ray that fall in cell (cx, cy, cz), double data.
 __device__ __forceinline__ void cell_samples_d(double acc[8], double rv, const double Qd[3],
                                                const double D[3], int n0, int n1, int cx,
                                                int cy, int cz) {
@@ -339,15 +172,16 @@ __device__ __forceinline__ void cell_samples_d(double acc[8], double rv, const d
         const double q2 = sample_coord(nf, D[2], Qd[2]);
         const double f0 = floor_t(q0), f1 = floor_t(q1), f2 = floor_t(q2);
         if ((int)f0 != cx || (int)f1 != cy || (int)f2 != cz) continue;
-        add_corners<double>(acc, rv, q0 - f0, q1 - f1, q2 - f2);
+        add_corners(acc, rv, q0 - f0, q1 - f1, q2 - f2);
     }
 }
 
 // Geometry-only preparation, once per plan and workspace:
-//   k_rays:        the increment D (double) and its float reciprocals of the
-//                  ray through every pixel of every view;
-//   k_brick_rects: for every view and brick, the pixel rectangle whose rays
-//                  can reach the brick (its staged footprint).
+//   k_rays:        the increment D (double) of the ray through every pixel of
+//                  every view;
+//   k_brick_views: for every brick and view, the pixels whose rays can reach
+//                  the brick and where its cells project, and the views of a
+//                  brick that are staged together.
 __global__ __launch_bounds__(256) void k_rays(const ViewConst *__restrict__ views, DetConst dc,
                                               int nu, int nv, PixelRay *__restrict__ rays) {
     const int i = blockIdx.x * 64 + (threadIdx.x & 63);
@@ -357,330 +191,511 @@ __global__ __launch_bounds__(256) void k_rays(const ViewConst *__restrict__ view
     double Q[3], D[3];
     ray_setup(views[k], dc, i, j, Q, D);
     PixelRay e;
-    e.D[0] = D[0];
-    e.D[1] = D[1];
-    e.D[2] = D[2];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) e.D[a] = fabs(D[a]) < TINY_D ? TINY_D : D[a];
     rays[((long long)k * nv + j) * nu + i] = e;
 }
 
-// First cell and the box (mm) of brick (bxi, byi, bzi); the last brick of an
-// axis ends at the grid's last cell.  Cells c_a run from -1 to N_a - 1.
-struct BrickBox {
-    int c0[3];
-    float lo[3], hi[3];
+// Directions of the rays through pixel columns i0 .. i1 of a view: 4 + (1 if
+// x increases along them) + (2 if y does), or 0 when they are not the same
+// along all of them or too near zero to tell.
+__device__ __forceinline__ int ray_directions(const ViewConst &vc, const DetConst &dc, int i0,
+                                              int i1) {
+    const float ua = dc.u0 + (float)i0 * dc.au, ub = dc.u0 + (float)i1 * dc.au;
+    const float tol = 1e-4f * (fabsf(vc.W[0]) + fabsf(vc.W[1]));
+    int dir = 4;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const float da = vc.W[a] + ua * vc.U[a], db = vc.W[a] + ub * vc.U[a];
+        if (fminf(da, db) > tol)
+            dir |= 1 << a;
+        else if (!(fmaxf(da, db) < -tol))
+            return 0;
+    }
+    return dir;
+}
+
+// A brick in one view (prepared once), 64 bytes.
+//
+// Its footprint: pixels (i0, j0) .. (i0 + w - 1, j0 + h - 1), the rays that
+// can reach it (w = h = 0 if none), and their directions (ray_directions).
+//
+// For each of its cells (px, py), relative to (i0, j0): the pixels whose rays
+// can cross the cell lie in columns c .. c + W - 1 and rows r .. r + H - 1,
+//     c = ceil(a0 + ax px + ay py),   r = ceil(b0 + bx px + by py).
+// That is the cell's projection with its centre's perspective map replaced
+// by the tangent map at the brick's centre, widened by the bound of what
+// that leaves out, of the cells' different sizes in the view and of 0.01
+// pixel: a few hundredths of a pixel for a brick of 16 cells.
+//
+// Views are staged in batches of consecutive views whose footprints fit the
+// table together and whose rays have the same directions: batch_n views and
+// batch_rays rays when a batch begins with this view (batch_n = 0: the
+// footprint alone exceeds the table and is staged in parts), base this
+// view's first table entry in its batch.
+struct BrickView {
+    int i0, j0, w, h;
+    int W, H, dirs, base;
+    float a0, ax, ay, b0, bx, by;
+    int batch_n, batch_rays;
+};
+static_assert(sizeof(BrickView) == 64, "one 64-byte scalar load");
+
+__device__ BrickView brick_view(const ViewConst &vc, const DetConst &dc, const GridConst &gc,
+                                double hx, double hy, double hz, int nu, int nv,
+                                const int c0[3], const int c1[3]) {
+    const double cs = vc.csd, sn = vc.snd;
+    // brick centre and half extents (mm) from the source; n across the view, d its depth
+    const double ex = 0.5 * (c1[0] - c0[0]) * hx, ey = 0.5 * (c1[1] - c0[1]) * hy;
+    const double wx = (0.5 * (c0[0] + c1[0]) - vc.Qd[0]) * hx;
+    const double wy = (0.5 * (c0[1] + c1[1]) - vc.Qd[1]) * hy;
+    const double d = wy * cs - wx * sn, r = 1.0 / d, u = (wx * cs + wy * sn) * r;
+    const double gx = cs + u * sn, gy = sn - u * cs;  // d u = (gx dx + gy dy) / depth
+    const double D = ex * fabs(sn) + ey * fabs(cs);   // depth is within d -+ D
+    const double G = ex * fabs(gx) + ey * fabs(gy);
+    const double rmax = 1.0 / (d - D), rmin = 1.0 / (d + D);
+    const double U = G * rmax;                        // u is within u -+ U
+    const double za = (c0[2] - vc.Qd[2]) * hz, zb = (c1[2] - vc.Qd[2]) * hz;
+    const double su = dc.sddd / dc.aud, sv = dc.sddd / dc.avd;
+    const double ci = -dc.u0d / dc.aud, cj = -dc.v0d / dc.avd;
+    BrickView o;
+    // footprint, widened by 0.01 pixel and clamped to the detector
+    const double fi0 = ceil((u - U) * su + ci - 0.01), fi1 = floor((u + U) * su + ci + 0.01);
+    const double fj0 = ceil(fmin(za * rmin, za * rmax) * sv + cj - 0.01);
+    const double fj1 = floor(fmax(zb * rmin, zb * rmax) * sv + cj + 0.01);
+    o.i0 = (int)fmin(fmax(fi0, 0.0), nu - 1.0);
+    o.j0 = (int)fmin(fmax(fj0, 0.0), nv - 1.0);
+    o.w = (int)fmin(fi1, nu - 1.0) - o.i0 + 1;
+    o.h = (int)fmin(fj1, nv - 1.0) - o.j0 + 1;
+    if (!(fi0 <= nu - 1.0 && fj0 <= nv - 1.0 && fi1 >= fi0 && fj1 >= fj0) || o.w <= 0 || o.h <= 0)
+        o.w = o.h = 0;
+    o.dirs = o.w > 0 ? ray_directions(vc, dc, o.i0, o.i0 + o.w - 1) : 0;
+    // cells: half width in u, the tangent map's error, and the same in v/sdd
+    const double hw = (0.5 * hx * (fabs(gx) + U * fabs(sn)) + 0.5 * hy * (fabs(gy) + U * fabs(cs))) * rmax;
+    const double eu = G * D * r * rmax;
+    const double P = (hw + eu) * su + 0.01;
+    const double zm = 0.5 * (za + zb);
+    const double m = 0.5 * (hx * fabs(sn) + hy * fabs(cs));
+    const double Pv = (0.5 * (zb - za) * rmax + fabs(zm) * (m * rmax * rmax + D * D * r * r * rmax)) * sv + 0.01;
+    const double dx = (c0[0] + 0.5 - 0.5 * (c0[0] + c1[0])) * hx;  // cell (0, 0) from the centre
+    const double dy = (c0[1] + 0.5 - 0.5 * (c0[1] + c1[1])) * hy;
+    o.a0 = (float)(u * su + ci + su * r * (gx * dx + gy * dy) - P - o.i0);
+    o.ax = (float)(su * r * gx * hx);
+    o.ay = (float)(su * r * gy * hy);
+    o.b0 = (float)(zm * sv * (r - r * r * (dy * cs - dx * sn)) + cj - Pv - o.j0);
+    o.bx = (float)(zm * sv * r * r * hx * sn);
+    o.by = (float)(-zm * sv * r * r * hy * cs);
+    o.W = (int)fmin(floor(2.0 * P) + 1.0, 1e8);  // may exceed w
+    o.H = (int)fmin(floor(2.0 * Pv) + 1.0, 1e8);
+    o.base = 0;
+    o.batch_n = 0;
+    o.batch_rays = 0;
+    return o;
+}
+
+// One wavefront per brick, one view per lane, 64 views at a time (batches end
+// there); the wavefront then walks its lanes' footprints to form the batches,
+// in scalar registers.
+__global__ __launch_bounds__(64) void k_brick_views(const ViewConst *__restrict__ views,
+                                                    DetConst dc, GridConst gc, double hx,
+                                                    double hy, double hz, int nu, int nv,
+                                                    int nbx, int nby, int nviews,
+                                                    BrickView *__restrict__ out) {
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const int c0[3] = {(b % nbx) * CB_X - 1, ((b / nbx) % nby) * CB_Y - 1,
+                       (b / (nbx * nby)) * CB_Z - 1};
+    const int c1[3] = {min(c0[0] + CB_X, gc.nx), min(c0[1] + CB_Y, gc.ny),
+                       min(c0[2] + CB_Z, gc.nz)};
+    for (int k0 = 0; k0 < nviews; k0 += 64) {
+        const int k = min(k0 + lane, nviews - 1);
+        BrickView o = brick_view(views[k], dc, gc, hx, hy, hz, nu, nv, c0, c1);
+        // a footprint beyond the table stands alone (batch_n = 0)
+        const long long pixels = (long long)o.w * o.h;
+        const int size = pixels > TABLE ? TABLE + 1 : (int)pixels;
+        int head = 0, n = 0, rays = 0, dirs = 0;
+        auto close = [&](int next) {
+            if (lane == head && n > 0) {
+                o.batch_n = n;
+                o.batch_rays = rays;
+                o.dirs = dirs;
+            }
+            head = next;
+            n = rays = dirs = 0;
+        };
+        const int count = min(64, nviews - k0);
+        for (int q = 0; q < count; ++q) {
+            const int sq = __builtin_amdgcn_readlane(size, q);
+            const int dq = __builtin_amdgcn_readlane(o.dirs, q);
+            if (sq > TABLE) {
+                close(q + 1);
+                continue;
+            }
+            if (n == PARTS || rays + sq > TABLE || (rays > 0 && sq > 0 && dq != dirs)) close(q);
+            if (rays == 0) dirs = dq;
+            if (lane == q) o.base = rays;
+            rays += sq;
+            ++n;
+        }
+        close(count);
+        if (k0 + lane < nviews) out[(long long)b * nviews + k0 + lane] = o;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Float pass 1.
+//
+// Staged ray of the current footprints, relative to its brick: n counts the
+// ray's samples from the first one in the brick, N of them lie in it, and
+// q_a(n) = f_a + n D_a is sample n's coordinate in cells from the brick's
+// first cell.  inv = 1/D, off = -f inv: fma(c, inv, off) is the (real) n at
+// which the ray crosses face c.  For z, of which a brick has one layer, the
+// centred weight is fma(n, D_z, fz) itself.
+struct StagedRay {
+    float4 a;  // inv_x, off_x, inv_y, off_y
+    float4 b;  // D_x, D_y, D_z, f_z - 1/2
+    float2 c;  // N, residual
 };
 
-__device__ __forceinline__ BrickBox brick_box(const GridConst &gc, int bxi, int byi, int bzi) {
-    BrickBox b;
-    b.c0[0] = bxi * CB_X - 1;
-    b.c0[1] = byi * CB_Y - 1;
-    b.c0[2] = bzi * CB_Z - 1;
-    const int x1 = min(b.c0[0] + CB_X - 1, gc.nx - 1), y1 = min(b.c0[1] + CB_Y - 1, gc.ny - 1),
-              z1 = min(b.c0[2] + CB_Z - 1, gc.nz - 1);
-    b.lo[0] = gc.x0 + (float)b.c0[0] * gc.hx;
-    b.hi[0] = gc.x0 + (float)(x1 + 1) * gc.hx;
-    b.lo[1] = gc.y0 + (float)b.c0[1] * gc.hy;
-    b.hi[1] = gc.y0 + (float)(y1 + 1) * gc.hy;
-    b.lo[2] = gc.z0 + (float)b.c0[2] * gc.hz;
-    b.hi[2] = gc.z0 + (float)(z1 + 1) * gc.hz;
-    return b;
-}
-
-__global__ __launch_bounds__(256) void k_brick_rects(const ViewConst *__restrict__ views,
-                                                     DetConst dc, GridConst gc, int nu, int nv,
-                                                     int nbx, int nby, int nbz, int nviews,
-                                                     int4 *__restrict__ rects) {
-    const long long nb = (long long)nbx * nby * nbz;
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (t >= nb * nviews) return;
-    const int k = (int)(t / nb);
-    const int b = (int)(t - (long long)k * nb);
-    const int bxi = b % nbx, byi = (b / nbx) % nby, bzi = b / (nbx * nby);
-    const BrickBox bb = brick_box(gc, bxi, byi, bzi);
-    float umin, umax, vmin, vmax;
-    box_footprint(views[k], dc.sdd, bb.lo[0], bb.hi[0], bb.lo[1], bb.hi[1], bb.lo[2], bb.hi[2],
-                  umin, umax, vmin, vmax);
-    int i0, i1, j0, j1;
-    pixel_range(dc, nu, nv, umin, umax, vmin, vmax, i0, i1, j0, j1);
-    rects[t] = make_int4(i0, i1, j0, j1);
-}
-
-// Accumulate the samples of one ray (residual rv) that fall in the cell:
-// from the LDS entries (float data) or from the ray table (either type).
-__device__ __forceinline__ void visit_staged(float acc[8], const float cq[2], const float kw[2],
-                                             const StagedEntry &en, const RayRef &ray,
-                                             const double Qd[3], int cx, int cy, int cz) {
-    const StagedRange &er = en.rg;
-    const float lx = __builtin_fmaf(cq[0], er.inv[0], er.lo[0]);
-    const float ly = __builtin_fmaf(cq[1], er.inv[1], er.lo[1]);
-    const float hx = lx + __builtin_fmaf(fabsf(er.inv[0]), kw[0], 2e-3f);
-    const float hy = ly + __builtin_fmaf(fabsf(er.inv[1]), kw[1], 2e-3f);
-    const float lo = fmaxf(fmaxf(lx, ly), er.zlo);
-    const float hi = fminf(fminf(hx, hy), er.zhi);
-    if (!(lo <= hi)) return;
-    // first and last candidate sample, clamped as clamp_to_int clamps, kept
-    // in float (integers below 2^24 are exact)
-    const float n0 = __builtin_amdgcn_fmed3f(-floor_t(-lo), -4.0f, (float)(1 << 24));
-    const float n1 = __builtin_amdgcn_fmed3f(floor_t(hi), -4.0f, (float)(1 << 24));
-    if (!(n0 <= n1)) return;
-    const float sf = floor_t(n0 * (1.0f / SEG));  // segment number
-    const StagedWalk &e = en.wk;
-    SegOrigin o;
-    if ((int)sf == (int)e.sq) {
-        o.I[0] = e.I[0];
-        o.I[1] = e.I[1];
-        o.I[2] = e.I[2];
-        o.f[0] = e.f[0];
-        o.f[1] = e.f[1];
-        o.f[2] = e.f[2];
-    } else {
-        const PixelRay *gray = ray.get();
-        const double D[3] = {gray->D[0], gray->D[1], gray->D[2]};
-        o = seg_origin(Qd, D, (int)sf * SEG);
+// The ray with increment D and its residual rv as the brick's cells use it.
+//
+// Which samples lie in the brick is decided by the ray's face crossings
+// T(c) = (c - q) / D_f counted from sample n_mid (q the float coordinate of
+// that sample, the same for every brick): neighbouring bricks form the same
+// float for the face they share, so every sample is in exactly one brick,
+// and inside a brick in exactly one cell (crossing_sums), whatever the
+// rounding.  A sample within rounding of a face (6e-5 of a step at 512
+// voxels) may get the cell beside the exact one; its weights, formed from
+// its position in that cell, then differ from the exact ones by a second
+// order of that distance.
+__device__ __forceinline__ StagedRay stage_ray(const double D[3], const double Qd[3], int nmid,
+                                               const int c0[3], const int c1[3], float rv) {
+    StagedRay e;
+    double qm[3];
+    float Df[3], inv[3];
+    float lo = -8388608.0f, hi = 8388608.0f;  // 2^23: beyond every sample
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        qm[a] = __builtin_fma((double)nmid, D[a], Qd[a]);
+        const float q = (float)qm[a];
+        Df[a] = (float)D[a];
+        inv[a] = __builtin_amdgcn_rcpf(Df[a]);
+        const float t0 = ((float)c0[a] - q) * inv[a], t1 = ((float)c1[a] - q) * inv[a];
+        lo = fmaxf(lo, fminf(t0, t1));
+        hi = fminf(hi, fmaxf(t0, t1));
     }
-    const float Df[3] = {e.Df[0], e.Df[1], e.Df[2]};
-    cell_samples_f(acc, e.r, Qd, ray, o, sf, Df, __builtin_fmaf(sf, -(float)SEG, n0),
-                   __builtin_fmaf(sf, -(float)SEG, n1), cx, cy, cz);
+    lo = fminf(__builtin_ceilf(lo), 8388608.0f);
+    hi = __builtin_ceilf(hi);
+    float f[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        f[a] = (float)(__builtin_fma((double)lo, D[a], qm[a]) - (double)c0[a]);
+    e.a = make_float4(inv[0], -f[0] * inv[0], inv[1], -f[1] * inv[1]);
+    e.b = make_float4(Df[0], Df[1], Df[2], f[2] - 0.5f);
+    e.c = make_float2(fmaxf(hi - lo, 0.0f), rv);
+    return e;
 }
 
-template <typename T>
-__device__ __forceinline__ void visit_global(T acc[8], const CellRange &cr, const RayRef &ray,
-                                             T rv, const double Qd[3], int cx, int cy, int cz) {
-    const PixelRay *gray = ray.get();
-    const PixelRay g = *gray;
-    float inv[3];
-    ray_inv(g, inv);
-    int n0, n1;
-    if (!candidates_inv(cr, inv, n0, n1)) return;
-    const double D[3] = {g.D[0], g.D[1], g.D[2]};
-    if constexpr (sizeof(T) == 4) {
-        const int ns = n0 & ~(SEG - 1);
-        float Df[3];
-        to_float3(D, Df);
-        cell_samples_f(acc, rv, Qd, ray, seg_origin(Qd, D, ns), (float)(ns / SEG), Df,
-                       (float)(n0 - ns), (float)(n1 - ns), cx, cy, cz);
-    } else {
-        cell_samples_d(acc, rv, Qd, D, n0, n1, cx, cy, cz);
+// A lane's cell in its brick: face coordinates for the crossings (the
+// brick's own faces moved outward: there N decides), and the constants
+// c = (face 0) - (the cell's lower face) - 1/2 of the weights.  Face 0 is
+// the one the ray enters through when the directions of the rays are known
+// (ORDERED), else the lower one.
+struct CellFaces {
+    float x0, x1, y0, y1;
+    float cx, cy;
+};
+
+// a * b, and zero where either is zero, whatever the other: one instruction.
+__device__ __forceinline__ float mul_zero(float a, float b) {
+    float p;
+    asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(p) : "v"(a), "v"(b));
+    return p;
+}
+
+// Add the ray's samples in the cell to the moments m = sum r (1, x, y, z,
+// xy, xz, yz, xyz), x, y, z the weights minus 1/2.
+//
+// The samples of the crossing are n0 .. n1 - 1, k of them, equally spaced
+// along a line: with their mean position (x, y, z), increments D and
+// B = r k (k^2 - 1) / 12 = r sum (n - mean)^2, the third central moments
+// vanish by symmetry and
+//     sum r       = r k,             sum r x   = r k x,
+//     sum r x y   = r k x y + B Dx Dy,
+//     sum r x y z = r k x y z + B (Dx Dy z + Dx Dz y + Dy Dz x)
+// exactly.  No loop over the samples, so lanes whose rays have different
+// numbers of them in their cells do not wait for one another.
+//
+// A = r k by mul_zero: a residual that is not finite then adds nothing to
+// the cells its ray does not cross.
+template <bool ORDERED>
+__device__ __forceinline__ void crossing_sums(float m[8], const float4 ra, const float4 rb,
+                                              const float2 rc, const CellFaces &cf) {
+    const float tx0 = __builtin_fmaf(cf.x0, ra.x, ra.y), tx1 = __builtin_fmaf(cf.x1, ra.x, ra.y);
+    const float ty0 = __builtin_fmaf(cf.y0, ra.z, ra.w), ty1 = __builtin_fmaf(cf.y1, ra.z, ra.w);
+    const float n0 = __builtin_ceilf(
+        ORDERED ? fmaxf(fmaxf(tx0, ty0), 0.0f)
+                : fmaxf(fmaxf(fminf(tx0, tx1), fminf(ty0, ty1)), 0.0f));
+    const float n1 = __builtin_ceilf(
+        ORDERED ? fminf(fminf(tx1, ty1), rc.x)
+                : fminf(fminf(fmaxf(tx0, tx1), fmaxf(ty0, ty1)), rc.x));
+    const float k = fmaxf(n1 - n0, 0.0f);
+    const float n = __builtin_fmaf(0.5f, n0 + n1, -0.5f);
+    const float x = __builtin_fmaf(n - tx0, rb.x, cf.cx);
+    const float y = __builtin_fmaf(n - ty0, rb.y, cf.cy);
+    const float z = __builtin_fmaf(n, rb.z, rb.w);
+    const float A = mul_zero(rc.y, k);
+    const float B = A * __builtin_fmaf(k * k, 1.0f / 12.0f, -1.0f / 12.0f);
+    const float bx = B * rb.x, by = B * rb.y;
+    const float bxy = bx * rb.y, bxz = bx * rb.z, byz = by * rb.z;
+    const float px = A * x, py = A * y;
+    const float pxy = __builtin_fmaf(px, y, bxy);
+    m[0] += A;
+    m[1] += px;
+    m[2] += py;
+    m[3] = __builtin_fmaf(A, z, m[3]);
+    m[4] += pxy;
+    m[5] = __builtin_fmaf(px, z, m[5]) + bxz;
+    m[6] = __builtin_fmaf(py, z, m[6]) + byz;
+    m[7] = __builtin_fmaf(pxy, z, __builtin_fmaf(bxz, y, __builtin_fmaf(byz, x, m[7])));
+}
+
+// Corner sums (index ox + 2 oy + 4 oz): corner weights are the products of
+// 1/2 -+ x, 1/2 -+ y and 1/2 -+ z.
+__device__ __forceinline__ void moments_to_corners(const float m[8], float c[8]) {
+#pragma unroll
+    for (int o = 0; o < 8; ++o) {
+        const float sx = o & 1 ? 1.0f : -1.0f, sy = o & 2 ? 1.0f : -1.0f, sz = o & 4 ? 1.0f : -1.0f;
+        c[o] = 0.125f * m[0] + 0.25f * (sx * m[1] + sy * m[2] + sz * m[3]) +
+               0.5f * (sx * sy * m[4] + sx * sz * m[5] + sy * sz * m[6]) + sx * sy * sz * m[7];
     }
 }
 
-// Workgroups of 256 lanes, one per brick.  Seven share a CU: 22.9 KB of
-// LDS (60 bytes per staged pixel and the brick's projected corners) and at
-// most 72 VGPRs.
-template <typename T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_cells(const ViewConst *__restrict__ views, DetConst dc,
-                                               GridConst gc, int nu, int nv, int nviews,
-                                               const PixelRay *__restrict__ rays,
-                                               const int4 *__restrict__ rects,
-                                               const T *__restrict__ r, T *__restrict__ cells,
-                                               T step) {
-    __shared__ StagedEntry table[TABLE];
-    __shared__ float2 corner[(CB_X + 1) * (CB_Y + 1)];
+// Workgroups of 256 lanes, one per 16 x 16 x 1 brick of cells.
+//
+// Bound by VALU issue: a visit of a (ray, cell) pair is 42 VALU and 3 LDS
+// instructions (40 bytes a lane), of which fused multiply-adds take about
+// 2.8 cycles of a SIMD and min, max, ceil, compare, select and integer
+// instructions about 4.2 (measured with chains of each).  So what is not
+// arithmetic of the moments is kept out of the visits: no counters in the
+// lanes (blocks of W x H pixels), no test per sample, no order of the two
+// faces where the rays' directions are known; and out of the views: where
+// a cell projects is two affine maps, prepared.  Against the previous
+// kernel, which tested candidate samples one by one (117 VALU a sample with
+// the lanes' different counts): head transpose (512 x 512 x 70, 40 views)
+// 17.63 -> 8.34 ms, 256 x 256 x 64 / 60 views 3.87 -> 1.52, 128^3 / 60 views
+// 2.00 -> 0.87, 64^3 / 16 views 0.150 -> 0.081; 2.5 cycles an instruction.
+// Table of 560 rays: seven groups fill the LDS (22.4 KB) as the 68 VGPRs
+// allow; 480 rays 1.5% slower, 650 (six groups) 2%.  Up to six views a
+// batch: 1 to 2% over four.
+__global__ __launch_bounds__(256) void k_cells_f(
+    const ViewConst *__restrict__ views, GridConst gc, int nu, int nv, int nviews,
+    const PixelRay *__restrict__ rays, const BrickView *__restrict__ bviews,
+    const float *__restrict__ r, float *__restrict__ cells, float step) {
+    __shared__ float4 tab[2 * TABLE];
+    __shared__ float2 tabc[TABLE];
+    __shared__ int4 slots[PARTS];  // first entry, width, first pixel of the batch's views
+    static_assert(CB_Z == 1, "a brick is one z layer of cells");
     const int tid = threadIdx.x;
     // bricks x-fastest, then y, then z; each XCD takes one contiguous range,
     // so the bricks resident on an XCD at a time are neighbours whose
     // footprints (ray table rows) overlap in its L2
     const int nbx = (gc.nx + 1 + CB_X - 1) / CB_X, nby = (gc.ny + 1 + CB_Y - 1) / CB_Y;
-    const int nb = gridDim.x;
-    const int brick = xcd_tile(blockIdx.x, nb);
-    const BrickBox bb = brick_box(gc, brick % nbx, (brick / nbx) % nby, brick / (nbx * nby));
-    const int cx = bb.c0[0] + (tid % CB_X);
-    const int cy = bb.c0[1] + (tid / CB_X) % CB_Y;
-    const int cz = bb.c0[2] + tid / (CB_X * CB_Y);
-    const bool valid = cx < gc.nx && cy < gc.ny && cz < gc.nz;
-    // the brick's single z layer (CB_Z = 1): cell cz0 = blo[2] below
-    static_assert(CB_Z == 1, "the staged z bounds assume one z layer per brick");
-    T acc[8];
+    const int brick = xcd_tile(blockIdx.x, gridDim.x);
+    const BrickView *bv = bviews + (long long)brick * nviews;
+    const int c0[3] = {(brick % nbx) * CB_X - 1, ((brick / nbx) % nby) * CB_Y - 1,
+                       (brick / (nbx * nby)) * CB_Z - 1};
+    const int c1[3] = {min(c0[0] + CB_X, gc.nx), min(c0[1] + CB_Y, gc.ny), c0[2] + 1};
+    // A wavefront covers 8 x 8 cells, every 16 consecutive lanes 4 x 4 of
+    // them: the rays such lanes read together are then few and near each
+    // other in the table, whatever the view's direction.
+    const int lx = (tid & 3) | ((tid >> 2) & 4) | ((tid >> 3) & 8);
+    const int ly = ((tid >> 2) & 3) | ((tid >> 3) & 4) | ((tid >> 4) & 8);
+    float m[8];
 #pragma unroll
-    for (int o = 0; o < 8; ++o) acc[o] = T(0);
+    for (int o = 0; o < 8; ++o) m[o] = 0.0f;
 
+    for (int k = 0; k < nviews;) {
+        // the batch, or the parts of a view too large for the table: bands of
+        // rows, or pieces of a row
+        int n = bv[k].batch_n, total = bv[k].batch_rays;
+        const int dirs = bv[k].dirs;
+        int cols = 1, pw = 0, ph = 0, parts = 1;
+        if (n == 0) {
+            n = 1;
+            cols = (bv[k].w + TABLE - 1) / TABLE;
+            pw = (bv[k].w + cols - 1) / cols;
+            ph = min(TABLE / pw, bv[k].h);
+            parts = cols * ((bv[k].h + ph - 1) / ph);
+        }
+        for (int part = 0; part < parts; ++part) {
+            int oi = 0, oj = 0, w = bv[k].w, h = bv[k].h;  // the part within the view
+            if (parts > 1) {
+                oi = (part % cols) * pw;
+                oj = (part / cols) * ph;
+                w = max(min(pw, w - oi), 0);
+                h = min(ph, h - oj);
+                total = w * h;
+            }
+            if (tid < PARTS) {
+                int4 s = make_int4(0x7fffffff, 1, 0, 0);
+                if (tid < n) {
+                    const BrickView &b = bv[k + tid];
+                    s = make_int4(b.base, parts > 1 ? w : b.w, b.i0 + oi, b.j0 + oj);
+                }
+                slots[tid] = s;
+            }
+            __syncthreads();  // readers of the table are done, the slots are there
+            for (int t = tid; t < total; t += 256) {
+                // The brick's faces pass through an empty asm statement here
+                // and the lane's cell below: their conversions, formed where
+                // they are used, then take no registers across the loops.
+                int f0[3] = {c0[0], c0[1], c0[2]}, f1[3] = {c1[0], c1[1], c1[2]};
+                asm volatile("" : "+s"(f0[0]), "+s"(f0[1]), "+s"(f0[2]), "+s"(f1[0]),
+                                  "+s"(f1[1]), "+s"(f1[2]));
+                int v = 0;
+#pragma unroll
+                for (int q = 1; q < PARTS; ++q) v += t >= slots[q].x;
+                const int4 sl = slots[v];
+                // row of the view's entry e by a float reciprocal: exact
+                // below 2^13, since (e + 1/2)/w stays >= 1/(2 w) from an
+                // integer
+                const int e = t - sl.x;
+                const int row = (int)(((float)e + 0.5f) * rcp((float)sl.y));
+                const int col = e - row * sl.y;
+                const long long pix =
+                    ((long long)(k + v) * nv + (sl.w + row)) * nu + (sl.z + col);
+                const PixelRay g = rays[pix];
+                const ViewConst &vc = views[k + v];
+                const double Qd[3] = {vc.Qd[0], vc.Qd[1], vc.Qd[2]};
+                const StagedRay ray = stage_ray(g.D, Qd, vc.nmid, f0, f1, r[pix]);
+                tab[t] = ray.a;
+                tab[t + TABLE] = ray.b;
+                tabc[t] = ray.c;
+            }
+            __syncthreads();
+            int px = lx, py = ly;
+            asm volatile("" : "+v"(px), "+v"(py));
+            const float fx = (float)px, fy = (float)py;
+            // the brick's own faces moved outward
+            const float fx0 = px == 0 ? -0.25f : fx, fy0 = py == 0 ? -0.25f : fy;
+            const float fx1 = fx + (c0[0] + px + 1 == c1[0] ? 1.25f : 1.0f);
+            const float fy1 = fy + (c0[1] + py + 1 == c1[1] ? 1.25f : 1.0f);
+            CellFaces cf;
+            cf.x0 = dirs == 0 || (dirs & 1) ? fx0 : fx1;
+            cf.x1 = dirs == 0 || (dirs & 1) ? fx1 : fx0;
+            cf.y0 = dirs == 0 || (dirs & 2) ? fy0 : fy1;
+            cf.y1 = dirs == 0 || (dirs & 2) ? fy1 : fy0;
+            cf.cx = cf.x0 - fx - 0.5f;
+            cf.cy = cf.y0 - fy - 0.5f;
+            auto visit = [&](auto ordered) {
+                constexpr bool ORD = decltype(ordered)::value;
+                for (int v = 0; v < n; ++v) {
+                    const BrickView b = bv[k + v];
+                    const int bw = parts > 1 ? w : b.w, bh = parts > 1 ? h : b.h;
+                    if (bw == 0) continue;
+                    // Every lane visits a block of W x H pixels that holds its
+                    // cell's, moved inside the part: a ray that does not cross
+                    // a cell adds nothing to it, and loops without per-lane
+                    // counters are shorter.
+                    const int W = min(b.W, bw), H = min(b.H, bh);
+                    const int ci = (int)__builtin_ceilf(b.a0 + b.ax * fx + b.ay * fy) - oi;
+                    const int cj = (int)__builtin_ceilf(b.b0 + b.bx * fx + b.by * fy) - oj;
+                    if (parts > 1 && !__builtin_amdgcn_ballot_w64(ci + b.W > 0 && ci < bw &&
+                                                                  cj + b.H > 0 && cj < bh))
+                        continue;
+                    const int e =
+                        b.base + max(min(cj, bh - H), 0) * bw + max(min(ci, bw - W), 0);
+                    const float4 *p = tab + e;
+                    const float2 *pc = tabc + e;
+                    for (int y = 0; y < H; ++y, p += bw, pc += bw) {
+                        int x = 0;
+                        for (; x + 1 < W; x += 2) {
+                            crossing_sums<ORD>(m, p[x], p[x + TABLE], pc[x], cf);
+                            crossing_sums<ORD>(m, p[x + 1], p[x + 1 + TABLE], pc[x + 1], cf);
+                        }
+                        if (x < W) crossing_sums<ORD>(m, p[x], p[x + TABLE], pc[x], cf);
+                    }
+                }
+            };
+            if (dirs)
+                visit(std::true_type());
+            else
+                visit(std::false_type());
+        }
+        k += n;
+    }
+    if (c0[0] + lx >= c1[0] || c0[1] + ly >= c1[1]) return;
+    const long long cp = cell_pitch(gc.nx);
+    const long long ncell = cp * (gc.ny + 1) * (gc.nz + 1);
+    const long long lin = (long long)(c0[0] + 1 + lx) +
+                          cp * ((c0[1] + 1 + ly) + (long long)(gc.ny + 1) * (c0[2] + 1));
+    float out[8];
+    moments_to_corners(m, out);
+#pragma unroll
+    for (int o = 0; o < 8; ++o) cells[o * ncell + lin] = out[o] * step;
+}
+
+// Double pass 1 (derivative checks): every candidate sample of every pixel
+// of the cell's rectangle, in double, from the ray table.
+__global__ __launch_bounds__(256) void k_cells_d(const ViewConst *__restrict__ views, DetConst dc,
+                                                 GridConst gc, int nu, int nv, int nviews,
+                                                 const PixelRay *__restrict__ rays,
+                                                 const BrickView *__restrict__ bviews,
+                                                 const double *__restrict__ r,
+                                                 double *__restrict__ cells, double step) {
+    const int tid = threadIdx.x;
+    const int nbx = (gc.nx + 1 + CB_X - 1) / CB_X, nby = (gc.ny + 1 + CB_Y - 1) / CB_Y;
+    const int brick = xcd_tile(blockIdx.x, gridDim.x);
+    const int cx = (brick % nbx) * CB_X - 1 + tid % CB_X;
+    const int cy = ((brick / nbx) % nby) * CB_Y - 1 + (tid / CB_X) % CB_Y;
+    const int cz = (brick / (nbx * nby)) * CB_Z - 1 + tid / (CB_X * CB_Y);
+    if (cx >= gc.nx || cy >= gc.ny || cz >= gc.nz) return;
+    // the cell's box (mm)
+    const float xa = gc.x0 + (float)cx * gc.hx, xb = gc.x0 + (float)(cx + 1) * gc.hx;
+    const float ya = gc.y0 + (float)cy * gc.hy, yb = gc.y0 + (float)(cy + 1) * gc.hy;
+    const float za = gc.z0 + (float)cz * gc.hz, zb = gc.z0 + (float)(cz + 1) * gc.hz;
+    double acc[8];
+#pragma unroll
+    for (int o = 0; o < 8; ++o) acc[o] = 0.0;
     for (int k = 0; k < nviews; ++k) {
-        // Per-view copies of brick and lane constants.  They are formed
-        // again in every view from copies passed through an empty asm
-        // statement: held across the view loop instead, they would be
-        // spilled under the register budget.
-        int c0[3] = {bb.c0[0], bb.c0[1], bb.c0[2]}, lx = cx, ly = cy;
-        asm volatile("" : "+s"(c0[0]), "+s"(c0[1]), "+s"(c0[2]), "+v"(lx), "+v"(ly));
-        // the brick in index coordinates: cells c0 .. c1 cover [c0, c1 + 1)
-        const float blo[3] = {(float)c0[0], (float)c0[1], (float)c0[2]};
-        const float bhi[3] = {(float)min(c0[0] + CB_X, gc.nx), (float)min(c0[1] + CB_Y, gc.ny),
-                              (float)min(c0[2] + CB_Z, gc.nz)};
-        // this lane's cell faces in z (same expressions as the brick box)
-        const float za = gc.z0 + (float)cz * gc.hz, zb = gc.z0 + (float)(cz + 1) * gc.hz;
-        const float cxf = (float)lx, cyf = (float)ly, czf = (float)cz;
-        // largest |c_a| over the brick's cells, for the staged range margins
-        const float cmax[3] = {fmaxf(fabsf(blo[0]), fabsf(bhi[0])),
-                               fmaxf(fabsf(blo[1]), fabsf(bhi[1])),
-                               fmaxf(fabsf(blo[2]), fabsf(bhi[2]))};
         const ViewConst vc = views[k];
         const long long vbase = (long long)k * nu * nv;
-        const T *rk = r + vbase;
-        const PixelRay *raysk = rays + vbase;
-        // the brick's footprint, identical in every lane
-        const int4 rect = rects[(long long)k * nb + brick];
-        const int bi0 = rect.x, bi1 = rect.y, bj0 = rect.z, bj1 = rect.w;
-        const int bw = bi1 - bi0 + 1, bh = bj1 - bj0 + 1;
-        if (bw <= 0 || bh <= 0) continue;  // uniform: the brick misses the detector
-        // float data stages the footprint in LDS; double reads the ray
-        // table and the residual at full precision from memory
-        const bool staged = sizeof(T) == 4 && bw * bh <= TABLE;
-        __syncthreads();  // readers of the previous view are done
-        // the brick's (CB_X + 1) x (CB_Y + 1) cell corners in the xy plane,
-        // projected: u / sdd and 1 / depth (the corner expressions of
-        // box_footprint, shared by the cells of every layer)
-        for (int t = tid; t < (CB_X + 1) * (CB_Y + 1); t += 256) {
-            const int a = t % (CB_X + 1), b = t / (CB_X + 1);
-            const float x = gc.x0 + (float)(bb.c0[0] + a) * gc.hx;
-            const float y = gc.y0 + (float)(bb.c0[1] + b) * gc.hy;
-            const float wx = x - vc.src[0], wy = y - vc.src[1];
-            const float n = wx * vc.cs + wy * vc.sn, d = wy * vc.cs - wx * vc.sn;
-            const float ri = rcp(d);
-            corner[t] = make_float2(n * ri, ri);
-        }
-        if (staged) {
-            // element t -> (row, col) by a float reciprocal: exact for
-            // t < 2^13, since (t + 1/2)/bw stays >= 1/(2 bw) from an integer
-            const float ibw = 1.0f / (float)bw;
-            int t0 = tid;
-            asm volatile("" : "+v"(t0));
-            for (int t = t0; t < bw * bh; t += 256) {
-                const int row = (int)(((float)t + 0.5f) * ibw);
-                const int col = t - row * bw;
-                const long long pix = (long long)(bj0 + row) * nu + (bi0 + col);
-                const PixelRay g = raysk[pix];
-                float ginv[3];
-                ray_inv(g, ginv);
-                // first sample of the ray in the brick (a float estimate:
-                // it only picks which segment origin to prepare)
-                float tin = -3.0e38f;
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    const float t0 = (blo[a] - vc.Q[a]) * ginv[a];
-                    const float t1 = (bhi[a] - vc.Q[a]) * ginv[a];
-                    tin = fmaxf(tin, fminf(t0, t1));
-                }
-                const int sb = max(clamp_to_int(floor_t(tin)), 0) & ~(SEG - 1);
-                const SegOrigin o = seg_origin(vc.Qd, g.D, sb);
-                StagedRange er;
-                StagedWalk ew;
-#pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    const float inv = ginv[a];
-                    const float m = __builtin_fmaf(
-                        4e-6f * (fabsf(vc.Q[a]) + cmax[a] + 1.0f), fabsf(inv), 1e-3f);
-                    er.inv[a] = inv;
-                    er.lo[a] = fminf(0.0f, inv) - m;
-                }
-                {
-                    // the z layer's bounds, as a cell of the layer would
-                    // compute them (cq = cz0 - Q_z in float)
-                    const float inv = ginv[2];
-                    const float t0 = (blo[2] - vc.Q[2]) * inv, t1 = t0 + inv;
-                    const float m = __builtin_fmaf(
-                        4e-6f * (fabsf(vc.Q[2]) + cmax[2] + 1.0f), fabsf(inv), 1e-3f);
-                    er.zlo = fminf(t0, t1) - m;
-                    er.zhi = fmaxf(t0, t1) + m;
-                }
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    ew.I[a] = (short)o.I[a];
-                    ew.f[a] = o.f[a];
-                    ew.Df[a] = (float)g.D[a];
-                }
-                // 32767 marks "no staged origin" (the plan bounds real
-                // sample indices below 32767 * SEG)
-                ew.sq = (short)min(sb / SEG, 32767);
-                ew.r = (float)rk[pix];
-                table[t].rg = er;
-                table[t].wk = ew;
-            }
-        }
-        __syncthreads();
-        if (!valid) continue;
-        // the cell's detector rectangle from its four xy corners (u) and
-        // the extreme depths at its z faces (v), as box_footprint does
-        const int cc = (cy - bb.c0[1]) * (CB_X + 1) + (cx - bb.c0[0]);
-        const float2 k00 = corner[cc], k10 = corner[cc + 1];
-        const float2 k01 = corner[cc + CB_X + 1], k11 = corner[cc + CB_X + 2];
-        const float umin = dc.sdd * fminf(fminf(k00.x, k10.x), fminf(k01.x, k11.x));
-        const float umax = dc.sdd * fmaxf(fmaxf(k00.x, k10.x), fmaxf(k01.x, k11.x));
-        const float ia = fmaxf(fmaxf(k00.y, k10.y), fmaxf(k01.y, k11.y));  // 1 / nearest
-        const float ib = fminf(fminf(k00.y, k10.y), fminf(k01.y, k11.y));  // 1 / farthest
-        const float v0 = za * ia, v1 = za * ib, v2 = zb * ia, v3 = zb * ib;
-        const float vmin = dc.sdd * fminf(fminf(v0, v1), fminf(v2, v3));
-        const float vmax = dc.sdd * fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
+        const BrickView &rect = bviews[(long long)brick * nviews + k];
+        float umin, umax, vmin, vmax;
+        box_footprint(vc, dc.sdd, xa, xb, ya, yb, za, zb, umin, umax, vmin, vmax);
         int i0, i1, j0, j1;
         pixel_range(dc, nu, nv, umin, umax, vmin, vmax, i0, i1, j0, j1);
         // the cell lies in the brick: keep its pixels inside the brick's
         // rectangle (they differ at most by rounding, inside the margin)
-        i0 = max(i0, bi0);
-        i1 = min(i1, bi1);
-        j0 = max(j0, bj0);
-        j1 = min(j1, bj1);
+        i0 = max(i0, rect.i0);
+        i1 = min(i1, rect.i0 + rect.w - 1);
+        j0 = max(j0, rect.j0);
+        j1 = min(j1, rect.j0 + rect.h - 1);
         const float Qf[3] = {vc.Q[0], vc.Q[1], vc.Q[2]};
-        const CellRange cr = cell_range(Qf, cxf, cyf, czf);
-        // 1 + 2 K_a of the staged margins (x, y)
-        const float kw[2] = {1.0f + 8e-6f * (fabsf(vc.Q[0]) + cmax[0] + 1.0f),
-                             1.0f + 8e-6f * (fabsf(vc.Q[1]) + cmax[1] + 1.0f)};
-        // One flat loop over the cell's rectangle (nearly its exact
-        // footprint): lanes with rectangles of different shapes then
-        // diverge only in the total pixel count.
+        const CellRange cr = cell_range(Qf, (float)cx, (float)cy, (float)cz);
         const int w = i1 - i0 + 1, h = j1 - j0 + 1;
         const int npix = (w > 0 && h > 0) ? w * h : 0;
         int i = i0, j = j0;
-        if constexpr (sizeof(T) == 4) {
-            if (staged) {
-                // the entry of pixel (i, j): a pointer advanced along the
-                // rectangle (no per-visit multiplications)
-                const StagedEntry *pe = table + (j0 - bj0) * bw + (i0 - bi0);
-                const int skip = bw - w;  // from a row's end to the next row's start
-                if (npix > 0) {
-                    for (;;) {
-                        const RayRef ray{raysk, nu, i, j};
-                        visit_staged(acc, cr.cq, kw, *pe, ray, vc.Qd, cx, cy, cz);
-                        ++pe;
-                        if (++i > i1) {
-                            if (++j > j1) break;
-                            i = i0;
-                            pe += skip;
-                        }
-                    }
-                }
-                continue;
-            }
-        }
         for (int q = 0; q < npix; ++q) {
-            const RayRef ray{raysk, nu, i, j};
-            const long long pix = (long long)j * nu + i;
+            const long long pix = vbase + (long long)j * nu + i;
             if (++i > i1) {
                 i = i0;
                 ++j;
             }
-            visit_global<T>(acc, cr, ray, rk[pix], vc.Qd, cx, cy, cz);
+            const PixelRay g = rays[pix];
+            float inv[3];
+            ray_inv(g, inv);
+            int n0, n1;
+            if (!candidates_inv(cr, inv, n0, n1)) continue;
+            cell_samples_d(acc, r[pix], vc.Qd, g.D, n0, n1, cx, cy, cz);
         }
     }
-    if (!valid) return;
-    // The cell's index is formed again from the launch coordinates (passed
-    // through an empty asm statement so the compiler does not keep the
-    // first computation alive across the view loop, where it would spill).
-    int b = (int)blockIdx.x, t = tid;
-    asm volatile("" : "+v"(t), "+s"(b));
-    const int br = xcd_tile(b, nb);
-    const int ox = (br % nbx) * CB_X + t % CB_X;                       // cx + 1
-    const int oy = ((br / nbx) % nby) * CB_Y + (t / CB_X) % CB_Y;      // cy + 1
-    const int oz = (br / (nbx * nby)) * CB_Z + t / (CB_X * CB_Y);      // cz + 1
     const long long cp = cell_pitch(gc.nx);
     const long long ncell = cp * (gc.ny + 1) * (gc.nz + 1);
-    const long long lin = (long long)ox + cp * (oy + (long long)(gc.ny + 1) * oz);
-    T out[8];
-    if constexpr (sizeof(T) == 4) {
-        moments_to_corners(acc, out);
-    } else {
+    const long long lin = (long long)(cx + 1) +
+                          cp * ((cy + 1) + (long long)(gc.ny + 1) * (cz + 1));
 #pragma unroll
-        for (int o = 0; o < 8; ++o) out[o] = acc[o];
-    }
-#pragma unroll
-    for (int o = 0; o < 8; ++o) cells[o * ncell + lin] = out[o] * step;
+    for (int o = 0; o < 8; ++o) cells[o * ncell + lin] = acc[o] * step;
 }
 
 // Pass 2: out = sum of corner o of cell (v - o) over o in {0,1}^3,
@@ -782,16 +797,16 @@ dim3 brick_grid(const cbct_geom &g) {
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Geometry tables of the transpose: the ray table at offset 0, then the
-// brick rectangles.
+// bricks' views.
 struct GeomLayout {
-    size_t rects, total;  // byte offsets
+    size_t bricks, total;  // byte offsets
 };
 
 GeomLayout geom_layout(const cbct_geom &g) {
     const dim3 b = brick_grid(g);
     GeomLayout l;
-    l.rects = align256(sizeof(PixelRay) * (size_t)g.n_views * g.nu * g.nv);
-    l.total = l.rects + sizeof(int4) * (size_t)b.x * b.y * b.z * g.n_views;
+    l.bricks = align256(sizeof(PixelRay) * (size_t)g.n_views * g.nu * g.nv);
+    l.total = l.bricks + sizeof(BrickView) * (size_t)b.x * b.y * b.z * g.n_views;
     return l;
 }
 
@@ -826,10 +841,9 @@ hipError_t launch_bp_prepare(const cbct_plan &p, void *geom, hipStream_t s) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 b = brick_grid(p.g);
-    const long long n = (long long)b.x * b.y * b.z * p.g.n_views;
-    hipLaunchKernelGGL(k_brick_rects, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                       p.d_views, p.det, p.grid, p.g.nu, p.g.nv, (int)b.x, (int)b.y, (int)b.z,
-                       p.g.n_views, (int4 *)(base + l.rects));
+    hipLaunchKernelGGL(k_brick_views, dim3(b.x * b.y * b.z), dim3(64), 0, s, p.d_views, p.det,
+                       p.grid, p.g.hx, p.g.hy, p.g.hz, p.g.nu, p.g.nv, (int)b.x, (int)b.y,
+                       p.g.n_views, (BrickView *)(base + l.bricks));
     return hipGetLastError();
 }
 
@@ -839,9 +853,15 @@ hipError_t launch_backproject_cells(const cbct_plan &p, const T *r, void *cells,
     const GeomLayout l = geom_layout(p.g);
     const char *base = (const char *)geom;
     const dim3 b = brick_grid(p.g);
-    hipLaunchKernelGGL(k_cells<T>, dim3(b.x * b.y * b.z), dim3(256), 0, s, p.d_views, p.det, p.grid,
-                       p.g.nu, p.g.nv, p.g.n_views, (const PixelRay *)base,
-                       (const int4 *)(base + l.rects), r, (T *)cells, (T)p.g.step);
+    const dim3 grid(b.x * b.y * b.z);
+    const PixelRay *rays = (const PixelRay *)base;
+    const BrickView *bv = (const BrickView *)(base + l.bricks);
+    if constexpr (sizeof(T) == 4)
+        hipLaunchKernelGGL(k_cells_f, grid, dim3(256), 0, s, p.d_views, p.grid, p.g.nu, p.g.nv,
+                           p.g.n_views, rays, bv, r, (T *)cells, (T)p.g.step);
+    else
+        hipLaunchKernelGGL(k_cells_d, grid, dim3(256), 0, s, p.d_views, p.det, p.grid, p.g.nu,
+                           p.g.nv, p.g.n_views, rays, bv, r, (T *)cells, (T)p.g.step);
     return hipGetLastError();
 }
 

@@ -31,6 +31,7 @@ struct ViewConst {
     double Qd[3];  // the same constants in double for the FP64 kernels
     double Wd[2], Ud[2], Vzd;
     double csd, snd;  // cos(theta), sin(theta) in double
+    int nmid;         // sample index at the grid centre's distance from the source
 };
 
 // The dispatcher hands the workgroups of a launch to the 8 XCDs of the chip

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void k_pad(const T *__restrict__ f, T *__restr
     }
 }
 
-// Cell of sample n (the definition shared with the transpose).
+// Cell of sample n.
 template <typename T>
 __device__ __forceinline__ void sample_cell(const double Q[3], const double D[3],
                                             const float Df[3], int n, int c[3]) {
@@ -212,8 +212,8 @@ __device__ __forceinline__ float staged_samples(const float *vol, int base, int 
 // volume is loaded straight into LDS (buffer loads to LDS, one z plane at a
 // time) and the eight trilinear taps of every sample are read from LDS; an
 // unfitting chunk reads its taps from global memory.  The samples, their
-// cells and weights are exactly those of sample_cell and seg_axis (the
-// definitions the transpose shares), whatever the chunking.  A square tile
+// cells and weights are exactly those of sample_cell and seg_axis,
+// whatever the chunking.  A square tile
 // keeps the bundle, and so the box, narrow in both detector directions.
 // Where a tile spans many cells (pixels near the voxel size) single pieces
 // still fit; where it spans few, runs spread the per-chunk staging and

@@ -1,17 +1,15 @@
 // Ray and sample arithmetic shared by the projector and its transpose.
 //
-// Both kernels must agree on which interpolation cell every sample falls
-// in, so the sample coordinate is produced by one function, with floating
-// point contraction disabled and explicit fused multiply-adds, and the cell
-// is always floor() of that coordinate.  Then the gather-form transpose
-// enumerates exactly the (ray, sample) pairs the projector visits.
+// Both use the same rays and the same samples.  A sample on a cell's face
+// has the same weights from both of its cells, so each may decide by its own
+// rounding to which one a sample within rounding of a face belongs, as long
+// as it gives every sample to exactly one.
 //
 // Sample coordinates are computed in double precision whatever the data
 // type: a sample about 1000 mm from the source needs its direction to
 // ~1e-9 relative to land within 1e-5 voxel of its true position, beyond
 // float's 24-bit mantissa.  Double FMA, floor and convert run at the same
-// vector rate as non-packed float on gfx950.  The float variant of
-// ray_setup only feeds conservative range estimates.
+// vector rate as non-packed float on gfx950.
 #pragma once
 
 #include "cbct_internal.hpp"
@@ -20,21 +18,6 @@ namespace cbct {
 
 // Index-space origin Q and per-sample increment D of the ray through
 // pixel (i, j) of view vc (see ViewConst).
-__device__ __forceinline__ void ray_setup(const ViewConst &vc, const DetConst &dc, int i, int j,
-                                          float Q[3], float D[3]) {
-#pragma clang fp contract(off)
-    const float u = __builtin_fmaf((float)i, dc.au, dc.u0);
-    const float v = __builtin_fmaf((float)j, dc.av, dc.v0);
-    const float l2 = __builtin_fmaf(u, u, __builtin_fmaf(v, v, dc.sdd2));
-    const float inv = __builtin_amdgcn_rsqf(l2);
-    D[0] = __builtin_fmaf(u, vc.U[0], vc.W[0]) * inv;
-    D[1] = __builtin_fmaf(u, vc.U[1], vc.W[1]) * inv;
-    D[2] = (v * vc.Vz) * inv;
-    Q[0] = vc.Q[0];
-    Q[1] = vc.Q[1];
-    Q[2] = vc.Q[2];
-}
-
 __device__ __forceinline__ void ray_setup(const ViewConst &vc, const DetConst &dc, int i, int j,
                                           double Q[3], double D[3]) {
 #pragma clang fp contract(off)
@@ -62,10 +45,7 @@ __device__ __forceinline__ void ray_setup(const ViewConst &vc, const DetConst &d
 // cell = I + floor(l), weight = l - floor(l).  With the default step
 // (|D_a| <= 1/2) |l| stays below SEG/2 + 1 = 129, so float keeps the
 // position to ~1.5e-5 voxel (one rounding of l plus the rounding of D_f
-// over 256 steps), and the double work is paid once per segment.  Long
-// segments matter to the transpose: the samples of one ray inside one
-// brick of cells (at most ~33 of them) nearly always share a segment,
-// whose origin can then be prepared once per pixel and brick.
+// over 256 steps), and the double work is paid once per segment.
 //
 // Double data (derivative checks): q = fma(n, D, Q) in double per sample.
 constexpr int SEG = 256;
@@ -106,9 +86,6 @@ __device__ __forceinline__ void to_float3(const double D[3], float Df[3]) {
 }
 
 // Voxel-index coordinate of sample n along one axis.
-__device__ __forceinline__ float sample_coord(float n, float D, float Q) {
-    return __builtin_fmaf(n, D, Q);
-}
 __device__ __forceinline__ double sample_coord(double n, double D, double Q) {
     return __builtin_fma(n, D, Q);
 }
@@ -139,29 +116,6 @@ __device__ __forceinline__ bool axis_interval(T Q, T D, T a, T b, T &lo, T &hi) 
     lo = T(-1e30);
     hi = T(1e30);
     return Q >= a && Q < b;
-}
-
-// Conservative float estimate of the sample indices whose coordinate along
-// one axis lies in [a, a + 1), for a ray given in float (Q, D).  The float
-// ray differs from the double one by at most ~1e-6 relative in Q and D, so
-// the true bounds (a - Q)/D move by at most 1e-6 (|Q| + |a| + 1) / |D|;
-// the interval is widened by four times that plus 1e-3.  Returns false
-// when no sample can have that coordinate.
-__device__ __forceinline__ bool axis_estimate(float Q, float D, float a, float &lo, float &hi) {
-    if (D == 0.0f) {
-        lo = -1e30f;
-        hi = 1e30f;
-        // q = Q exactly for every n in double too (D is exactly zero there
-        // only when the double D is zero as well: both come from u = 0 or
-        // v = 0 for the same pixel)
-        return Q >= a - 1e-3f && Q < a + 1.0f + 1e-3f;
-    }
-    const float inv = __builtin_amdgcn_rcpf(D);
-    const float m = 1e-3f + 4e-6f * (fabsf(Q) + fabsf(a) + 1.0f) * fabsf(inv);
-    const float t0 = (a - Q) * inv, t1 = (a + 1.0f - Q) * inv;
-    lo = fminf(t0, t1) - m;
-    hi = fmaxf(t0, t1) + m;
-    return true;
 }
 
 // Clamp a real sample index into a range safe for int conversion.
