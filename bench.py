@@ -556,19 +556,19 @@ def main():
 
     # per-kernel algorithmic work over the timed region
     nvox_f, nvox_c = g.n_vox, plan_c.geom.nx * plan_c.geom.ny * plan_c.geom.nz
-    tv_launches = list(rep.n_inner_used)  # one launch per inner step
-    sweeps = tv_launches[0] * iters[0] * nvox_c + tv_launches[1] * iters[1] * nvox_f
+    n_inner = list(rep.n_inner_used)
+    sweeps = n_inner[0] * iters[0] * nvox_c + n_inner[1] * iters[1] * nvox_f
     work = {
         "project": ("alu", FLOPS_PER_SAMPLE * (iters[0] * s_c + (iters[1] + 1) * s_f)),
         "cells": ("alu", FLOPS_PER_SAMPLE * (iters[0] * s_c + iters[1] * s_f)),
         "tv_sweep": ("hbm", TV_BYTES_PER_VOXEL * sweeps),
         "gather": ("hbm", 4.0 * (8 + 1 + 1) * (iters[0] * nvox_c + iters[1] * nvox_f)),
     }
-    # launches per level (coarse, fine) of each kernel in one solve
+    # launches per level (coarse, fine) of each kernel in one solve (a TV
+    # launch makes one to three steps)
     mix = {
         "project": (iters[0], iters[1] + 1),
         "cells": (iters[0], iters[1]),
-        "tv_sweep": (tv_launches[0] * iters[0], tv_launches[1] * iters[1]),
         "gather": (iters[0], iters[1]),
     }
     per_kernel = {k: {"launches": n, "ms_per_step": tot} for k, (n, tot) in kall.items()}

@@ -280,7 +280,7 @@ size_t cbct_fbs_footprint(const cbct_geom *g, const cbct_fbs_params *prm);
 #define CBCT_KERNEL_PROJECT 1    /* ray march (P, optionally P f - Y) */
 #define CBCT_KERNEL_CELLS 2      /* P^T pass 1: per-cell corner sums */
 #define CBCT_KERNEL_GATHER 3     /* P^T pass 2: per-voxel sum (+ Step 1) */
-#define CBCT_KERNEL_TV_SWEEP 4   /* one projected TV gradient step */
+#define CBCT_KERNEL_TV_SWEEP 4   /* one to three projected TV gradient steps */
 #define CBCT_KERNEL_TV_ENERGY 5  /* E1 partial sums */
 #define CBCT_KERNEL_OTHER 6      /* reductions, fills, transfers */
 #define CBCT_KERNEL_EQ2 7        /* Eq. (2) gradient (+ Step 1) */

@@ -551,16 +551,25 @@ int default_inner(const cbct_geom &g, double beta, double eps) {
     return k > 200.0 ? 200 : (int)k;
 }
 
-// K sweeps from z0 = f (in place), ping-ponging with `tmp` (nvox floats).
+// n_inner steps from z0 = f (in place), ping-ponging with `tmp` (nvox floats):
+// one launch and a copy back for as many steps as a launch makes, else an
+// even number of launches, so that the last one writes f, with the steps
+// spread evenly over them.
 // `timing` = false launches without the diagnostic HIP events (whose
 // creation the no-allocation entry point must not make).
 int prox_sweeps(const GridConst &gc, size_t nvox, const float *g, float *f, float *tmp,
                 double beta, double eps, int n_inner, double step, int nonneg, hipStream_t s,
                 bool timing = true) {
     float *a = f, *b = tmp;
-    for (int m = 0; m < n_inner; ++m) {
+    const int most = tv_steps_per_launch(gc);
+    const int launches = n_inner <= most || most == 1
+                             ? (n_inner + most - 1) / most
+                             : 2 * (int)((n_inner + 2LL * most - 1) / (2 * most));
+    for (int m = 0; m < launches; ++m) {
+        const int steps = n_inner / launches + (m < n_inner % launches ? 1 : 0);
         auto launch = [&] {
-            return launch_tv_sweep(gc, a, g, b, (float)beta, (float)eps, (float)step, nonneg, s);
+            return launch_tv_steps(gc, a, g, b, (float)beta, (float)eps, (float)step, nonneg,
+                                   steps, s);
         };
         int rc = check_hip(timing ? timed(CBCT_KERNEL_TV_SWEEP, s, launch) : launch(),
                            "tv sweep");

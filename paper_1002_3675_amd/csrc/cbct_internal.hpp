@@ -136,8 +136,12 @@ size_t project_partials_count(const cbct_plan &p);
 size_t project_partials_count(const cbct_geom &g);
 size_t padded_count(const cbct_plan &p);
 
-hipError_t launch_tv_sweep(const GridConst &gc, const float *z, const float *g, float *out,
-                           float beta, float eps, float step, int nonneg, hipStream_t s);
+// One launch makes 1 .. 3 projected gradient steps (only 1 where
+// tv_steps_per_launch, the most that pay on this grid, is 1).
+int tv_steps_per_launch(const GridConst &gc);
+hipError_t launch_tv_steps(const GridConst &gc, const float *z, const float *g, float *out,
+                           float beta, float eps, float step, int nonneg, int steps,
+                           hipStream_t s);
 hipError_t launch_tv_energy(const GridConst &gc, const float *z, double eps,
                             double *partials, int *n_partials, hipStream_t s);
 hipError_t launch_reduce_sum(const double *partials, int n, double *out, int n_out_cols,

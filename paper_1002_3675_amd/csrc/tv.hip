@@ -3,15 +3,11 @@
 //
 // D_a z = (z[v + e_a] - z[v]) / h_a (zero at the last index of axis a) and
 // D^T p = sum_a ([i_a > 0] p_a[v - e_a] - [i_a < N_a - 1] p_a[v]) / h_a.
-// The update at v needs p = Dz/|Dz|_eps at v and at v - e_a.  The sweep is
-// HBM-bound (12 bytes per voxel: read z and g, write z).  A workgroup owns a
-// 32 x 8 column of voxels and marches a chunk of z planes: each plane of z
-// (with a one-voxel halo) is staged once in LDS, p is computed once per
-// position of the tile and its low halo, and p_z of the plane below stays
-// in a register, so every voxel costs one read of z and g, one write, and
-// one reciprocal square root.  Arrays whose rows are a multiple of 4 voxels
-// and 16-byte aligned take k_tv_sweep4 (one wavefront per tile, four voxels
-// per lane, 16-byte loads and stores); others take the 256-lane k_tv_sweep.
+// The update at v needs p = Dz/|Dz|_eps at v and at v - e_a.  One step a
+// launch moves 12 bytes per voxel (z and g in, z out) and on small grids
+// costs a launch's latency; k_tv_steps makes up to three steps of a box a
+// launch, in registers and LDS.  Rows too long for its offsets take
+// k_tv_sweep, one step a launch.
 #include "cbct_internal.hpp"
 
 namespace cbct {
@@ -25,6 +21,15 @@ constexpr int ST_Z = 16;            // longest z chunk
 // A sweep should put at least this many workgroups in flight (8 per CU):
 // grids with few 32 x 8 columns get shorter z chunks.
 constexpr int SWEEP_MIN_GROUPS = 2048;
+
+// Boxes of k_tv_steps (planes for launches of one step and of more), and the
+// grids by number of steps a launch.  Measured, us a step (512 x 512 x 70 /
+// 256 x 256 x 64 / 128^3 / 64^3): two steps a launch 32 / 9.3 / 6.0 / 3.1,
+// three 40 / 10.5 / 6.1 / 2.3; a grid of 500 000 voxels takes 3.2 either way,
+// one of a million 4.2 with two and 3.9 with three.
+constexpr int BOX_X = 32, BOX_Y = 16, BOX_Z1 = 10, BOX_Z = 12;
+constexpr int TV_MAX_NX = 1 << 24;         // rows beyond it take k_tv_sweep
+constexpr long long TV_LARGE = 1500000;    // voxels from which two steps a launch beat three
 
 struct TvArgs {
     int nx, ny, nz;
@@ -56,8 +61,9 @@ __device__ __forceinline__ SweepTile sweep_tile(const TvArgs &a, int b) {
     return t;
 }
 
-// One projected gradient step on a 32 x 8 tile marching a chunk of planes.
-// Plane k + 2 is fetched into registers while plane k is processed.
+// One projected gradient step on a 32 x 8 tile marching a chunk of planes
+// (grids of any row length, 64-bit addresses).  Plane k + 2 is fetched into
+// registers while plane k is processed.
 __global__ __launch_bounds__(256) void k_tv_sweep(TvArgs a, const float *__restrict__ z,
                                                   const float *__restrict__ g,
                                                   float *__restrict__ out, float beta, float step,
@@ -150,151 +156,119 @@ __global__ __launch_bounds__(256) void k_tv_sweep(TvArgs a, const float *__restr
     }
 }
 
-// The same step with 16-byte accesses: one wavefront per 32 x 8 tile, each
-// lane owning four consecutive x voxels of one row (nx a multiple of 4,
-// arrays 16-byte aligned).  z planes are staged in LDS with float4 loads
-// (plus the two x-halo columns), g is read and the result written as
-// float4, and the barriers are those of a single wavefront.  The
-// arithmetic per voxel is that of k_tv_sweep, in the same order.
-constexpr int W_X = 32, W_Y = 8;  // tile
-constexpr int W_PITCH = 40;       // LDS row: column 3 is x = i0 - 1, 4..35 the tile, 36 x = i0 + 32
+// The value of the next or the previous lane of the wavefront.
+__device__ __forceinline__ float from_next(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+        0, __builtin_bit_cast(int, v), 0x130 /* wave_shl:1 */, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float from_prev(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+        0, __builtin_bit_cast(int, v), 0x138 /* wave_shr:1 */, 0xf, 0xf, true));
+}
 
-__global__ __launch_bounds__(64) void k_tv_sweep4(TvArgs a, const float *__restrict__ z,
-                                                  const float *__restrict__ g,
-                                                  float *__restrict__ out, float beta, float step,
-                                                  int nonneg) {
-    // z planes k and k+1: rows y = j0 - 1 .. j0 + 8
-    __shared__ __attribute__((aligned(16))) float zs[2][W_Y + 2][W_PITCH];
-    // p_x and p_y of plane k: rows y = j0 - 1 .. j0 + 7, columns as zs
-    __shared__ __attribute__((aligned(16))) float ps[2][W_Y + 1][W_PITCH];
-    const int lane = threadIdx.x;
-    const int tx = lane & 7, ty = lane >> 3;
-    const SweepTile st = sweep_tile(a, blockIdx.x);
-    const int i0 = st.i0, j0 = st.j0, k0 = st.k0, k1 = st.k1;
-    const int i = i0 + 4 * tx, j = j0 + ty;  // this lane's first voxel
-    const bool own = i < a.nx && j < a.ny;   // all four, since 4 | nx
-    const long long sy = a.nx, sz = (long long)a.nx * a.ny;
-
-    // staging work of this lane: interior float4 (row r1 = ty, and for
-    // lanes 0..15 also row 8 + lane / 8), or for lanes 16..35 one x-halo
-    // element (row (lane - 16) / 2, column low or high)
-    const int rB = lane < 16 ? 8 + (lane >> 3) : -1;           // second interior row
-    const int hrow = (lane >= 16 && lane < 36) ? (lane - 16) >> 1 : -1;
-    const int hcol = (lane & 1) ? 36 : 3;                        // LDS column of the halo
-    const int hx = (lane & 1) ? i0 + W_X : i0 - 1;               // its x
-    auto row_ok = [&](int r) {
-        const int y = j0 - 1 + r;
-        return r >= 0 && y >= 0 && y < a.ny;
+// T projected gradient steps in one launch.  A workgroup of X x Y lanes owns
+// a box of X x Y x NZ voxels, a column of NZ planes per lane in registers.
+// It reads the box once, makes the T steps, and writes the voxels that are T
+// or more from the box's sides (a step makes the outermost layer that is
+// left stale).  z and p_y pass between rows through LDS, between the lanes
+// of a row by DPP, so a step has two barriers for all of its planes.
+//
+// At the grid's sides D_a = 0 follows from a zero 1/h (mx, my, mz); voxels
+// outside the grid read as zero and stay zero.
+//
+// What bounds it at 512 x 512 x 70 and two steps: about 500 VALU instructions
+// a lane for 16 voxel-steps, two thirds of the lanes' work kept (28 x 12 of
+// 32 x 16), near the rate of the loads of the boxes' sides (380 MB a launch).
+// 61 us a launch for two steps against 43 us for one before; 64^3 with three
+// steps 6.8 us against 5.3 for one, whose chain of loads and launch it paid
+// per step.  Boxes of 32 x 16 x 10 or 14, 16 x 16 x 12, 32 x 24 x 12 and
+// 64 x 16 x 12 were 6, 11, 11, 4 and 52% slower there; four steps a launch
+// (16 x 16 x 16) 2% faster at 64^3 and slower elsewhere.
+template <int X, int Y, int NZ, int T, bool NONNEG>
+__global__ __launch_bounds__(X *Y) void k_tv_steps(TvArgs a, const float *__restrict__ zin,
+                                                    const float *__restrict__ g,
+                                                    float *__restrict__ out, float beta,
+                                                    float step) {
+// the same roundings whatever T: T steps are T launches of one, bit for bit
+#pragma clang fp contract(off)
+    __shared__ float zs[NZ][(Y + 1) * X];  // z: row y + 1 read by row y
+    __shared__ float ys[NZ][(Y + 1) * X];  // p_y: row y - 1 read by row y
+    const int tid = threadIdx.x;
+    const int tx = tid % X, ty = tid / X;
+    constexpr int SX = X - 2 * T, SY = Y - 2 * T, SZ = NZ - 2 * T;
+    const int nbx = (a.nx + SX - 1) / SX, nby = (a.ny + SY - 1) / SY;
+    // boxes x-fastest, then y, then z; each XCD takes one contiguous range,
+    // so neighbouring boxes share their sides in one L2
+    const int b = xcd_tile(blockIdx.x, gridDim.x);
+    const int i0 = __builtin_amdgcn_readfirstlane(b % nbx) * SX - T;
+    const int j0 = __builtin_amdgcn_readfirstlane((b / nbx) % nby) * SY - T;
+    const int k0 = __builtin_amdgcn_readfirstlane(b / (nbx * nby)) * SZ - T;
+    const int i = i0 + tx, j = j0 + ty;
+    const bool own = i >= 0 && i < a.nx && j >= 0 && j < a.ny;
+    // Buffer accesses to the box's rows of a plane: reads outside the grid
+    // (an offset beyond the rows, a plane without records) give zero, writes
+    // there are dropped.  Offsets stay below 2^31 (nx at most TV_MAX_NX).
+    const int jb = max(j0, 0);
+    const int rows = min(a.ny - jb, Y) * a.nx * 4;
+    const int off = own ? (i + a.nx * (j - jb)) * 4 : 0x7fffffff;
+    const long long plane = (long long)a.nx * a.ny * 4;
+    const long long first = plane * k0 + (long long)a.nx * jb * 4;  // bytes, may be negative
+    auto rsrc = [&](unsigned long long base, int k) {
+        return __builtin_amdgcn_make_buffer_rsrc(
+            (void *)base, (short)0, (unsigned)k < (unsigned)a.nz ? rows : 0, 0x00020000);
     };
-    const bool qA = i < a.nx && row_ok(ty);
-    const bool qB = rB >= 0 && i < a.nx && row_ok(rB);
-    const bool qH = hrow >= 0 && hx >= 0 && hx < a.nx && row_ok(hrow);
-    const long long oA = (long long)i + sy * (j0 - 1 + ty);
-    const long long oB = (long long)i + sy * (j0 - 1 + rB);
-    const long long oH = (long long)hx + sy * (j0 - 1 + hrow);
-    struct Plane {
-        float4 A, B;
-        float H;
-    };
-    auto fetch = [&](int k, Plane &pl) {
-        const bool kin = k < a.nz;
-        pl.A = (kin && qA) ? *(const float4 *)(z + oA + sz * k) : make_float4(0.f, 0.f, 0.f, 0.f);
-        pl.B = (kin && qB) ? *(const float4 *)(z + oB + sz * k) : make_float4(0.f, 0.f, 0.f, 0.f);
-        pl.H = (kin && qH) ? z[oH + sz * k] : 0.0f;
-    };
-    auto put = [&](int slot, const Plane &pl) {
-        *(float4 *)&zs[slot][ty][4 + 4 * tx] = pl.A;
-        if (rB >= 0) *(float4 *)&zs[slot][rB][4 + 4 * tx] = pl.B;
-        if (hrow >= 0) zs[slot][hrow][hcol] = pl.H;
-    };
-
-    // p_z of the plane below the chunk, for this lane's voxels
-    float pz_prev[4] = {0.f, 0.f, 0.f, 0.f};
-    if (own && k0 > 0) {
+    float z[NZ], gv[NZ], d[NZ];
+    unsigned long long zp = (unsigned long long)zin + first, gp = (unsigned long long)g + first;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const long long v = i + q + sy * j + sz * (k0 - 1);
-            const float zc = z[v];
-            const float gx = (i + q < a.nx - 1) ? (z[v + 1] - zc) * a.ihx : 0.0f;
-            const float gy = (j < a.ny - 1) ? (z[v + sy] - zc) * a.ihy : 0.0f;
-            const float gz = (z[v + sz] - zc) * a.ihz;  // k0 - 1 < nz - 1
-            pz_prev[q] = gz * __builtin_amdgcn_rsqf(gx * gx + gy * gy + gz * gz + a.eps2);
-        }
+    for (int q = 0; q < NZ; ++q, zp += plane, gp += plane) {
+        z[q] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(rsrc(zp, k0 + q), off, 0, 0));
+        gv[q] = 0.0f;
+        if (q > 0 && q < NZ - 1)
+            gv[q] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(rsrc(gp, k0 + q), off, 0, 0));
     }
-    Plane nxt;
-    fetch(k0, nxt);
-    put(k0 & 1, nxt);
-    fetch(k0 + 1, nxt);
-    // the lane's extra p position: low x column (x = i0 - 1, 9 rows) for
-    // lanes 0..8, low y row (y = j0 - 1, 32 columns) for lanes 9..40
-    const int ex_r = lane < 9 ? lane : (lane < 41 ? 0 : -1);
-    const int ex_c = lane < 9 ? 3 : 4 + (lane - 9);
-    const int ex_x = i0 - 1 + (ex_c - 3), ex_y = j0 - 1 + ex_r;
-    for (int k = k0; k < k1; ++k) {
-        const int A = k & 1, B = A ^ 1;
-        put(B, nxt);                             // plane k + 1
-        if (k + 2 < k1 + 1) fetch(k + 2, nxt);  // in flight during this plane
-        const long long v = i + sy * j + sz * k;
-        const float4 gv = own ? *(const float4 *)(g + v) : make_float4(0.f, 0.f, 0.f, 0.f);
-        __syncthreads();
-        // p at the lane's own four positions (row ty + 1 of ps)
-        const int r = ty + 1, c = 4 + 4 * tx;
-        const float4 zc4 = *(const float4 *)&zs[A][r][c];
-        const float zr = zs[A][r][c + 4];
-        const float4 zu4 = *(const float4 *)&zs[A][r + 1][c];
-        const float4 zn4 = *(const float4 *)&zs[B][r][c];
-        const float zcv[4] = {zc4.x, zc4.y, zc4.z, zc4.w};
-        const float zxn[4] = {zc4.y, zc4.z, zc4.w, zr};
-        const float zyn[4] = {zu4.x, zu4.y, zu4.z, zu4.w};
-        const float zzn[4] = {zn4.x, zn4.y, zn4.z, zn4.w};
-        float px[4], py[4], pz[4];
+    const float mx = own && i < a.nx - 1 ? a.ihx : 0.0f;
+    const float my = own && j < a.ny - 1 ? a.ihy : 0.0f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float gx = (i + q < a.nx - 1) ? (zxn[q] - zcv[q]) * a.ihx : 0.0f;
-            const float gy = (j < a.ny - 1) ? (zyn[q] - zcv[q]) * a.ihy : 0.0f;
-            const float gz = (k < a.nz - 1) ? (zzn[q] - zcv[q]) * a.ihz : 0.0f;
-            const float inv = __builtin_amdgcn_rsqf(gx * gx + gy * gy + gz * gz + a.eps2);
-            px[q] = gx * inv;
-            py[q] = gy * inv;
-            pz[q] = gz * inv;
-        }
-        *(float4 *)&ps[0][r][c] = make_float4(px[0], px[1], px[2], px[3]);
-        *(float4 *)&ps[1][r][c] = make_float4(py[0], py[1], py[2], py[3]);
-        if (ex_r >= 0) {
-            // p at the low halo position (only p_x or p_y is read there)
-            const float zc = zs[A][ex_r][ex_c];
-            const float gx = (ex_x < a.nx - 1) ? (zs[A][ex_r][ex_c + 1] - zc) * a.ihx : 0.0f;
-            const float gy = (ex_y < a.ny - 1) ? (zs[A][ex_r + 1][ex_c] - zc) * a.ihy : 0.0f;
-            const float gz = (k < a.nz - 1) ? (zs[B][ex_r][ex_c] - zc) * a.ihz : 0.0f;
-            const float inv = __builtin_amdgcn_rsqf(gx * gx + gy * gy + gz * gz + a.eps2);
-            ps[0][ex_r][ex_c] = gx * inv;
-            ps[1][ex_r][ex_c] = gy * inv;
+    for (int t = 0; t < T; ++t) {
+        // planes t + 1 .. NZ - 2 - t take the step
+#pragma unroll
+        for (int q = t; q < NZ - 1 - t; ++q) zs[q][tid] = z[q];
+        __syncthreads();
+        float pzm = 0.0f;
+#pragma unroll
+        for (int q = t; q < NZ - 1 - t; ++q) {
+            // 1/hz or zero at the last plane, in a scalar register
+            const int in = ~((k0 + q) >> 31) & ((k0 + q - (a.nz - 1)) >> 31);
+            const float mz = __builtin_bit_cast(float, __builtin_bit_cast(int, a.ihz) & in);
+            const float gx = (from_next(z[q]) - z[q]) * mx;
+            const float gy = (zs[q][tid + X] - z[q]) * my;
+            const float gz = (z[q + 1] - z[q]) * mz;
+            const float inv = __builtin_amdgcn_rsqf(__builtin_fmaf(
+                gx, gx, __builtin_fmaf(gy, gy, __builtin_fmaf(gz, gz, a.eps2))));
+            const float px = gx * inv, py = gy * inv, pz = gz * inv;
+            ys[q][tid + X] = py;
+            d[q] = __builtin_fmaf(from_prev(px) - px, a.ihx,
+                                  __builtin_fmaf(pzm - pz, a.ihz, -(py * a.ihy)));
+            pzm = pz;
         }
         __syncthreads();
-        if (own) {
-            const float4 pl = *(const float4 *)&ps[0][r][c - 4];  // columns c - 4 .. c - 1
-            const float4 pu = *(const float4 *)&ps[1][r - 1][c];
-            const float pxm[4] = {pl.w, px[0], px[1], px[2]};
-            const float pym[4] = {pu.x, pu.y, pu.z, pu.w};
-            const float gvv[4] = {gv.x, gv.y, gv.z, gv.w};
-            float res[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float div = 0.0f;
-                if (i + q < a.nx - 1) div -= px[q] * a.ihx;
-                if (j < a.ny - 1) div -= py[q] * a.ihy;
-                if (k < a.nz - 1) div -= pz[q] * a.ihz;
-                if (i + q > 0) div += pxm[q] * a.ihx;
-                if (j > 0) div += pym[q] * a.ihy;
-                if (k > 0) div += pz_prev[q] * a.ihz;
-                float zn = zcv[q] - step * (div + beta * (zcv[q] - gvv[q]));
-                if (nonneg) zn = fmaxf(zn, 0.0f);
-                res[q] = zn;
-                pz_prev[q] = pz[q];
-            }
-            *(float4 *)(out + v) = make_float4(res[0], res[1], res[2], res[3]);
+        for (int q = t + 1; q < NZ - 1 - t; ++q) {
+            const float div = __builtin_fmaf(ys[q][tid], a.ihy, d[q]);
+            const float zn =
+                __builtin_fmaf(-step, __builtin_fmaf(beta, z[q] - gv[q], div), z[q]);
+            z[q] = NONNEG ? fmaxf(zn, 0.0f) : zn;
         }
     }
+    const bool inner = tx >= T && tx < X - T && ty >= T && ty < Y - T;
+    const int to = inner ? off : 0x7fffffff;
+    unsigned long long op = (unsigned long long)out + first + T * plane;
+#pragma unroll
+    for (int q = T; q < NZ - T; ++q, op += plane)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, z[q]),
+                                              rsrc(op, k0 + q), to, 0, 0);
 }
 
 // Per-block partial sums of |Dz| and sqrt(|Dz|^2 + eps^2), in double.
@@ -358,22 +332,44 @@ dim3 tv_grid(const GridConst &gc) {
     return dim3((gc.nx + TV_BX - 1) / TV_BX, (gc.ny + TV_BY - 1) / TV_BY, gc.nz);
 }
 
+template <int T>
+hipError_t steps_launch(const TvArgs &a, const float *z, const float *g, float *out, float beta,
+                        float step, int nonneg, hipStream_t s) {
+    constexpr int NZ = T == 1 ? BOX_Z1 : BOX_Z;
+    auto boxes = [](int n, int side) { return ((long long)n + side - 2 * T - 1) / (side - 2 * T); };
+    const long long n = boxes(a.nx, BOX_X) * boxes(a.ny, BOX_Y) * boxes(a.nz, NZ);
+    const auto kernel = nonneg ? k_tv_steps<BOX_X, BOX_Y, NZ, T, true>
+                               : k_tv_steps<BOX_X, BOX_Y, NZ, T, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(BOX_X * BOX_Y), 0, s, a, z, g, out, beta,
+                       step);
+    return hipGetLastError();
+}
+
 }  // namespace
 
-hipError_t launch_tv_sweep(const GridConst &gc, const float *z, const float *g, float *out,
-                           float beta, float eps, float step, int nonneg, hipStream_t s) {
+int tv_steps_per_launch(const GridConst &gc) {
+    if (gc.nx > TV_MAX_NX) return 1;
+    return (long long)gc.nx * gc.ny * gc.nz < TV_LARGE ? 3 : 2;
+}
+
+hipError_t launch_tv_steps(const GridConst &gc, const float *z, const float *g, float *out,
+                           float beta, float eps, float step, int nonneg, int steps,
+                           hipStream_t s) {
     const TvArgs a = args_of(gc, eps);
-    const int grid = ((gc.nx + ST_X - 1) / ST_X) * ((gc.ny + ST_Y - 1) / ST_Y) *
-                     ((gc.nz + a.zc - 1) / a.zc);
-    const bool vec4 = gc.nx % 4 == 0 && ((uintptr_t)z | (uintptr_t)g | (uintptr_t)out) % 16 == 0;
-    static_assert(W_X == ST_X && W_Y == ST_Y, "both sweeps use the same tiles");
-    if (vec4)
-        hipLaunchKernelGGL(k_tv_sweep4, dim3(grid), dim3(64), 0, s, a, z, g, out, beta, step,
-                           nonneg);
-    else
+    if (gc.nx > TV_MAX_NX) {
+        if (steps != 1) return hipErrorInvalidValue;
+        const int grid = ((gc.nx + ST_X - 1) / ST_X) * ((gc.ny + ST_Y - 1) / ST_Y) *
+                         ((gc.nz + a.zc - 1) / a.zc);
         hipLaunchKernelGGL(k_tv_sweep, dim3(grid), dim3(256), 0, s, a, z, g, out, beta, step,
                            nonneg);
-    return hipGetLastError();
+        return hipGetLastError();
+    }
+    switch (steps) {
+        case 1: return steps_launch<1>(a, z, g, out, beta, step, nonneg, s);
+        case 2: return steps_launch<2>(a, z, g, out, beta, step, nonneg, s);
+        case 3: return steps_launch<3>(a, z, g, out, beta, step, nonneg, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 size_t tv_energy_partials_count(const GridConst &gc) {
