@@ -340,6 +340,12 @@ extern "C" int cbct_plan_create(const cbct_geom *gin, cbct_plan **out) {
             v.sn = (float)sn;
             v.csd = cs;
             v.snd = sn;
+            v.en[0] = h[0] * cs;
+            v.en[1] = h[1] * sn;
+            v.en[2] = x0[0] * cs + x0[1] * sn;  // the source lies on e_w
+            v.ew[0] = -h[0] * sn;
+            v.ew[1] = h[1] * cs;
+            v.ew[2] = x0[1] * cs - x0[0] * sn + g.sad;
             v.nmid = (int)lround(sqrt(pow(src[0] - off[0], 2) + pow(src[1] - off[1], 2) +
                                       off[2] * off[2]) / step);
         }

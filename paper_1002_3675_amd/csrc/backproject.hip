@@ -723,17 +723,33 @@ __global__ __launch_bounds__(256) void k_gather(GridConst gc, const T *__restric
     out[v] = f ? f[v] - tau * s : s;
 }
 
-// The paper's Eq. (2) gradient, voxel-driven: one lane per voxel sums over
-// the views L^3/(L0 l^2) times the bilinear interpolant of the residual at
-// the voxel's imager point (zero beyond the outermost pixel centres), and
-// scales by hx hy hz / (au av) (the transpose's scale).  The imager point
-// in double (1/d from a float reciprocal refined by one double Newton
-// step), the distance l and the interpolation in float, the sum in double.
-// L^3/(L0 l^2)
-// is evaluated as L0^2 l / d^3 (L/l = L0/d along the ray, d the depth of
-// the voxel along the central ray).
+// The paper's Eq. (2) gradient, voxel-driven: a lane sums, for ZC voxels of a
+// column, over the views L^3/(L0 l^2) times the bilinear interpolant of the
+// residual at the voxel's imager point (zero beyond the outermost pixel
+// centres), and scales by hx hy hz / (au av) (the transpose's scale).  The
+// imager point in double (1/d from a float reciprocal refined by one double
+// Newton step), the distance l and the interpolation in float, weights and
+// sum in double.  L^3/(L0 l^2) is evaluated as L0^2 l / d^3 (L/l = L0/d along
+// the ray, d the depth of the voxel along the central ray).
+//
+// Everything of a view but the row coordinate and l is the same along a
+// column.  Where all the wavefront's imager points have their four taps on
+// the detector, their tests go too.  Bound by VALU issue, the double
+// arithmetic above all: about 35 instructions a voxel and view with four
+// voxels a lane, 26 of them for the view.  Head (512 x 512 x 70, 40 views)
+// 1640 us with one voxel a lane and tested taps, 825 now.  Eight voxels a
+// lane take 140 registers and 924 us.
 constexpr int Q_BX = 64, Q_BY = 4;
 
+// sqrt(x) for x > 0: the hardware's reciprocal root and a correction, within
+// an ulp of the correctly rounded value.
+__device__ __forceinline__ float sqrt_pos(float x) {
+    const float r = __builtin_amdgcn_rsqf(x);
+    const float y = x * r;
+    return __builtin_fmaf(__builtin_fmaf(-y, y, x), 0.5f * r, y);
+}
+
+template <int ZC>
 __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views, DetConst dc,
                                              GridConst gc, double hx, double hy, double hz,
                                              int nu, int nv, int nviews,
@@ -742,47 +758,80 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
                                              double tau, float *__restrict__ out) {
     const int i = blockIdx.x * Q_BX + threadIdx.x;
     const int j = blockIdx.y * Q_BY + threadIdx.y;
-    const int k = blockIdx.z;
+    const int k0 = blockIdx.z * ZC;
     if (i >= gc.nx || j >= gc.ny) return;
-    const double sdd = dc.sddd, sdd2 = dc.sdd2d;
-    const double iau = 1.0 / dc.aud, iav = 1.0 / dc.avd;
-    const double ci = -dc.u0d * iau, cj = -dc.v0d * iav;  // index of u = 0, v = 0
-    double sum = 0.0;
+    const double su = dc.sddd / dc.aud, sv = dc.sddd / dc.avd;
+    const double ci = -dc.u0d / dc.aud, cj = -dc.v0d / dc.avd;  // index of u = 0, v = 0
+    const double kz = (double)k0 - views[0].Qd[2];  // the same in every view
+    double sum[ZC], wz2[ZC];
+#pragma unroll
+    for (int q = 0; q < ZC; ++q) {
+        sum[q] = 0.0;
+        wz2[q] = (kz + q) * hz * ((kz + q) * hz);
+    }
+    // 32-bit byte offsets within a view
+    const bool narrow = (long long)nu * nv < (1LL << 30);
     for (int t = 0; t < nviews; ++t) {
-        const ViewConst vc = views[t];
-        // source-to-voxel vector in mm (index coordinates of the voxel
-        // centre minus those of the source, times the spacing)
-        const double wx = ((double)i - vc.Qd[0]) * hx;
-        const double wy = ((double)j - vc.Qd[1]) * hy;
-        const double wz = ((double)k - vc.Qd[2]) * hz;
-        const double n = wx * vc.csd + wy * vc.snd;      // along e_u
-        const double d = wy * vc.csd - wx * vc.snd;      // along e_w (depth)
+        const ViewConst &vc = views[t];
+        // source-to-voxel vector (mm): n along e_u, d along e_w (depth)
+        const double n = __builtin_fma((double)i, vc.en[0], __builtin_fma((double)j, vc.en[1], vc.en[2]));
+        const double d = __builtin_fma((double)i, vc.ew[0], __builtin_fma((double)j, vc.ew[1], vc.ew[2]));
         // 1/d from the float reciprocal and one Newton step in double: the
         // relative error squares, from ~2e-7 to ~4e-14
         const double id0 = (double)__builtin_amdgcn_rcpf((float)d);
         const double id = id0 * __builtin_fma(-d, id0, 2.0);
-        const double fi = sdd * n * id * iau + ci;       // fractional pixel indices
-        const double fj = sdd * wz * id * iav + cj;
-        // l enters only the weight, where float's 1e-7 is ample
-        const double l = (double)__builtin_sqrtf((float)(wx * wx + wy * wy + wz * wz));
-        const double w = sdd2 * l * (id * id * id);
-        const double i0d = __builtin_floor(fi), j0d = __builtin_floor(fj);
-        const float a = (float)(fi - i0d), b = (float)(fj - j0d);
-        const int i0 = (int)fmax(fmin(i0d, (double)nu), -2.0);
-        const int j0 = (int)fmax(fmin(j0d, (double)nv), -2.0);
+        // fractional pixel indices: fi, and fj = fj0 + q dj in plane k0 + q
+        const double fi = __builtin_fma(n * id, su, ci);
+        const double dj = id * (sv * hz);
+        const double fj0 = __builtin_fma(kz, dj, cj);
+        const double fj1 = __builtin_fma((double)(ZC - 1), dj, fj0);
+        const double i0d = __builtin_floor(fi);
+        const float a = (float)(fi - i0d);
+        const double w0 = dc.sdd2d * (id * id * id);     // weight / l
+        const double lxy2 = __builtin_fma(n, n, d * d);
+        auto weight = [&](int q) { return w0 * (double)sqrt_pos((float)(wz2[q] + lxy2)); };
         const float *rt = r + (long long)t * nu * nv;
+        const bool inside = narrow && fi >= 0.0 && fi < nu - 1.0 && fmin(fj0, fj1) >= 0.0 &&
+                            fmax(fj0, fj1) < nv - 1.0;
+        if (!__builtin_amdgcn_ballot_w64(!inside)) {
+            const float *rt1 = rt + nu;
+            const unsigned i4 = 4u * (unsigned)(int)i0d, nu4 = 4u * (unsigned)nu;
+#pragma unroll
+            for (int q = 0; q < ZC; ++q) {
+                const double fj = __builtin_fma((double)q, dj, fj0);
+                const unsigned o = (unsigned)(int)fj * nu4 + i4;  // fj >= 0
+                const float b = (float)__builtin_amdgcn_fract(fj);
+                const float *p = (const float *)((const char *)rt + o);
+                const float *p1 = (const float *)((const char *)rt1 + o);
+                const float v0 = p[0] + a * (p[1] - p[0]), v1 = p1[0] + a * (p1[1] - p1[0]);
+                sum[q] = __builtin_fma(weight(q), (double)(v0 + b * (v1 - v0)), sum[q]);
+            }
+            continue;
+        }
+        const int i0 = (int)fmax(fmin(i0d, (double)nu), -2.0);
         const bool in0 = i0 >= 0 && i0 < nu, in1 = i0 + 1 >= 0 && i0 + 1 < nu;
-        const bool jn0 = j0 >= 0 && j0 < nv, jn1 = j0 + 1 >= 0 && j0 + 1 < nv;
-        const float r00 = (in0 && jn0) ? rt[(long long)j0 * nu + i0] : 0.0f;
-        const float r10 = (in1 && jn0) ? rt[(long long)j0 * nu + i0 + 1] : 0.0f;
-        const float r01 = (in0 && jn1) ? rt[(long long)(j0 + 1) * nu + i0] : 0.0f;
-        const float r11 = (in1 && jn1) ? rt[(long long)(j0 + 1) * nu + i0 + 1] : 0.0f;
-        const float v0 = r00 + a * (r10 - r00), v1 = r01 + a * (r11 - r01);
-        sum += w * (double)(v0 + b * (v1 - v0));
+#pragma unroll
+        for (int q = 0; q < ZC; ++q) {
+            const double fj = __builtin_fma((double)q, dj, fj0);
+            const double j0d = __builtin_floor(fj);
+            const float b = (float)(fj - j0d);
+            const int j0 = (int)fmax(fmin(j0d, (double)nv), -2.0);
+            const bool jn0 = j0 >= 0 && j0 < nv, jn1 = j0 + 1 >= 0 && j0 + 1 < nv;
+            const float r00 = (in0 && jn0) ? rt[(long long)j0 * nu + i0] : 0.0f;
+            const float r10 = (in1 && jn0) ? rt[(long long)j0 * nu + i0 + 1] : 0.0f;
+            const float r01 = (in0 && jn1) ? rt[(long long)(j0 + 1) * nu + i0] : 0.0f;
+            const float r11 = (in1 && jn1) ? rt[(long long)(j0 + 1) * nu + i0 + 1] : 0.0f;
+            const float v0 = r00 + a * (r10 - r00), v1 = r01 + a * (r11 - r01);
+            sum[q] = __builtin_fma(weight(q), (double)(v0 + b * (v1 - v0)), sum[q]);
+        }
     }
-    const long long v = (long long)i + (long long)gc.nx * (j + (long long)gc.ny * k);
-    const double s = scale * sum;
-    out[v] = f ? (float)((double)f[v] - tau * s) : (float)s;
+#pragma unroll
+    for (int q = 0; q < ZC; ++q) {
+        if (k0 + q >= gc.nz) break;
+        const long long v = (long long)i + (long long)gc.nx * (j + (long long)gc.ny * (k0 + q));
+        const double s = scale * sum[q];
+        out[v] = f ? (float)((double)f[v] - tau * s) : (float)s;
+    }
 }
 
 }  // namespace
@@ -877,9 +926,26 @@ hipError_t launch_gather_cells(const cbct_plan &p, const void *ws, const T *f, d
 hipError_t launch_eq2(const cbct_plan &p, const float *r, const float *f, double tau,
                       float *out, hipStream_t s) {
     const double scale = p.g.hx * p.g.hy * p.g.hz / (p.g.au * p.g.av);
-    dim3 grid((p.g.nx + Q_BX - 1) / Q_BX, (p.g.ny + Q_BY - 1) / Q_BY, p.g.nz);
-    hipLaunchKernelGGL(k_eq2, grid, dim3(Q_BX, Q_BY), 0, s, p.d_views, p.det, p.grid, p.g.hx,
-                       p.g.hy, p.g.hz, p.g.nu, p.g.nv, p.g.n_views, r, f, scale, tau, out);
+    auto launch = [&](auto kernel, int zc) {
+        dim3 grid((p.g.nx + Q_BX - 1) / Q_BX, (p.g.ny + Q_BY - 1) / Q_BY,
+                  (p.g.nz + zc - 1) / zc);
+        hipLaunchKernelGGL(kernel, grid, dim3(Q_BX, Q_BY), 0, s, p.d_views, p.det, p.grid,
+                           p.g.hx, p.g.hy, p.g.hz, p.g.nu, p.g.nv, p.g.n_views, r, f, scale, tau,
+                           out);
+    };
+    // Voxels a lane: more share a view's arithmetic, fewer leave more
+    // wavefronts.  Measured, us with 1 / 2 / 4: 4096 wavefronts of single
+    // voxels (64^3) 15 / 16 / 23, 29k (157 x 141 x 67) 101 / 84 / 91, 33k
+    // (128^3) 195 / 156 / 161, 66k (256 x 256 x 64) 407 / 309 / 289, 287k
+    // (head) 1293 / 891 / 825.
+    const long long waves = ((p.g.nx + Q_BX - 1LL) / Q_BX) * ((p.g.ny + Q_BY - 1LL) / Q_BY) * Q_BY *
+                            p.g.nz;
+    if (waves >= 49152)
+        launch(k_eq2<4>, 4);
+    else if (waves >= 8192)
+        launch(k_eq2<2>, 2);
+    else
+        launch(k_eq2<1>, 1);
     return hipGetLastError();
 }
 

@@ -31,6 +31,9 @@ struct ViewConst {
     double Qd[3];  // the same constants in double for the FP64 kernels
     double Wd[2], Ud[2], Vzd;
     double csd, snd;  // cos(theta), sin(theta) in double
+    // source-to-voxel (i, j) vector (mm) along e_u and along e_w (the depth):
+    // en[0] i + en[1] j + en[2], ew alike
+    double en[3], ew[3];
     int nmid;         // sample index at the grid centre's distance from the source
 };
 
