@@ -161,17 +161,24 @@ __device__ __forceinline__ double march_double(const double Q[3], const double D
 }
 
 // Sum of the trilinear samples m = ma .. mb of one chunk from the staged
-// box (row pitch RX, plane pitch RXY floats, base the LDS offset of the
-// segment origin's cell): seg_axis's coordinates and weights, the LDS offset
-// of the floors formed in float (exact: |offset| < 2^24), m counted in float
-// (exact below 2^24); two samples per loop step, summed in order.  RXC > 0
-// fixes the row pitch at compile time.
+// box (row pitch RX, plane pitch RXY floats, base the LDS byte address of the
+// segment origin's cell): seg_axis's coordinates and weights, m counted in
+// float (exact below 2^24); two samples per loop step, summed in order.
+// RXC > 0 fixes the row pitch at compile time.  The LDS address is formed in
+// subnormal floats, whose bits are the integer itself: every product and sum
+// below is a multiple of 4 * 2^-149 smaller than 2^26 of these, so exact, and
+// no zero among them is negative (base is +0 or not zero).  Multiply-adds
+// cost two thirds of what the conversion and the integer adds of the same
+// sum cost: 31 -> 29 vector instructions a sample.
 template <int RXC>
-__device__ __forceinline__ float staged_samples(const float *vol, int base, int RXr, int RXY,
-                                                float m, float mb, const float Df[3],
-                                                const float of[3]) {
+__device__ __forceinline__ float staged_samples(int base, int RXr, int RXY, float m, float mb,
+                                                const float Df[3], const float of[3]) {
+    typedef const __attribute__((address_space(3))) float *lds_t;
     const int RX = RXC > 0 ? RXC : RXr;
-    const float RXf = (float)RX, RXYf = (float)RXY;
+    const float Xf = __builtin_bit_cast(float, 4);
+    const float RXf = __builtin_bit_cast(float, 4 * RX);
+    const float RXYf = __builtin_bit_cast(float, 4 * RXY);
+    const float basef = (float)base * __builtin_bit_cast(float, 1);
     float seg = 0.0f;
     auto sample = [&](float m) {
         const float lx = __builtin_fmaf(m, Df[0], of[0]);
@@ -180,8 +187,10 @@ __device__ __forceinline__ float staged_samples(const float *vol, int base, int 
         const float fx = __builtin_floorf(lx), fy = __builtin_floorf(ly),
                     fz = __builtin_floorf(lz);
         const float wx = lx - fx, wy = ly - fy, wz = lz - fz;
-        const float *p = vol + base + (int)__builtin_fmaf(fz, RXYf, __builtin_fmaf(fy, RXf, fx));
-        const float *q = p + RXY;
+        const float at = __builtin_fmaf(
+            fz, RXYf, __builtin_fmaf(fy, RXf, __builtin_fmaf(fx, Xf, basef)));
+        const lds_t p = (lds_t)(size_t)__builtin_bit_cast(unsigned, at);
+        const lds_t q = (lds_t)(size_t)__builtin_bit_cast(unsigned, at + RXYf);
         const float c00 = p[0] + wx * (p[1] - p[0]);
         const float c10 = p[RX] + wx * (p[RX + 1] - p[RX]);
         const float c01 = q[0] + wx * (q[1] - q[0]);
@@ -190,7 +199,8 @@ __device__ __forceinline__ float staged_samples(const float *vol, int base, int 
         const float c1 = c01 + wy * (c11 - c01);
         seg += c0 + wz * (c1 - c0);
     };
-    for (; m + 1.0f <= mb; m += 2.0f) {
+    const float mc = mb - 1.0f;
+    for (; m <= mc; m += 2.0f) {
         sample(m);
         sample(m + 1.0f);
     }
@@ -215,13 +225,24 @@ __device__ __forceinline__ float staged_samples(const float *vol, int base, int 
 // cells and weights are exactly those of sample_cell and seg_axis,
 // whatever the chunking.  A square tile
 // keeps the bundle, and so the box, narrow in both detector directions.
+//
+// What bounds it: the vector units (29 instructions a sample) and the LDS
+// reads (four pairs of taps, four cycles each of the CU's LDS without bank
+// conflicts) take about the same time.  The LDS serves 32 lanes at a time
+// from 32 banks, so each half of a wavefront takes 4 x 8 rays (along u, v),
+// which meet few columns of many planes, and the planes' pitch is chosen per
+// tile so that they fall on different banks (best_residue).  Rows of 16 x 2
+// rays with planes packed close lost 1.4 cycles a read at the head size and
+// 3.3-3.5 at 256 x 256 x 64 and 128^3 / 60 views; now 0.6, 1.4 and 2.0:
+// P 5.60 -> 5.05 ms, 1.19 -> 1.04, 0.68 -> 0.57; 64^3 / 16 views 56 -> 44 us.
 // Where a tile spans many cells (pixels near the voxel size) single pieces
 // still fit; where it spans few, runs spread the per-chunk staging and
 // segment-origin work over more samples.
 constexpr int TILE_U = 16, TILE_V = 16;
 constexpr int TILE_SUB = 16;    // samples per box
 constexpr int TILE_MERGE = 8;   // boxes per chunk at most
-constexpr int TILE_LDS = 5632;  // floats (larger boxes stage more slowly than they save)
+constexpr int TILE_LDS = 5760;  // floats (larger boxes stage more slowly than they save)
+constexpr int TILE_VOL = 6016;  // floats of LDS: a fitting box, and room to space its planes
 constexpr int BOX_TAB = 128;    // boxes computed together
 static_assert(SEG % (TILE_SUB * TILE_MERGE) == 0, "a block of pieces lies inside one segment");
 static_assert(BOX_TAB % TILE_MERGE == 0 && BOX_TAB <= 256, "whole blocks per box table");
@@ -249,8 +270,9 @@ __device__ __forceinline__ bool box_fits(const int b0[3], const int b1[3]) {
 
 // Groups the pieces [q0, q1) of one block of the table into chunks: the
 // entry of a chunk's first piece takes the chunk's box and, in w, its
-// length in pieces (negative for a chunk read from global memory).
-__device__ __forceinline__ void group_block(int4 *tab, int q0, int q1) {
+// length in pieces (negative for a chunk read from global memory);
+// *pitch_max rises to the widest fitting chunk's row pitch.
+__device__ __forceinline__ void group_block(int4 *tab, int q0, int q1, int *pitch_max) {
     for (int q = q0; q < q1;) {
         int b0[3], b1[3];
         unpack_box(tab[q], b0, b1);
@@ -277,19 +299,78 @@ __device__ __forceinline__ void group_block(int4 *tab, int q0, int q1) {
         }
         tab[q] = make_int4((b0[0] & 0xffff) | (b1[0] << 16), (b0[1] & 0xffff) | (b1[1] << 16),
                            (b0[2] & 0xffff) | (b1[2] << 16), fits ? e - q : q - e);
+        if (fits) atomicMax(pitch_max, (b1[0] - b0[0] + 1) | 1);
         q = e;
     }
 }
 
-// At most 80 VGPRs: six wavefronts per SIMD (six groups of 24 KB of LDS per
-// CU) instead of the five that the unconstrained 95 allow.
+// The cells of the 32 rays of one half of a wavefront (the second half of
+// wavefront 0, or the first of wavefront 3) at sample n, for best_residue:
+// x, y, z modulo 256 in bytes, and 1, or 0 where a neighbour before it in
+// the half holds the same cell (lanes that read one address do not conflict).
+__device__ __forceinline__ void half_pattern(uint2 *pat, const double Q[3], const double D[3],
+                                             const float Df[3], int n, int wid, int lane) {
+    int c[3];
+    sample_cell<float>(Q, D, Df, n, c);
+    const int key = (c[0] & 1023) | (c[1] & 1023) << 10 | (c[2] & 1023) << 20;
+    bool same = false;
+#pragma unroll
+    for (int d : {1, 3, 4, 5}) {
+        const int k = __shfl_up(key, d, 32);
+        same = same || ((lane & 31) >= d && k == key);
+    }
+    const int half = wid == 0;
+    if ((lane >> 5) == half)
+        pat[32 * (1 - half) + (lane & 31)] =
+            make_uint2((c[0] & 255) | (c[1] & 255) << 8 | (c[2] & 255) << 16, same ? 0u : 1u);
+}
+
+// The residue modulo 32 (the LDS banks) of the plane pitch, at row pitch p,
+// for which the cells of the two patterns load the fullest bank least: lane
+// l and lane l + 32 try residue l on one pattern each.  Where a tap's row
+// and column lie in the box shifts all its lanes' banks alike, so the cells
+// stand for all eight taps, and rays of one tile keep their pattern along
+// the tile, so two depths stand for all samples.  The search costs about
+// 250 vector instructions a tile, 1 to 3% of its samples'.
+__device__ __forceinline__ int best_residue(const uint4 *pat, int p, int lane) {
+    const unsigned cand = 1u | (unsigned)(p & 31) << 8 | (unsigned)(lane & 31) << 16;
+    const uint4 *q = pat + 16 * (lane >> 5);
+    unsigned t1 = 0, t2 = 0, t3 = 0, t4 = 0;  // banks with at least that many cells
+#pragma unroll 4
+    for (int l = 0; l < 16; ++l) {
+        const uint4 v = q[l];
+        unsigned b = v.y << (__builtin_amdgcn_udot4(v.x, cand, 0, false) & 31);
+        t4 |= t3 & b;
+        t3 |= t2 & b;
+        t2 |= t1 & b;
+        t1 |= b;
+        b = v.w << (__builtin_amdgcn_udot4(v.z, cand, 0, false) & 31);
+        t4 |= t3 & b;
+        t3 |= t2 & b;
+        t2 |= t1 & b;
+        t1 |= b;
+    }
+    int cost = 64 * ((t2 != 0) + (t3 != 0) + (t4 != 0)) + 32 - __popc(t1);
+    cost += __shfl_xor(cost, 32, 64);
+    int key = cost << 5 | (lane & 31);
+    for (int off = 16; off > 0; off >>= 1) key = min(key, __shfl_xor(key, off, 64));
+    return key & 31;
+}
+
+// At most 80 VGPRs: six wavefronts per SIMD (six groups of 27 KB of LDS per
+// CU).  Seven or eight with smaller boxes leave chunks that do not fit
+// (256 x 256 x 64: 1.04 -> 1.47 and 2.56 ms); five with larger ones are slower
+// at the head size (5.35 -> 5.46 ms) and no faster elsewhere.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_project_tile(
     const ViewConst *__restrict__ views, DetConst dc, GridConst gc, int nu, int nv,
     const float *__restrict__ fp, int fp_elems, const float *__restrict__ Y,
     float *__restrict__ out, double *__restrict__ partials, float step, int margin) {
-    __shared__ float vol[TILE_LDS];
+    __shared__ float vol[TILE_VOL];
+    __shared__ uint4 pattern[32];
     __shared__ int4 boxes[BOX_TAB];  // piece boxes, packed b0 | b1 << 16 per axis
     __shared__ int red[2][4];
+    __shared__ int pitch_max, plane_res[4];
+    __shared__ double corner[4][3];
     const int tid = threadIdx.x;
     const int lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     // tiles u-fastest, then v, then view; contiguous per XCD, so the rays
@@ -297,16 +378,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     const int ntu = (nu + TILE_U - 1) / TILE_U, ntv = (nv + TILE_V - 1) / TILE_V;
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int tu = tile % ntu, tv = (tile / ntu) % ntv, k = tile / (ntu * ntv);
-    const int i = tu * TILE_U + (tid & (TILE_U - 1));
-    const int j = tv * TILE_V + tid / TILE_U;
+    const int i = tu * TILE_U + 8 * (wid & 1) + 4 * (lane >> 5) + (lane & 3);
+    const int j = tv * TILE_V + 8 * (wid >> 1) + ((lane & 31) >> 2);
     const bool valid = i < nu && j < nv;
     const ViewConst vc = views[k];
     double Q[3], D[3];
     float Df[3];
-    ray_setup(vc, dc, valid ? i : 0, valid ? j : 0, Q, D);
+    ray_setup(vc, dc, min(i, nu - 1), min(j, nv - 1), Q, D);
     to_float3(D, Df);
     int n0 = 1, n1 = 0;
     if (valid) ray_interval<float>(Q, D, Df, gc, n0, n1);
+    // the rays of the tile's corners (at a detector edge, of its last
+    // column or row)
+    const int ti = i - tu * TILE_U, tj = j - tv * TILE_V;
+    if ((ti == 0 || ti == TILE_U - 1) && (tj == 0 || tj == TILE_V - 1))
+#pragma unroll
+        for (int a = 0; a < 3; ++a) corner[(ti != 0) + 2 * (tj != 0)][a] = D[a];
     // union of the tile's sample intervals
     const bool any = n0 <= n1;
     int lo = wave_min(any ? n0 : 0x7fffffff), hi = wave_max(any ? n1 : -1);
@@ -317,6 +404,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     __syncthreads();
     lo = min(min(red[0][0], red[0][1]), min(red[0][2], red[0][3]));
     hi = max(max(red[1][0], red[1][1]), max(red[1][2], red[1][3]));
+    if (lo <= hi && (wid == 0 || wid == 3))
+        half_pattern(reinterpret_cast<uint2 *>(pattern), Q, D, Df,
+                     lo + ((hi - lo) >> 2) * (wid == 0 ? 1 : 3), wid, lane);
     const int N[3] = {gc.nx, gc.ny, gc.nz};
     const int px = gc.nx + 2, pxy = px * (gc.ny + 2);
     const __amdgpu_buffer_rsrc_t gvol =
@@ -332,21 +422,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
             // box of padded cells [b0, b1] per axis touched by piece cg + tid,
             // from the tile's four corner rays
             const int nc = nc0 + TILE_SUB * (cg + tid);
-            const int ci0 = tu * TILE_U, ci1 = min(ci0 + TILE_U - 1, nu - 1);
-            const int cj0 = tv * TILE_V, cj1 = min(cj0 + TILE_V - 1, nv - 1);
-            double Dc[4][3], Qc[3];
-            ray_setup(vc, dc, ci0, cj0, Qc, Dc[0]);
-            ray_setup(vc, dc, ci1, cj0, Qc, Dc[1]);
-            ray_setup(vc, dc, ci0, cj1, Qc, Dc[2]);
-            ray_setup(vc, dc, ci1, cj1, Qc, Dc[3]);
             int pk[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 double qmin = 1e300, qmax = -1e300;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const double qa = Qc[a] + (double)nc * Dc[c][a];
-                    const double qb = Qc[a] + (double)(nc + TILE_SUB - 1) * Dc[c][a];
+                    const double qa = Q[a] + (double)nc * corner[c][a];
+                    const double qb = Q[a] + (double)(nc + TILE_SUB - 1) * corner[c][a];
                     qmin = fmin(qmin, fmin(qa, qb));
                     qmax = fmax(qmax, fmax(qa, qb));
                 }
@@ -359,10 +442,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
             }
             boxes[tid] = make_int4(pk[0], pk[1], pk[2], 0);
         }
+        if (tid == 0) pitch_max = 0;
         __syncthreads();
         const int cend = min(npieces, cg + BOX_TAB);
         if (tid < BOX_TAB / TILE_MERGE && cg + TILE_MERGE * tid < cend)
-            group_block(boxes, TILE_MERGE * tid, min(TILE_MERGE * (tid + 1), cend - cg));
+            group_block(boxes, TILE_MERGE * tid, min(TILE_MERGE * (tid + 1), cend - cg),
+                        &pitch_max);
+        __syncthreads();
+        const int pmax = __builtin_amdgcn_readfirstlane(pitch_max);
+        if (pmax > 0) {  // for the four widest row pitches, one a wavefront
+            const int e = best_residue(pattern, pmax - 2 * wid, lane);
+            if (lane == 0) plane_res[wid] = e;
+        }
         __syncthreads();
         for (int c = cg; c < cend;) {
             const int nc = nc0 + TILE_SUB * c;
@@ -381,6 +472,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
             // LDS rows have an odd pitch, so rays spread across rows (views whose
             // rays run along x) do not pile onto one bank
             const int RXP = RX | 1;
+            // the plane pitch: the residue found for this row pitch, if the
+            // spaced planes fit; narrower rows keep close planes
+            int RXY = RXP * RY;
+            const int pi = (pmax - RXP) >> 1;
+            if (staged && pi < 4) {
+                const int padded =
+                    RXY + ((__builtin_amdgcn_readfirstlane(plane_res[pi]) - RXY) & 31);
+                if (padded * RZ <= TILE_VOL) RXY = padded;
+            }
             __syncthreads();  // the previous chunk's readers are done
             if (staged) {
                 // Plane z of the box is RXP * RY consecutive LDS elements, x
@@ -406,7 +506,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
                         const int off = (__mul24(row, px) + x) * 4;
                         for (int rz = 0; rz < RZ; ++rz)
                             __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                                gvol, (__attribute__((address_space(3))) void *)&vol[rz * npl + t0],
+                                gvol, (__attribute__((address_space(3))) void *)&vol[rz * RXY + t0],
                                 4, off, g0 + rz * pxy * 4, 0, 0);
                     }
                 }
@@ -419,16 +519,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
             const SegOrigin o = seg_origin(Q, D, s);
             float seg = 0.0f;
             if (staged) {
-                const int RXY = RXP * RY;
-                const int base = (o.I[2] + 1 - b0[2]) * RXY + (o.I[1] + 1 - b0[1]) * RXP +
-                                 (o.I[0] + 1 - b0[0]);
+                const int base = 4 * ((o.I[2] + 1 - b0[2]) * RXY + (o.I[1] + 1 - b0[1]) * RXP +
+                                      (o.I[0] + 1 - b0[0])) +
+                                 (int)(size_t)(__attribute__((address_space(3))) float *)vol;
                 const float ma = (float)(na - s), mb = (float)(nb - s);
                 // common row pitches as constants: the row offsets then sit in
                 // the LDS instructions' immediates
                 switch (RXP) {
 #define CBCT_PITCH(n)                                                                   \
     case n:                                                                             \
-        seg = staged_samples<n>(vol, base, RXP, RXY, ma, mb, Df, o.f);                   \
+        seg = staged_samples<n>(base, RXP, RXY, ma, mb, Df, o.f);                   \
         break;
                     CBCT_PITCH(5) CBCT_PITCH(7) CBCT_PITCH(9) CBCT_PITCH(11) CBCT_PITCH(13)
                     CBCT_PITCH(15) CBCT_PITCH(17) CBCT_PITCH(19) CBCT_PITCH(21) CBCT_PITCH(23)
@@ -436,7 +536,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
                     CBCT_PITCH(35) CBCT_PITCH(37) CBCT_PITCH(39) CBCT_PITCH(41)
 #undef CBCT_PITCH
                     default:
-                        seg = staged_samples<0>(vol, base, RXP, RXY, ma, mb, Df, o.f);
+                        seg = staged_samples<0>(base, RXP, RXY, ma, mb, Df, o.f);
                 }
             } else {
                 const int base = (o.I[2] + 1) * pxy + (o.I[1] + 1) * px + (o.I[0] + 1);
