@@ -14,9 +14,8 @@
 //     for every view the workgroup stages the rays of its brick's footprint
 //     in LDS; each lane then visits the pixels whose rays can cross its
 //     cell and adds each ray's samples in the cell, r * (trilinear corner
-//     weight), to eight moments in registers.  In float the samples of one
-//     crossing are added in closed form (see crossing_sums); in double one
-//     by one;
+//     weight), to eight moments in registers, the samples of one crossing
+//     in closed form (see crossing_sums), in float and double alike;
 //   * pass 2 (one lane per voxel): sum the matching corner of the eight
 //     cells that share the voxel, optionally fused with Step 1 of
 //     Algorithm A1, g = f - tau * P^T r.
@@ -33,7 +32,7 @@ namespace cbct {
 namespace {
 
 constexpr int CB_X = 16, CB_Y = 16, CB_Z = 1;  // cells per workgroup: one z layer
-constexpr int TABLE = 560;                     // rays staged at a time (40 B each)
+constexpr int TABLE = 560;                     // rays staged at a time (40 B each, 80 in double)
 constexpr int PARTS = 6;                       // views staged at a time, at most
 constexpr int G_BX = 64, G_BY = 4;            // pass-2 block
 
@@ -55,126 +54,18 @@ struct PixelRay {
     double D[3];
 };
 
-// Reciprocals of the float rounding of a ray's increment.
-__device__ __forceinline__ void ray_inv(const PixelRay &g, float inv[3]) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) inv[a] = __builtin_amdgcn_rcpf((float)g.D[a]);
-}
-
-// Per-lane, per-view constants of the candidate range of cell c: along
-// axis a the samples with coordinate in [c_a, c_a + 1) lie between
-// (c_a - Q_a)/D_a and (c_a + 1 - Q_a)/D_a.  The float Q and D differ from
-// the double ones by at most ~1e-6 relative, which moves those bounds by at
-// most 1e-6 (|Q| + |c| + 1)/|D|; the range is widened by four times that
-// plus 1e-3 (covers the rounding of the float estimate itself).
-struct CellRange {
-    float cq[3];  // c_a - Q_a
-    float K[3];   // 4e-6 (|Q_a| + |c_a| + 1)
-};
-
-__device__ __forceinline__ CellRange cell_range(const float Qf[3], float cx, float cy, float cz) {
-    CellRange cr;
-    const float c[3] = {cx, cy, cz};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        cr.cq[a] = c[a] - Qf[a];
-        cr.K[a] = 4e-6f * (fabsf(Qf[a]) + fabsf(c[a]) + 1.0f);
-    }
-    return cr;
-}
-
-// Candidate samples [n0, n1] of the ray with reciprocal increments inv.
-__device__ __forceinline__ bool candidates_inv(const CellRange &cr, const float inv[3], int &n0,
-                                               int &n1) {
-    float lo[3], hi[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const float t0 = cr.cq[a] * inv[a];
-        const float t1 = t0 + inv[a];
-        const float m = __builtin_fmaf(cr.K[a], fabsf(inv[a]), 1e-3f);
-        lo[a] = fminf(t0, t1) - m;
-        hi[a] = fmaxf(t0, t1) + m;
-    }
-    const float l = fmaxf(fmaxf(lo[0], lo[1]), lo[2]);
-    const float h = fminf(fminf(hi[0], hi[1]), hi[2]);
-    if (!(l <= h)) return false;
-    n0 = clamp_to_int(-floor_t(-l));
-    n1 = clamp_to_int(floor_t(h));
-    return n0 <= n1;
-}
-
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ double rcp(double x) { return 1.0 / x; }
 
-// Detector-coordinate bounds of the projection of an axis-aligned box
-// [xa, xb] x [ya, yb] x [za, zb] (mm) for view vc; the extremes of the
-// perspective map over a box are taken at its corners.
-__device__ __forceinline__ void box_footprint(const ViewConst &vc, float sdd, float xa, float xb,
-                                              float ya, float yb, float za, float zb,
-                                              float &umin, float &umax, float &vmin,
-                                              float &vmax) {
-    const float wx0 = xa - vc.src[0], wx1 = xb - vc.src[0];
-    const float wy0 = ya - vc.src[1], wy1 = yb - vc.src[1];
-    // numerator of u (w . e_u) and depth (w . e_w) at the four xy corners
-    const float n00 = wx0 * vc.cs + wy0 * vc.sn, d00 = wy0 * vc.cs - wx0 * vc.sn;
-    const float n10 = wx1 * vc.cs + wy0 * vc.sn, d10 = wy0 * vc.cs - wx1 * vc.sn;
-    const float n01 = wx0 * vc.cs + wy1 * vc.sn, d01 = wy1 * vc.cs - wx0 * vc.sn;
-    const float n11 = wx1 * vc.cs + wy1 * vc.sn, d11 = wy1 * vc.cs - wx1 * vc.sn;
-    const float u00 = n00 * rcp(d00), u10 = n10 * rcp(d10);
-    const float u01 = n01 * rcp(d01), u11 = n11 * rcp(d11);
-    umin = sdd * fminf(fminf(u00, u10), fminf(u01, u11));
-    umax = sdd * fmaxf(fmaxf(u00, u10), fmaxf(u01, u11));
-    const float ia = rcp(fminf(fminf(d00, d10), fminf(d01, d11)));
-    const float ib = rcp(fmaxf(fmaxf(d00, d10), fmaxf(d01, d11)));
-    const float v0 = za * ia, v1 = za * ib, v2 = zb * ia, v3 = zb * ib;
-    vmin = sdd * fminf(fminf(v0, v1), fminf(v2, v3));
-    vmax = sdd * fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
-}
-
-// Pixel index range [i0, i1] x [j0, j1] whose centres fall inside the
-// detector rectangle [umin, umax] x [vmin, vmax] widened by 0.01 pixel.
-__device__ __forceinline__ void pixel_range(const DetConst &dc, int nu, int nv, float umin,
-                                            float umax, float vmin, float vmax, int &i0, int &i1,
-                                            int &j0, int &j1) {
-    const float margin = 0.01f;
-    const float iau = rcp(dc.au), iav = rcp(dc.av);
-    i0 = (int)ceilf(fmaxf((umin - dc.u0) * iau - margin, -1.0f));
-    i1 = (int)floorf(fminf((umax - dc.u0) * iau + margin, (float)nu));
-    j0 = (int)ceilf(fmaxf((vmin - dc.v0) * iav - margin, -1.0f));
-    j1 = (int)floorf(fminf((vmax - dc.v0) * iav + margin, (float)nv));
-    i0 = i0 < 0 ? 0 : i0;
-    j0 = j0 < 0 ? 0 : j0;
-    i1 = i1 > nu - 1 ? nu - 1 : i1;
-    j1 = j1 > nv - 1 ? nv - 1 : j1;
-}
-
-// Accumulate r * corner weights of sample weights (wx, wy, wz).
-__device__ __forceinline__ void add_corners(double acc[8], double rv, double wx, double wy,
-                                            double wz) {
-    typedef double T;
-    const T b1 = rv * wz, b0 = rv - b1;
-    const T a01 = b0 * wy, a00 = b0 - a01;
-    const T a11 = b1 * wy, a10 = b1 - a11;
-    T t;
-    t = a00 * wx; acc[0] += a00 - t; acc[1] += t;
-    t = a01 * wx; acc[2] += a01 - t; acc[3] += t;
-    t = a10 * wx; acc[4] += a10 - t; acc[5] += t;
-    t = a11 * wx; acc[6] += a11 - t; acc[7] += t;
-}
-
-// Samples n0 .. n1 of a ray that fall in cell (cx, cy, cz), double data.
-__device__ __forceinline__ void cell_samples_d(double acc[8], double rv, const double Qd[3],
-                                               const double D[3], int n0, int n1, int cx,
-                                               int cy, int cz) {
-    double nf = (double)n0;
-    for (int n = n0; n <= n1; ++n, nf += 1.0) {
-        const double q0 = sample_coord(nf, D[0], Qd[0]);
-        const double q1 = sample_coord(nf, D[1], Qd[1]);
-        const double q2 = sample_coord(nf, D[2], Qd[2]);
-        const double f0 = floor_t(q0), f1 = floor_t(q1), f2 = floor_t(q2);
-        if ((int)f0 != cx || (int)f1 != cy || (int)f2 != cz) continue;
-        add_corners(acc, rv, q0 - f0, q1 - f1, q2 - f2);
-    }
-}
+template <typename T> __device__ __forceinline__ T fma_t(T a, T b, T c);
+template <> __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+template <> __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float min_t(float a, float b) { return fminf(a, b); }
+__device__ __forceinline__ double min_t(double a, double b) { return fmin(a, b); }
+__device__ __forceinline__ float max_t(float a, float b) { return fmaxf(a, b); }
+__device__ __forceinline__ double max_t(double a, double b) { return fmax(a, b); }
+__device__ __forceinline__ float ceil_t(float a) { return __builtin_ceilf(a); }
+__device__ __forceinline__ double ceil_t(double a) { return __builtin_ceil(a); }
 
 // Geometry-only preparation, once per plan and workspace:
 //   k_rays:        the increment D (double) of the ray through every pixel of
@@ -342,7 +233,7 @@ __global__ __launch_bounds__(64) void k_brick_views(const ViewConst *__restrict_
 }
 
 // ---------------------------------------------------------------------------
-// Float pass 1.
+// Pass 1.
 //
 // Staged ray of the current footprints, relative to its brick: n counts the
 // ray's samples from the first one in the brick, N of them lie in it, and
@@ -350,10 +241,13 @@ __global__ __launch_bounds__(64) void k_brick_views(const ViewConst *__restrict_
 // first cell.  inv = 1/D, off = -f inv: fma(c, inv, off) is the (real) n at
 // which the ray crosses face c.  For z, of which a brick has one layer, the
 // centred weight is fma(n, D_z, fz) itself.
-struct StagedRay {
-    float4 a;  // inv_x, off_x, inv_y, off_y
-    float4 b;  // D_x, D_y, D_z, f_z - 1/2
-    float2 c;  // N, residual
+template <typename T> using vec4 = T __attribute__((ext_vector_type(4)));
+template <typename T> using vec2 = T __attribute__((ext_vector_type(2)));
+
+template <typename T> struct StagedRay {
+    vec4<T> a;  // inv_x, off_x, inv_y, off_y
+    vec4<T> b;  // D_x, D_y, D_z, f_z - 1/2
+    vec2<T> c;  // N, residual
 };
 
 // The ray with increment D and its residual rv as the brick's cells use it.
@@ -367,31 +261,32 @@ struct StagedRay {
 // voxels) may get the cell beside the exact one; its weights, formed from
 // its position in that cell, then differ from the exact ones by a second
 // order of that distance.
-__device__ __forceinline__ StagedRay stage_ray(const double D[3], const double Qd[3], int nmid,
-                                               const int c0[3], const int c1[3], float rv) {
-    StagedRay e;
+template <typename T>
+__device__ __forceinline__ StagedRay<T> stage_ray(const double D[3], const double Qd[3], int nmid,
+                                                  const int c0[3], const int c1[3], T rv) {
+    StagedRay<T> e;
     double qm[3];
-    float Df[3], inv[3];
-    float lo = -8388608.0f, hi = 8388608.0f;  // 2^23: beyond every sample
+    T Dt[3], inv[3];
+    T lo = T(-8388608), hi = T(8388608);  // 2^23: beyond every sample
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         qm[a] = __builtin_fma((double)nmid, D[a], Qd[a]);
-        const float q = (float)qm[a];
-        Df[a] = (float)D[a];
-        inv[a] = __builtin_amdgcn_rcpf(Df[a]);
-        const float t0 = ((float)c0[a] - q) * inv[a], t1 = ((float)c1[a] - q) * inv[a];
-        lo = fmaxf(lo, fminf(t0, t1));
-        hi = fminf(hi, fmaxf(t0, t1));
+        const T q = (T)qm[a];
+        Dt[a] = (T)D[a];
+        inv[a] = rcp(Dt[a]);
+        const T t0 = ((T)c0[a] - q) * inv[a], t1 = ((T)c1[a] - q) * inv[a];
+        lo = max_t(lo, min_t(t0, t1));
+        hi = min_t(hi, max_t(t0, t1));
     }
-    lo = fminf(__builtin_ceilf(lo), 8388608.0f);
-    hi = __builtin_ceilf(hi);
-    float f[3];
+    lo = min_t(ceil_t(lo), T(8388608));
+    hi = ceil_t(hi);
+    T f[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
-        f[a] = (float)(__builtin_fma((double)lo, D[a], qm[a]) - (double)c0[a]);
-    e.a = make_float4(inv[0], -f[0] * inv[0], inv[1], -f[1] * inv[1]);
-    e.b = make_float4(Df[0], Df[1], Df[2], f[2] - 0.5f);
-    e.c = make_float2(fmaxf(hi - lo, 0.0f), rv);
+        f[a] = (T)(__builtin_fma((double)lo, D[a], qm[a]) - (double)c0[a]);
+    e.a = vec4<T>{inv[0], -f[0] * inv[0], inv[1], -f[1] * inv[1]};
+    e.b = vec4<T>{Dt[0], Dt[1], Dt[2], f[2] - T(0.5)};
+    e.c = vec2<T>{max_t(hi - lo, T(0)), rv};
     return e;
 }
 
@@ -400,17 +295,18 @@ __device__ __forceinline__ StagedRay stage_ray(const double D[3], const double Q
 // c = (face 0) - (the cell's lower face) - 1/2 of the weights.  Face 0 is
 // the one the ray enters through when the directions of the rays are known
 // (ORDERED), else the lower one.
-struct CellFaces {
-    float x0, x1, y0, y1;
-    float cx, cy;
+template <typename T> struct CellFaces {
+    T x0, x1, y0, y1;
+    T cx, cy;
 };
 
-// a * b, and zero where either is zero, whatever the other: one instruction.
+// a * b, and zero where b is zero, whatever a: one instruction in float.
 __device__ __forceinline__ float mul_zero(float a, float b) {
     float p;
     asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(p) : "v"(a), "v"(b));
     return p;
 }
+__device__ __forceinline__ double mul_zero(double a, double b) { return b == 0.0 ? 0.0 : a * b; }
 
 // Add the ray's samples in the cell to the moments m = sum r (1, x, y, z,
 // xy, xz, yz, xyz), x, y, z the weights minus 1/2.
@@ -427,46 +323,47 @@ __device__ __forceinline__ float mul_zero(float a, float b) {
 //
 // A = r k by mul_zero: a residual that is not finite then adds nothing to
 // the cells its ray does not cross.
-template <bool ORDERED>
-__device__ __forceinline__ void crossing_sums(float m[8], const float4 ra, const float4 rb,
-                                              const float2 rc, const CellFaces &cf) {
-    const float tx0 = __builtin_fmaf(cf.x0, ra.x, ra.y), tx1 = __builtin_fmaf(cf.x1, ra.x, ra.y);
-    const float ty0 = __builtin_fmaf(cf.y0, ra.z, ra.w), ty1 = __builtin_fmaf(cf.y1, ra.z, ra.w);
-    const float n0 = __builtin_ceilf(
-        ORDERED ? fmaxf(fmaxf(tx0, ty0), 0.0f)
-                : fmaxf(fmaxf(fminf(tx0, tx1), fminf(ty0, ty1)), 0.0f));
-    const float n1 = __builtin_ceilf(
-        ORDERED ? fminf(fminf(tx1, ty1), rc.x)
-                : fminf(fminf(fmaxf(tx0, tx1), fmaxf(ty0, ty1)), rc.x));
-    const float k = fmaxf(n1 - n0, 0.0f);
-    const float n = __builtin_fmaf(0.5f, n0 + n1, -0.5f);
-    const float x = __builtin_fmaf(n - tx0, rb.x, cf.cx);
-    const float y = __builtin_fmaf(n - ty0, rb.y, cf.cy);
-    const float z = __builtin_fmaf(n, rb.z, rb.w);
-    const float A = mul_zero(rc.y, k);
-    const float B = A * __builtin_fmaf(k * k, 1.0f / 12.0f, -1.0f / 12.0f);
-    const float bx = B * rb.x, by = B * rb.y;
-    const float bxy = bx * rb.y, bxz = bx * rb.z, byz = by * rb.z;
-    const float px = A * x, py = A * y;
-    const float pxy = __builtin_fmaf(px, y, bxy);
+template <bool ORDERED, typename T>
+__device__ __forceinline__ void crossing_sums(T m[8], const vec4<T> ra, const vec4<T> rb,
+                                              const vec2<T> rc, const CellFaces<T> &cf) {
+    const T tx0 = fma_t(cf.x0, ra.x, ra.y), tx1 = fma_t(cf.x1, ra.x, ra.y);
+    const T ty0 = fma_t(cf.y0, ra.z, ra.w), ty1 = fma_t(cf.y1, ra.z, ra.w);
+    const T n0 = ceil_t(
+        ORDERED ? max_t(max_t(tx0, ty0), T(0))
+                : max_t(max_t(min_t(tx0, tx1), min_t(ty0, ty1)), T(0)));
+    const T n1 = ceil_t(
+        ORDERED ? min_t(min_t(tx1, ty1), rc.x)
+                : min_t(min_t(max_t(tx0, tx1), max_t(ty0, ty1)), rc.x));
+    const T k = max_t(n1 - n0, T(0));
+    const T n = fma_t(T(0.5), n0 + n1, T(-0.5));
+    const T x = fma_t(n - tx0, rb.x, cf.cx);
+    const T y = fma_t(n - ty0, rb.y, cf.cy);
+    const T z = fma_t(n, rb.z, rb.w);
+    const T A = mul_zero(rc.y, k);
+    const T B = A * fma_t(k * k, T(1) / T(12), T(-1) / T(12));
+    const T bx = B * rb.x, by = B * rb.y;
+    const T bxy = bx * rb.y, bxz = bx * rb.z, byz = by * rb.z;
+    const T px = A * x, py = A * y;
+    const T pxy = fma_t(px, y, bxy);
     m[0] += A;
     m[1] += px;
     m[2] += py;
-    m[3] = __builtin_fmaf(A, z, m[3]);
+    m[3] = fma_t(A, z, m[3]);
     m[4] += pxy;
-    m[5] = __builtin_fmaf(px, z, m[5]) + bxz;
-    m[6] = __builtin_fmaf(py, z, m[6]) + byz;
-    m[7] = __builtin_fmaf(pxy, z, __builtin_fmaf(bxz, y, __builtin_fmaf(byz, x, m[7])));
+    m[5] = fma_t(px, z, m[5]) + bxz;
+    m[6] = fma_t(py, z, m[6]) + byz;
+    m[7] = fma_t(pxy, z, fma_t(bxz, y, fma_t(byz, x, m[7])));
 }
 
 // Corner sums (index ox + 2 oy + 4 oz): corner weights are the products of
 // 1/2 -+ x, 1/2 -+ y and 1/2 -+ z.
-__device__ __forceinline__ void moments_to_corners(const float m[8], float c[8]) {
+template <typename T>
+__device__ __forceinline__ void moments_to_corners(const T m[8], T c[8]) {
 #pragma unroll
     for (int o = 0; o < 8; ++o) {
-        const float sx = o & 1 ? 1.0f : -1.0f, sy = o & 2 ? 1.0f : -1.0f, sz = o & 4 ? 1.0f : -1.0f;
-        c[o] = 0.125f * m[0] + 0.25f * (sx * m[1] + sy * m[2] + sz * m[3]) +
-               0.5f * (sx * sy * m[4] + sx * sz * m[5] + sy * sz * m[6]) + sx * sy * sz * m[7];
+        const T sx = o & 1 ? 1 : -1, sy = o & 2 ? 1 : -1, sz = o & 4 ? 1 : -1;
+        c[o] = T(0.125) * m[0] + T(0.25) * (sx * m[1] + sy * m[2] + sz * m[3]) +
+               T(0.5) * (sx * sy * m[4] + sx * sz * m[5] + sy * sz * m[6]) + sx * sy * sz * m[7];
     }
 }
 
@@ -487,12 +384,17 @@ __device__ __forceinline__ void moments_to_corners(const float m[8], float c[8])
 // Table of 560 rays: seven groups fill the LDS (22.4 KB) as the 68 VGPRs
 // allow; 480 rays 1.5% slower, 650 (six groups) 2%.  Up to six views a
 // batch: 1 to 2% over four.
-__global__ __launch_bounds__(256) void k_cells_f(
+//
+// Double data (derivative checks) took every candidate sample of every pixel
+// from the ray table; with the staged rays and the closed form a transpose
+// of 32^3 from 60 views takes 163 us instead of 213.
+template <typename T>
+__global__ __launch_bounds__(256) void k_cells(
     const ViewConst *__restrict__ views, GridConst gc, int nu, int nv, int nviews,
     const PixelRay *__restrict__ rays, const BrickView *__restrict__ bviews,
-    const float *__restrict__ r, float *__restrict__ cells, float step) {
-    __shared__ float4 tab[2 * TABLE];
-    __shared__ float2 tabc[TABLE];
+    const T *__restrict__ r, T *__restrict__ cells, T step) {
+    __shared__ vec4<T> tab[2 * TABLE];
+    __shared__ vec2<T> tabc[TABLE];
     __shared__ int4 slots[PARTS];  // first entry, width, first pixel of the batch's views
     static_assert(CB_Z == 1, "a brick is one z layer of cells");
     const int tid = threadIdx.x;
@@ -510,9 +412,9 @@ __global__ __launch_bounds__(256) void k_cells_f(
     // other in the table, whatever the view's direction.
     const int lx = (tid & 3) | ((tid >> 2) & 4) | ((tid >> 3) & 8);
     const int ly = ((tid >> 2) & 3) | ((tid >> 3) & 4) | ((tid >> 4) & 8);
-    float m[8];
+    T m[8];
 #pragma unroll
-    for (int o = 0; o < 8; ++o) m[o] = 0.0f;
+    for (int o = 0; o < 8; ++o) m[o] = T(0);
 
     for (int k = 0; k < nviews;) {
         // the batch, or the parts of a view too large for the table: bands of
@@ -567,7 +469,7 @@ __global__ __launch_bounds__(256) void k_cells_f(
                 const PixelRay g = rays[pix];
                 const ViewConst &vc = views[k + v];
                 const double Qd[3] = {vc.Qd[0], vc.Qd[1], vc.Qd[2]};
-                const StagedRay ray = stage_ray(g.D, Qd, vc.nmid, f0, f1, r[pix]);
+                const StagedRay<T> ray = stage_ray(g.D, Qd, vc.nmid, f0, f1, r[pix]);
                 tab[t] = ray.a;
                 tab[t + TABLE] = ray.b;
                 tabc[t] = ray.c;
@@ -580,13 +482,13 @@ __global__ __launch_bounds__(256) void k_cells_f(
             const float fx0 = px == 0 ? -0.25f : fx, fy0 = py == 0 ? -0.25f : fy;
             const float fx1 = fx + (c0[0] + px + 1 == c1[0] ? 1.25f : 1.0f);
             const float fy1 = fy + (c0[1] + py + 1 == c1[1] ? 1.25f : 1.0f);
-            CellFaces cf;
+            CellFaces<T> cf;
             cf.x0 = dirs == 0 || (dirs & 1) ? fx0 : fx1;
             cf.x1 = dirs == 0 || (dirs & 1) ? fx1 : fx0;
             cf.y0 = dirs == 0 || (dirs & 2) ? fy0 : fy1;
             cf.y1 = dirs == 0 || (dirs & 2) ? fy1 : fy0;
-            cf.cx = cf.x0 - fx - 0.5f;
-            cf.cy = cf.y0 - fy - 0.5f;
+            cf.cx = cf.x0 - fx - T(0.5);
+            cf.cy = cf.y0 - fy - T(0.5);
             auto visit = [&](auto ordered) {
                 constexpr bool ORD = decltype(ordered)::value;
                 for (int v = 0; v < n; ++v) {
@@ -605,8 +507,8 @@ __global__ __launch_bounds__(256) void k_cells_f(
                         continue;
                     const int e =
                         b.base + max(min(cj, bh - H), 0) * bw + max(min(ci, bw - W), 0);
-                    const float4 *p = tab + e;
-                    const float2 *pc = tabc + e;
+                    const vec4<T> *p = tab + e;
+                    const vec2<T> *pc = tabc + e;
                     for (int y = 0; y < H; ++y, p += bw, pc += bw) {
                         int x = 0;
                         for (; x + 1 < W; x += 2) {
@@ -629,73 +531,10 @@ __global__ __launch_bounds__(256) void k_cells_f(
     const long long ncell = cp * (gc.ny + 1) * (gc.nz + 1);
     const long long lin = (long long)(c0[0] + 1 + lx) +
                           cp * ((c0[1] + 1 + ly) + (long long)(gc.ny + 1) * (c0[2] + 1));
-    float out[8];
+    T out[8];
     moments_to_corners(m, out);
 #pragma unroll
     for (int o = 0; o < 8; ++o) cells[o * ncell + lin] = out[o] * step;
-}
-
-// Double pass 1 (derivative checks): every candidate sample of every pixel
-// of the cell's rectangle, in double, from the ray table.
-__global__ __launch_bounds__(256) void k_cells_d(const ViewConst *__restrict__ views, DetConst dc,
-                                                 GridConst gc, int nu, int nv, int nviews,
-                                                 const PixelRay *__restrict__ rays,
-                                                 const BrickView *__restrict__ bviews,
-                                                 const double *__restrict__ r,
-                                                 double *__restrict__ cells, double step) {
-    const int tid = threadIdx.x;
-    const int nbx = (gc.nx + 1 + CB_X - 1) / CB_X, nby = (gc.ny + 1 + CB_Y - 1) / CB_Y;
-    const int brick = xcd_tile(blockIdx.x, gridDim.x);
-    const int cx = (brick % nbx) * CB_X - 1 + tid % CB_X;
-    const int cy = ((brick / nbx) % nby) * CB_Y - 1 + (tid / CB_X) % CB_Y;
-    const int cz = (brick / (nbx * nby)) * CB_Z - 1 + tid / (CB_X * CB_Y);
-    if (cx >= gc.nx || cy >= gc.ny || cz >= gc.nz) return;
-    // the cell's box (mm)
-    const float xa = gc.x0 + (float)cx * gc.hx, xb = gc.x0 + (float)(cx + 1) * gc.hx;
-    const float ya = gc.y0 + (float)cy * gc.hy, yb = gc.y0 + (float)(cy + 1) * gc.hy;
-    const float za = gc.z0 + (float)cz * gc.hz, zb = gc.z0 + (float)(cz + 1) * gc.hz;
-    double acc[8];
-#pragma unroll
-    for (int o = 0; o < 8; ++o) acc[o] = 0.0;
-    for (int k = 0; k < nviews; ++k) {
-        const ViewConst vc = views[k];
-        const long long vbase = (long long)k * nu * nv;
-        const BrickView &rect = bviews[(long long)brick * nviews + k];
-        float umin, umax, vmin, vmax;
-        box_footprint(vc, dc.sdd, xa, xb, ya, yb, za, zb, umin, umax, vmin, vmax);
-        int i0, i1, j0, j1;
-        pixel_range(dc, nu, nv, umin, umax, vmin, vmax, i0, i1, j0, j1);
-        // the cell lies in the brick: keep its pixels inside the brick's
-        // rectangle (they differ at most by rounding, inside the margin)
-        i0 = max(i0, rect.i0);
-        i1 = min(i1, rect.i0 + rect.w - 1);
-        j0 = max(j0, rect.j0);
-        j1 = min(j1, rect.j0 + rect.h - 1);
-        const float Qf[3] = {vc.Q[0], vc.Q[1], vc.Q[2]};
-        const CellRange cr = cell_range(Qf, (float)cx, (float)cy, (float)cz);
-        const int w = i1 - i0 + 1, h = j1 - j0 + 1;
-        const int npix = (w > 0 && h > 0) ? w * h : 0;
-        int i = i0, j = j0;
-        for (int q = 0; q < npix; ++q) {
-            const long long pix = vbase + (long long)j * nu + i;
-            if (++i > i1) {
-                i = i0;
-                ++j;
-            }
-            const PixelRay g = rays[pix];
-            float inv[3];
-            ray_inv(g, inv);
-            int n0, n1;
-            if (!candidates_inv(cr, inv, n0, n1)) continue;
-            cell_samples_d(acc, r[pix], vc.Qd, g.D, n0, n1, cx, cy, cz);
-        }
-    }
-    const long long cp = cell_pitch(gc.nx);
-    const long long ncell = cp * (gc.ny + 1) * (gc.nz + 1);
-    const long long lin = (long long)(cx + 1) +
-                          cp * ((cy + 1) + (long long)(gc.ny + 1) * (cz + 1));
-#pragma unroll
-    for (int o = 0; o < 8; ++o) cells[o * ncell + lin] = acc[o] * step;
 }
 
 // Pass 2: out = sum of corner o of cell (v - o) over o in {0,1}^3,
@@ -905,12 +744,8 @@ hipError_t launch_backproject_cells(const cbct_plan &p, const T *r, void *cells,
     const dim3 grid(b.x * b.y * b.z);
     const PixelRay *rays = (const PixelRay *)base;
     const BrickView *bv = (const BrickView *)(base + l.bricks);
-    if constexpr (sizeof(T) == 4)
-        hipLaunchKernelGGL(k_cells_f, grid, dim3(256), 0, s, p.d_views, p.grid, p.g.nu, p.g.nv,
-                           p.g.n_views, rays, bv, r, (T *)cells, (T)p.g.step);
-    else
-        hipLaunchKernelGGL(k_cells_d, grid, dim3(256), 0, s, p.d_views, p.det, p.grid, p.g.nu,
-                           p.g.nv, p.g.n_views, rays, bv, r, (T *)cells, (T)p.g.step);
+    hipLaunchKernelGGL(k_cells<T>, grid, dim3(256), 0, s, p.d_views, p.grid, p.g.nu, p.g.nv,
+                       p.g.n_views, rays, bv, r, (T *)cells, (T)p.g.step);
     return hipGetLastError();
 }
 
