@@ -185,12 +185,12 @@ __device__ BrickView brick_view(const ViewConst &vc, const DetConst &dc, const G
 }
 
 // One wavefront per brick, one view per lane, 64 views at a time (batches end
-// there); the wavefront then walks its lanes' footprints to form the batches,
+// there, and at multiples of chunk); the wavefront then walks its lanes' footprints to form the batches,
 // in scalar registers.
 __global__ __launch_bounds__(64) void k_brick_views(const ViewConst *__restrict__ views,
                                                     DetConst dc, GridConst gc, double hx,
                                                     double hy, double hz, int nu, int nv,
-                                                    int nbx, int nby, int nviews,
+                                                    int nbx, int nby, int nviews, int chunk,
                                                     BrickView *__restrict__ out) {
     const int b = blockIdx.x, lane = threadIdx.x;
     const int c0[3] = {(b % nbx) * CB_X - 1, ((b / nbx) % nby) * CB_Y - 1,
@@ -221,7 +221,9 @@ __global__ __launch_bounds__(64) void k_brick_views(const ViewConst *__restrict_
                 close(q + 1);
                 continue;
             }
-            if (n == PARTS || rays + sq > TABLE || (rays > 0 && sq > 0 && dq != dirs)) close(q);
+            if (n == PARTS || rays + sq > TABLE || (rays > 0 && sq > 0 && dq != dirs) ||
+                (k0 + q) % chunk == 0)
+                close(q);
             if (rays == 0) dirs = dq;
             if (lane == q) o.base = rays;
             rays += sq;
@@ -387,10 +389,10 @@ __device__ __forceinline__ void moments_to_corners(const T m[8], T c[8]) {
 //
 // Double data (derivative checks) took every candidate sample of every pixel
 // from the ray table; with the staged rays and the closed form a transpose
-// of 32^3 from 60 views takes 163 us instead of 213.
+// of 32^3 from 60 views takes 76 us instead of 213 (163 with one chunk of views).
 template <typename T>
 __global__ __launch_bounds__(256) void k_cells(
-    const ViewConst *__restrict__ views, GridConst gc, int nu, int nv, int nviews,
+    const ViewConst *__restrict__ views, GridConst gc, int nu, int nv, int nviews, int chunk,
     const PixelRay *__restrict__ rays, const BrickView *__restrict__ bviews,
     const T *__restrict__ r, T *__restrict__ cells, T step) {
     __shared__ vec4<T> tab[2 * TABLE];
@@ -416,7 +418,8 @@ __global__ __launch_bounds__(256) void k_cells(
 #pragma unroll
     for (int o = 0; o < 8; ++o) m[o] = T(0);
 
-    for (int k = 0; k < nviews;) {
+    const int kend = min(nviews, (int)(blockIdx.y + 1) * chunk);
+    for (int k = blockIdx.y * chunk; k < kend;) {
         // the batch, or the parts of a view too large for the table: bands of
         // rows, or pieces of a row
         int n = bv[k].batch_n, total = bv[k].batch_rays;
@@ -533,14 +536,16 @@ __global__ __launch_bounds__(256) void k_cells(
                           cp * ((c0[1] + 1 + ly) + (long long)(gc.ny + 1) * (c0[2] + 1));
     T out[8];
     moments_to_corners(m, out);
+    cells += 8 * ncell * blockIdx.y;
 #pragma unroll
     for (int o = 0; o < 8; ++o) cells[o * ncell + lin] = out[o] * step;
 }
 
-// Pass 2: out = sum of corner o of cell (v - o) over o in {0,1}^3,
-// then out = f - tau * out when f is given.
+// Pass 2: out = sum of corner o of cell (v - o) over o in {0,1}^3 and over the
+// chunks of views, then out = f - tau * out when f is given.
 template <typename T>
-__global__ __launch_bounds__(256) void k_gather(GridConst gc, const T *__restrict__ cells,
+__global__ __launch_bounds__(256) void k_gather(GridConst gc, int chunks,
+                                                const T *__restrict__ cells,
                                                 const T *__restrict__ f, T tau,
                                                 T *__restrict__ out) {
     const int ix = blockIdx.x * G_BX + threadIdx.x;
@@ -552,12 +557,13 @@ __global__ __launch_bounds__(256) void k_gather(GridConst gc, const T *__restric
     // cell (ix - ox, iy - oy, iz - oz) is stored at (ix - ox + 1, ...)
     const long long base = (long long)(ix + 1) + cxn * (iy + 1) + cxyn * (iz + 1);
     T s = T(0);
+    for (int c = 0; c < chunks; ++c, cells += 8 * ncell)
 #pragma unroll
-    for (int o = 0; o < 8; ++o) {
-        const int ox = o & 1, oy = (o >> 1) & 1, oz = o >> 2;
-        // voxel v is corner o of cell v - o (corners of cell c are c + o)
-        s += cells[o * ncell + base - ox - oy * cxn - oz * cxyn];
-    }
+        for (int o = 0; o < 8; ++o) {
+            const int ox = o & 1, oy = (o >> 1) & 1, oz = o >> 2;
+            // voxel v is corner o of cell v - o (corners of cell c are c + o)
+            s += cells[o * ncell + base - ox - oy * cxn - oz * cxyn];
+        }
     const long long v = (long long)ix + (long long)gc.nx * (iy + (long long)gc.ny * iz);
     out[v] = f ? f[v] - tau * s : s;
 }
@@ -682,6 +688,29 @@ dim3 brick_grid(const cbct_geom &g) {
                 (g.nz + 1 + CB_Z - 1) / CB_Z);
 }
 
+// Views a workgroup of the cell pass takes.  A small grid has fewer bricks
+// than the chip has room for (about 1800 workgroups), and each works its way
+// through the views' loads and barriers alone; its views are then cut into
+// up to eight chunks of four or more, with cell sums of their own, as long
+// as no more than SPLIT_GROUPS workgroups result.  Transposes with 1 chunk,
+// with up to 3072 workgroups and with up to 6144 (us): 32^3 / 60 views
+// 115 / 50 / 50, 48^3 / 16 47 / 38 / 39, 64^3 / 16 79 / 79 / 67, 64^3 / 60
+// 197 / 197 / 164; 80^3 and 96^3 / 16 lose 3 to 9% with two chunks.
+constexpr int SPLIT_GROUPS = 6144, SPLIT_MAX = 8, SPLIT_VIEWS = 4;
+
+int view_chunk(const cbct_geom &g) {
+    const dim3 b = brick_grid(g);
+    const long long bricks = (long long)b.x * b.y * b.z;
+    const int want = (int)std::min((long long)SPLIT_MAX, SPLIT_GROUPS / bricks);
+    const int n = std::max(1, std::min(want, g.n_views / SPLIT_VIEWS));
+    return (g.n_views + n - 1) / n;
+}
+
+int view_chunks(const cbct_geom &g) {
+    const int c = view_chunk(g);
+    return (g.n_views + c - 1) / c;
+}
+
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Geometry tables of the transpose: the ray table at offset 0, then the
@@ -701,7 +730,7 @@ GeomLayout geom_layout(const cbct_geom &g) {
 }  // namespace
 
 size_t bp_cells_bytes(const cbct_geom &g, size_t elem) {
-    return align256(elem * 8 * (size_t)cell_pitch(g.nx) * (g.ny + 1) * (g.nz + 1));
+    return align256(elem * 8 * view_chunks(g) * (size_t)cell_pitch(g.nx) * (g.ny + 1) * (g.nz + 1));
 }
 
 size_t bp_geom_bytes(const cbct_geom &g) { return geom_layout(g).total; }
@@ -731,7 +760,7 @@ hipError_t launch_bp_prepare(const cbct_plan &p, void *geom, hipStream_t s) {
     const dim3 b = brick_grid(p.g);
     hipLaunchKernelGGL(k_brick_views, dim3(b.x * b.y * b.z), dim3(64), 0, s, p.d_views, p.det,
                        p.grid, p.g.hx, p.g.hy, p.g.hz, p.g.nu, p.g.nv, (int)b.x, (int)b.y,
-                       p.g.n_views, (BrickView *)(base + l.bricks));
+                       p.g.n_views, view_chunk(p.g), (BrickView *)(base + l.bricks));
     return hipGetLastError();
 }
 
@@ -741,11 +770,11 @@ hipError_t launch_backproject_cells(const cbct_plan &p, const T *r, void *cells,
     const GeomLayout l = geom_layout(p.g);
     const char *base = (const char *)geom;
     const dim3 b = brick_grid(p.g);
-    const dim3 grid(b.x * b.y * b.z);
+    const dim3 grid(b.x * b.y * b.z, view_chunks(p.g));
     const PixelRay *rays = (const PixelRay *)base;
     const BrickView *bv = (const BrickView *)(base + l.bricks);
     hipLaunchKernelGGL(k_cells<T>, grid, dim3(256), 0, s, p.d_views, p.grid, p.g.nu, p.g.nv,
-                       p.g.n_views, rays, bv, r, (T *)cells, (T)p.g.step);
+                       p.g.n_views, view_chunk(p.g), rays, bv, r, (T *)cells, (T)p.g.step);
     return hipGetLastError();
 }
 
@@ -753,8 +782,8 @@ template <typename T>
 hipError_t launch_gather_cells(const cbct_plan &p, const void *ws, const T *f, double tau,
                                T *out, hipStream_t s) {
     dim3 grid((p.g.nx + G_BX - 1) / G_BX, (p.g.ny + G_BY - 1) / G_BY, p.g.nz);
-    hipLaunchKernelGGL(k_gather<T>, grid, dim3(G_BX, G_BY), 0, s, p.grid, (const T *)ws, f,
-                       (T)tau, out);
+    hipLaunchKernelGGL(k_gather<T>, grid, dim3(G_BX, G_BY), 0, s, p.grid, view_chunks(p.g),
+                       (const T *)ws, f, (T)tau, out);
     return hipGetLastError();
 }
 

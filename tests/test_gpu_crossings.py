@@ -50,6 +50,8 @@ CASES = {
     # close source: wide fans, rays of both signs in one brick
     "wide_angle": dataclasses.replace(BASE, nx=40, ny=40, nz=20, nu=64, nv=40, au=4.0, av=4.0,
                                       sad=62.0, sdd=120.0, n_views=16),
+    # the views in chunks that end inside and across batches of 64
+    "many_views": dataclasses.replace(BASE, n_views=70),
     "shifted": dataclasses.replace(BASE, x_off=41.3, y_off=-17.7, z_off=6.1, u_off=9.0, nu=80,
                                    n_views=11),
 }
