@@ -429,21 +429,20 @@ template <typename T>
 int project_impl(const cbct_plan *p, const T *f, const T *Y, T *out, double *sumsq,
                  hipStream_t s) {
     if (!p || !f || !out) return set_error(CBCT_EINVAL, "NULL argument");
-    Scratch pad(s), part(s);
-    int rc = check_hip(pad.alloc(sizeof(T) * padded_count(*p)), "scratch (padded volume)");
-    if (rc) return rc;
+    // one block for the padded volume and the partial sums: an allocation
+    // and its return cost the host about 10 us, more than these launches
+    Scratch pad(s);
     const size_t np = project_partials_count(*p);
-    if (sumsq) {
-        rc = check_hip(part.alloc(sizeof(double) * np), "scratch (partials)");
-        if (rc) return rc;
-    }
+    const size_t at = (sizeof(T) * padded_count(*p) + 255) & ~(size_t)255;
+    int rc = check_hip(pad.alloc(at + (sumsq ? sizeof(double) * np : 0)), "scratch (padded volume)");
+    if (rc) return rc;
+    double *part = sumsq ? reinterpret_cast<double *>(pad.as<char>() + at) : nullptr;
     rc = check_hip(timed(CBCT_KERNEL_PAD, s, [&] { return launch_pad<T>(*p, f, pad.as<T>(), s); }), "pad kernel");
     if (rc) return rc;
-    rc = check_hip(timed(CBCT_KERNEL_PROJECT, s, [&] { return launch_project<T>(*p, pad.as<T>(), Y, out, sumsq ? part.as<double>() : nullptr,
-                                     s); }),
+    rc = check_hip(timed(CBCT_KERNEL_PROJECT, s, [&] { return launch_project<T>(*p, pad.as<T>(), Y, out, part, s); }),
                    "project kernel");
     if (rc) return rc;
-    if (sumsq) rc = check_hip(timed(CBCT_KERNEL_OTHER, s, [&] { return launch_reduce_sum(part.as<double>(), (int)np, sumsq, 1, s); }), "reduce");
+    if (sumsq) rc = check_hip(timed(CBCT_KERNEL_OTHER, s, [&] { return launch_reduce_sum(part, (int)np, sumsq, 1, s); }), "reduce");
     return rc;
 }
 
@@ -690,15 +689,15 @@ extern "C" int cbct_tv_energy(const cbct_geom *grid, const float *f, double eps,
     if (!f || !out_host) return set_error(CBCT_EINVAL, "NULL argument");
     hipStream_t s = as_stream(stream);
     const GridConst gc = grid_of(*grid);
-    Scratch part(s), res(s);
-    rc = check_hip(part.alloc(sizeof(double) * tv_energy_partials_count(gc)), "scratch");
+    Scratch part(s);  // the partial sums, and after them the two results
+    const size_t np = tv_energy_partials_count(gc);
+    rc = check_hip(part.alloc(sizeof(double) * (np + 2)), "scratch");
     if (rc) return rc;
-    rc = check_hip(res.alloc(sizeof(double) * 2), "scratch");
-    if (rc) return rc;
-    rc = tv_sums(gc, f, eps, part.as<double>(), res.as<double>(), s);
+    double *res = part.as<double>() + np;
+    rc = tv_sums(gc, f, eps, part.as<double>(), res, s);
     if (rc) return rc;
     double h[2];
-    rc = check_hip(hipMemcpyAsync(h, res.p, sizeof(h), hipMemcpyDeviceToHost, s), "readback");
+    rc = check_hip(hipMemcpyAsync(h, res, sizeof(h), hipMemcpyDeviceToHost, s), "readback");
     if (rc) return rc;
     rc = check_hip(hipStreamSynchronize(s), "sync");
     if (rc) return rc;
