@@ -306,7 +306,8 @@ int cbct_probe_fma_rate(int32_t fp64, double *tflops_host, void *stream);
  * array out_host (at most n entries): [0] projector tile width and [1]
  * height in pixels, [2] samples per box (the projector stages runs of
  * such pieces), [3] LDS box capacity in floats; [4..6] transpose brick in
- * cells (x, y, z), [7] LDS table capacity in pixels.  A piece whose box
+ * cells (x, y, z; near-square ones of no more cells where they cover a grid
+ * with fewer bricks), [7] LDS table capacity in pixels.  A piece whose box
  * exceeds [3] reads global memory instead of LDS, and a brick whose
  * footprint on the detector exceeds [7] pixels is staged in parts (same
  * results).  Returns the number of entries written (8 when n >= 8),

@@ -10,7 +10,9 @@
 //   * preparation (geometry only, once per plan or workspace): the ray
 //     increment of every pixel of every view, and every brick's footprint
 //     on the detector and map from cells to pixels per view;
-//   * pass 1 (one lane per cell, a workgroup per 16x16x1 brick of cells):
+//   * pass 1 (one lane per cell, a workgroup per brick of 16x16x1 cells or of
+//     about as many; of few bricks, several per brick with a share of the
+//     views each):
 //     for every view the workgroup stages the rays of its brick's footprint
 //     in LDS; each lane then visits the pixels whose rays can cross its
 //     cell and adds each ray's samples in the cell, r * (trilinear corner
@@ -31,7 +33,7 @@ namespace cbct {
 
 namespace {
 
-constexpr int CB_X = 16, CB_Y = 16, CB_Z = 1;  // cells per workgroup: one z layer
+constexpr int CB_X = 16, CB_Y = 16, CB_Z = 1;  // cells per workgroup: one z layer (see brick_shape)
 constexpr int TABLE = 560;                     // rays staged at a time (40 B each, 80 in double)
 constexpr int PARTS = 6;                       // views staged at a time, at most
 constexpr int G_BX = 64, G_BY = 4;            // pass-2 block
@@ -190,13 +192,13 @@ __device__ BrickView brick_view(const ViewConst &vc, const DetConst &dc, const G
 __global__ __launch_bounds__(64) void k_brick_views(const ViewConst *__restrict__ views,
                                                     DetConst dc, GridConst gc, double hx,
                                                     double hy, double hz, int nu, int nv,
-                                                    int nbx, int nby, int nviews, int chunk,
+                                                    int2 shape, int nbx, int nby, int nviews,
+                                                    int chunk,
                                                     BrickView *__restrict__ out) {
     const int b = blockIdx.x, lane = threadIdx.x;
-    const int c0[3] = {(b % nbx) * CB_X - 1, ((b / nbx) % nby) * CB_Y - 1,
-                       (b / (nbx * nby)) * CB_Z - 1};
-    const int c1[3] = {min(c0[0] + CB_X, gc.nx), min(c0[1] + CB_Y, gc.ny),
-                       min(c0[2] + CB_Z, gc.nz)};
+    const int c0[3] = {(b % nbx) * shape.x - 1, ((b / nbx) % nby) * shape.y - 1,
+                       b / (nbx * nby) - 1};
+    const int c1[3] = {min(c0[0] + shape.x, gc.nx), min(c0[1] + shape.y, gc.ny), c0[2] + 1};
     for (int k0 = 0; k0 < nviews; k0 += 64) {
         const int k = min(k0 + lane, nviews - 1);
         BrickView o = brick_view(views[k], dc, gc, hx, hy, hz, nu, nv, c0, c1);
@@ -369,7 +371,8 @@ __device__ __forceinline__ void moments_to_corners(const T m[8], T c[8]) {
     }
 }
 
-// Workgroups of 256 lanes, one per 16 x 16 x 1 brick of cells.
+// Workgroups of 256 lanes, one per brick (see brick_shape) and chunk of views
+// (see view_chunk).
 //
 // Bound by VALU issue: a visit of a (ray, cell) pair is 42 VALU and 3 LDS
 // instructions (40 bytes a lane), of which fused multiply-adds take about
@@ -389,11 +392,12 @@ __device__ __forceinline__ void moments_to_corners(const T m[8], T c[8]) {
 //
 // Double data (derivative checks) took every candidate sample of every pixel
 // from the ray table; with the staged rays and the closed form a transpose
-// of 32^3 from 60 views takes 76 us instead of 213 (163 with one chunk of views).
+// of 32^3 from 60 views takes 76 us instead of 213
+// (163 with one chunk of views).
 template <typename T>
 __global__ __launch_bounds__(256) void k_cells(
-    const ViewConst *__restrict__ views, GridConst gc, int nu, int nv, int nviews, int chunk,
-    const PixelRay *__restrict__ rays, const BrickView *__restrict__ bviews,
+    const ViewConst *__restrict__ views, GridConst gc, int2 shape, int nu, int nv, int nviews,
+    int chunk, const PixelRay *__restrict__ rays, const BrickView *__restrict__ bviews,
     const T *__restrict__ r, T *__restrict__ cells, T step) {
     __shared__ vec4<T> tab[2 * TABLE];
     __shared__ vec2<T> tabc[TABLE];
@@ -403,17 +407,22 @@ __global__ __launch_bounds__(256) void k_cells(
     // bricks x-fastest, then y, then z; each XCD takes one contiguous range,
     // so the bricks resident on an XCD at a time are neighbours whose
     // footprints (ray table rows) overlap in its L2
-    const int nbx = (gc.nx + 1 + CB_X - 1) / CB_X, nby = (gc.ny + 1 + CB_Y - 1) / CB_Y;
+    // bricks x-fastest, then y, then z; each XCD takes one contiguous range,
+    // so the bricks resident on an XCD at a time are neighbours whose
+    // footprints (ray table rows) overlap in its L2
+    const int nbx = (gc.nx + shape.x) / shape.x, nby = (gc.ny + shape.y) / shape.y;
     const int brick = xcd_tile(blockIdx.x, gridDim.x);
     const BrickView *bv = bviews + (long long)brick * nviews;
-    const int c0[3] = {(brick % nbx) * CB_X - 1, ((brick / nbx) % nby) * CB_Y - 1,
-                       (brick / (nbx * nby)) * CB_Z - 1};
-    const int c1[3] = {min(c0[0] + CB_X, gc.nx), min(c0[1] + CB_Y, gc.ny), c0[2] + 1};
-    // A wavefront covers 8 x 8 cells, every 16 consecutive lanes 4 x 4 of
-    // them: the rays such lanes read together are then few and near each
-    // other in the table, whatever the view's direction.
-    const int lx = (tid & 3) | ((tid >> 2) & 4) | ((tid >> 3) & 8);
-    const int ly = ((tid >> 2) & 3) | ((tid >> 3) & 4) | ((tid >> 4) & 8);
+    const int c0[3] = {(brick % nbx) * shape.x - 1, ((brick / nbx) % nby) * shape.y - 1,
+                       brick / (nbx * nby) - 1};
+    const int c1[3] = {min(c0[0] + shape.x, gc.nx), min(c0[1] + shape.y, gc.ny), c0[2] + 1};
+    // A wavefront of a 16 x 16 brick covers 8 x 8 cells, every 16 consecutive
+    // lanes 4 x 4 of them: the rays such lanes read together are then few and
+    // near each other in the table, whatever the view's direction.  Other
+    // bricks take their cells row by row (lanes beyond the last row idle).
+    const bool square = shape.x == 16 && shape.y == 16;
+    const int lx = square ? (tid & 3) | ((tid >> 2) & 4) | ((tid >> 3) & 8) : tid % shape.x;
+    const int ly = square ? ((tid >> 2) & 3) | ((tid >> 3) & 4) | ((tid >> 4) & 8) : tid / shape.x;
     T m[8];
 #pragma unroll
     for (int o = 0; o < 8; ++o) m[o] = T(0);
@@ -683,9 +692,32 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
 
 namespace {
 
+// Cells of a brick in x and y: 16 x 16, or of the near-square shapes of at
+// most 256 the one that covers the grid's nx + 1 by ny + 1 cells with the
+// fewest bricks.  A grid of 2^k voxels has one cell more than whole 16 x 16
+// bricks, and a last row and column of nearly empty ones: 18 bricks of
+// 22 x 11 instead of 25 cover 65 x 65 cells, 70 of 13 x 19 instead of 81
+// 129 x 129.  Transposes 16 x 16 / so (us): 64^3 / 16 views 67 / 58, 96^3 / 16
+// 132 / 121, 128^3 / 60 893 / 821.  Rows of other bricks do not line up with
+// the wavefronts: with 3% fewer bricks, at 256 x 256 x 64 and 256^3, the time
+// is the same to 1% more, so 16 x 16 stays where others save less than 5%.
+int2 brick_shape(const cbct_geom &g) {
+    auto bricks = [&](int2 s) {
+        return (long long)((g.nx + s.x) / s.x) * ((g.ny + s.y) / s.y);
+    };
+    const int2 square = make_int2(CB_X, CB_Y);
+    int2 best = square;
+    for (int x = 11; x <= 23; ++x) {
+        const int2 s = make_int2(x, CB_X * CB_Y / x);
+        const long long a = bricks(s), b = bricks(best);
+        if (a < b || (a == b && abs(s.x - s.y) < abs(best.x - best.y))) best = s;
+    }
+    return 20 * bricks(best) <= 19 * bricks(square) ? best : square;
+}
+
 dim3 brick_grid(const cbct_geom &g) {
-    return dim3((g.nx + 1 + CB_X - 1) / CB_X, (g.ny + 1 + CB_Y - 1) / CB_Y,
-                (g.nz + 1 + CB_Z - 1) / CB_Z);
+    const int2 s = brick_shape(g);
+    return dim3((g.nx + s.x) / s.x, (g.ny + s.y) / s.y, g.nz + 1);
 }
 
 // Views a workgroup of the cell pass takes.  A small grid has fewer bricks
@@ -759,7 +791,7 @@ hipError_t launch_bp_prepare(const cbct_plan &p, void *geom, hipStream_t s) {
     if (e != hipSuccess) return e;
     const dim3 b = brick_grid(p.g);
     hipLaunchKernelGGL(k_brick_views, dim3(b.x * b.y * b.z), dim3(64), 0, s, p.d_views, p.det,
-                       p.grid, p.g.hx, p.g.hy, p.g.hz, p.g.nu, p.g.nv, (int)b.x, (int)b.y,
+                       p.grid, p.g.hx, p.g.hy, p.g.hz, p.g.nu, p.g.nv, brick_shape(p.g), (int)b.x, (int)b.y,
                        p.g.n_views, view_chunk(p.g), (BrickView *)(base + l.bricks));
     return hipGetLastError();
 }
@@ -773,8 +805,8 @@ hipError_t launch_backproject_cells(const cbct_plan &p, const T *r, void *cells,
     const dim3 grid(b.x * b.y * b.z, view_chunks(p.g));
     const PixelRay *rays = (const PixelRay *)base;
     const BrickView *bv = (const BrickView *)(base + l.bricks);
-    hipLaunchKernelGGL(k_cells<T>, grid, dim3(256), 0, s, p.d_views, p.grid, p.g.nu, p.g.nv,
-                       p.g.n_views, view_chunk(p.g), rays, bv, r, (T *)cells, (T)p.g.step);
+    hipLaunchKernelGGL(k_cells<T>, grid, dim3(256), 0, s, p.d_views, p.grid, brick_shape(p.g),
+                       p.g.nu, p.g.nv, p.g.n_views, view_chunk(p.g), rays, bv, r, (T *)cells, (T)p.g.step);
     return hipGetLastError();
 }
 
