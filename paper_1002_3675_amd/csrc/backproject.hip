@@ -588,11 +588,15 @@ __global__ __launch_bounds__(256) void k_gather(GridConst gc, int chunks,
 //
 // Everything of a view but the row coordinate and l is the same along a
 // column.  Where all the wavefront's imager points have their four taps on
-// the detector, their tests go too.  Bound by VALU issue, the double
-// arithmetic above all: about 35 instructions a voxel and view with four
-// voxels a lane, 26 of them for the view.  Head (512 x 512 x 70, 40 views)
-// 1640 us with one voxel a lane and tested taps, 825 now.  Eight voxels a
-// lane take 140 registers and 924 us.
+// the detector, their tests go too, and the row coordinate's whole part and
+// fraction are read from the bits of a double: 2^-32 of a row, where the
+// weight formed of it is rounded to 2^-25.  Bound by VALU issue, the double
+// arithmetic above all, and by the gathers: about 32 instructions a voxel
+// and view with four voxels a lane, 26 / 4 of them for the view, and two
+// loads.  Head (512 x 512 x 70, 40 views) 1640 us with one voxel a lane and
+// tested taps, 825 with four and conversions of the row, 765 now.  Eight
+// voxels a lane take 140 registers and 924 us; four in the 80 registers of
+// six wavefronts spill, 1014 us.
 constexpr int Q_BX = 64, Q_BY = 4;
 
 // sqrt(x) for x > 0: the hardware's reciprocal root and a correction, within
@@ -623,8 +627,8 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
         sum[q] = 0.0;
         wz2[q] = (kz + q) * hz * ((kz + q) * hz);
     }
-    // 32-bit byte offsets within a view
-    const bool narrow = (long long)nu * nv < (1LL << 30);
+    // 32-bit byte offsets within a view, 24-bit factors, rows below 2^20
+    const bool narrow = (long long)nu * nv < (1LL << 30) && nu < (1 << 22) && nv < (1 << 20);
     for (int t = 0; t < nviews; ++t) {
         const ViewConst &vc = views[t];
         // source-to-voxel vector (mm): n along e_u, d along e_w (depth)
@@ -649,12 +653,18 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
                             fmax(fj0, fj1) < nv - 1.0;
         if (!__builtin_amdgcn_ballot_w64(!inside)) {
             const float *rt1 = rt + nu;
-            const unsigned i4 = 4u * (unsigned)(int)i0d, nu4 = 4u * (unsigned)nu;
+            // 2^20 + fj has fj's whole part in the low 20 bits of its upper
+            // word (0x41300000 above them) and 32 bits of its fraction in the
+            // lower: they need no conversions
+            const unsigned nu4 = 4u * (unsigned)nu;
+            const unsigned i4 = 4u * (unsigned)(int)i0d - 0x300000u * nu4;
+            const double fjm = fj0 + 1048576.0;
 #pragma unroll
             for (int q = 0; q < ZC; ++q) {
-                const double fj = __builtin_fma((double)q, dj, fj0);
-                const unsigned o = (unsigned)(int)fj * nu4 + i4;  // fj >= 0
-                const float b = (float)__builtin_amdgcn_fract(fj);
+                const unsigned long long x =
+                    __builtin_bit_cast(unsigned long long, __builtin_fma((double)q, dj, fjm));
+                const unsigned o = __umul24((unsigned)(x >> 32), nu4) + i4;
+                const float b = (float)(unsigned)x * 0x1p-32f;
                 const float *p = (const float *)((const char *)rt + o);
                 const float *p1 = (const float *)((const char *)rt1 + o);
                 const float v0 = p[0] + a * (p[1] - p[0]), v1 = p1[0] + a * (p1[1] - p1[0]);
@@ -830,7 +840,8 @@ hipError_t launch_eq2(const cbct_plan &p, const float *r, const float *f, double
                            out);
     };
     // Voxels a lane: more share a view's arithmetic, fewer leave more
-    // wavefronts.  Measured, us with 1 / 2 / 4: 4096 wavefronts of single
+    // wavefronts.  Measured (before the rows' conversions went, which took 4
+    // to 7%), us with 1 / 2 / 4: 4096 wavefronts of single
     // voxels (64^3) 15 / 16 / 23, 29k (157 x 141 x 67) 101 / 84 / 91, 33k
     // (128^3) 195 / 156 / 161, 66k (256 x 256 x 64) 407 / 309 / 289, 287k
     // (head) 1293 / 891 / 825.

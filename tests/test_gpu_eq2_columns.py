@@ -47,6 +47,22 @@ def test_eq2_matches_oracle(g, lo, hi, det):
     assert rel_l2(f, want) <= TOL, rel_l2(f, want)
 
 
+@pytest.mark.parametrize("nv", [(1 << 20) - 1, (1 << 20) + 5])
+def test_eq2_with_many_rows(nv):
+    """About 2^20 detector rows, the most that the row's bits are read for,
+    and a few more.  Rows are 5e-5 mm high: float rounding of the rows'
+    residuals is as before, the row coordinate's error of 2^-32 rows is none."""
+    require_gpu()
+    import paper_1002_3675_amd as cb
+    g = dataclasses.replace(TWO, nu=12, au=13.0, nv=nv, av=5.3e-5, n_views=1)
+    rng = np.random.default_rng(63)
+    y = rng.uniform(0.5, 4.0, g.proj_shape).astype(np.float32)
+    f = to_np(cb.Plan(g).backproject_eq2(to_dev(y)))
+    want = oracle.eq2_backproject(g, y.astype(np.float64))
+    assert np.count_nonzero(want) > want.size // 2
+    assert rel_l2(f, want) <= TOL, rel_l2(f, want)
+
+
 def test_a_value_that_is_not_finite_reaches_its_taps_only():
     require_gpu()
     import paper_1002_3675_amd as cb
