@@ -34,7 +34,8 @@ namespace cbct {
 namespace {
 
 constexpr int CB_X = 16, CB_Y = 16, CB_Z = 1;  // cells per workgroup: one z layer (see brick_shape)
-constexpr int TABLE = 560;                     // rays staged at a time (40 B each, 80 in double)
+constexpr int TABLE = 560;                     // rays staged at a time (at most 40 B each, 80 in double)
+constexpr int COLUMNS = 256;                   // and pixel columns (k_cells by columns; 16 B, 32)
 constexpr int PARTS = 6;                       // views staged at a time, at most
 constexpr int G_BX = 64, G_BY = 4;            // pass-2 block
 
@@ -66,6 +67,9 @@ __device__ __forceinline__ float min_t(float a, float b) { return fminf(a, b); }
 __device__ __forceinline__ double min_t(double a, double b) { return fmin(a, b); }
 __device__ __forceinline__ float max_t(float a, float b) { return fmaxf(a, b); }
 __device__ __forceinline__ double max_t(double a, double b) { return fmax(a, b); }
+// a limited to [0, hi]
+__device__ __forceinline__ float clamp_t(float a, float hi) { return __builtin_amdgcn_fmed3f(a, 0.0f, hi); }
+__device__ __forceinline__ double clamp_t(double a, double hi) { return fmin(fmax(a, 0.0), hi); }
 __device__ __forceinline__ float ceil_t(float a) { return __builtin_ceilf(a); }
 __device__ __forceinline__ double ceil_t(double a) { return __builtin_ceil(a); }
 
@@ -89,23 +93,34 @@ __global__ __launch_bounds__(256) void k_rays(const ViewConst *__restrict__ view
     rays[((long long)k * nv + j) * nu + i] = e;
 }
 
-// Directions of the rays through pixel columns i0 .. i1 of a view: 4 + (1 if
-// x increases along them) + (2 if y does), or 0 when they are not the same
-// along all of them or too near zero to tell.
+// How the rays through pixel columns i0 .. i1 of a view run in x and y, a sum
+// of these.  1: x increases along them, 2: y does.  4: for both axes they all
+// run the same way, and not too near zero to tell.  16: they have a main
+// axis, along which each advances, in cells, at least a third as fast as
+// along the other; it is y if 8 is there, else x.  Only rays more than 50
+// degrees apart in one brick, which the source is then very near to, have
+// none.
 __device__ __forceinline__ int ray_directions(const ViewConst &vc, const DetConst &dc, int i0,
                                               int i1) {
     const float ua = dc.u0 + (float)i0 * dc.au, ub = dc.u0 + (float)i1 * dc.au;
     const float tol = 1e-4f * (fabsf(vc.W[0]) + fabsf(vc.W[1]));
+    float da[2], db[2];
     int dir = 4;
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
-        const float da = vc.W[a] + ua * vc.U[a], db = vc.W[a] + ub * vc.U[a];
-        if (fminf(da, db) > tol)
-            dir |= 1 << a;
-        else if (!(fmaxf(da, db) < -tol))
-            return 0;
+        da[a] = vc.W[a] + ua * vc.U[a];
+        db[a] = vc.W[a] + ub * vc.U[a];
+        if (da[a] > 0.0f) dir |= 1 << a;
+        if (!(fminf(da[a], db[a]) > tol || fmaxf(da[a], db[a]) < -tol)) dir &= ~4;
     }
-    return dir;
+    auto leads = [&](int a) {  // at both ends, so between: the ratio is monotone in u
+        return da[a] * db[a] > 0.0f && 3.0f * fabsf(da[a]) >= fabsf(da[1 - a]) &&
+               3.0f * fabsf(db[a]) >= fabsf(db[1 - a]);
+    };
+    const bool x = leads(0), y = leads(1);
+    if (y && (!x || fminf(fabsf(da[1]), fabsf(db[1])) > fminf(fabsf(da[0]), fabsf(db[0]))))
+        dir |= 8;
+    return x || y ? dir | 16 : dir;
 }
 
 // A brick in one view (prepared once), 64 bytes.
@@ -122,10 +137,12 @@ __device__ __forceinline__ int ray_directions(const ViewConst &vc, const DetCons
 // pixel: a few hundredths of a pixel for a brick of 16 cells.
 //
 // Views are staged in batches of consecutive views whose footprints fit the
-// table together and whose rays have the same directions: batch_n views and
-// batch_rays rays when a batch begins with this view (batch_n = 0: the
-// footprint alone exceeds the table and is staged in parts), base this
-// view's first table entry in its batch.
+// table together and whose rays, for k_cells by rays, have the same
+// directions: batch_n views and batch_rays rays when a batch begins with this
+// view (batch_n = 0: the footprint alone exceeds the table and is staged in
+// parts), base this view's first table entry in its batch.  For k_cells by
+// columns both hold the pixel columns too, in the upper 16 bits, and a view
+// without a main axis stands alone with batch_n = 0.
 struct BrickView {
     int i0, j0, w, h;
     int W, H, dirs, base;
@@ -193,7 +210,7 @@ __global__ __launch_bounds__(64) void k_brick_views(const ViewConst *__restrict_
                                                     DetConst dc, GridConst gc, double hx,
                                                     double hy, double hz, int nu, int nv,
                                                     int2 shape, int nbx, int nby, int nviews,
-                                                    int chunk,
+                                                    int chunk, bool by_columns,
                                                     BrickView *__restrict__ out) {
     const int b = blockIdx.x, lane = threadIdx.x;
     const int c0[3] = {(b % nbx) * shape.x - 1, ((b / nbx) % nby) * shape.y - 1,
@@ -204,31 +221,36 @@ __global__ __launch_bounds__(64) void k_brick_views(const ViewConst *__restrict_
         BrickView o = brick_view(views[k], dc, gc, hx, hy, hz, nu, nv, c0, c1);
         // a footprint beyond the table stands alone (batch_n = 0)
         const long long pixels = (long long)o.w * o.h;
-        const int size = pixels > TABLE ? TABLE + 1 : (int)pixels;
-        int head = 0, n = 0, rays = 0, dirs = 0;
+        const bool alone = pixels > TABLE || (by_columns && pixels > 0 &&
+                                              (o.w > COLUMNS || !(o.dirs & 16)));
+        const int size = alone ? -1 : (int)pixels | (by_columns ? o.w << 16 : 0);
+        const int dir = o.dirs & 4 ? o.dirs & 7 : 0;
+        int head = 0, n = 0, rays = 0, cols = 0, dirs = 0;
         auto close = [&](int next) {
             if (lane == head && n > 0) {
                 o.batch_n = n;
-                o.batch_rays = rays;
-                o.dirs = dirs;
+                o.batch_rays = rays | cols << 16;
+                if (!by_columns) o.dirs = dirs;
             }
             head = next;
-            n = rays = dirs = 0;
+            n = rays = cols = dirs = 0;
         };
         const int count = min(64, nviews - k0);
         for (int q = 0; q < count; ++q) {
             const int sq = __builtin_amdgcn_readlane(size, q);
-            const int dq = __builtin_amdgcn_readlane(o.dirs, q);
-            if (sq > TABLE) {
+            const int dq = __builtin_amdgcn_readlane(dir, q);
+            if (sq < 0) {
                 close(q + 1);
                 continue;
             }
-            if (n == PARTS || rays + sq > TABLE || (rays > 0 && sq > 0 && dq != dirs) ||
-                (k0 + q) % chunk == 0)
+            const int rq = sq & 0xffff, cq = sq >> 16;
+            if (n == PARTS || rays + rq > TABLE || cols + cq > COLUMNS ||
+                (!by_columns && rays > 0 && rq > 0 && dq != dirs) || (k0 + q) % chunk == 0)
                 close(q);
             if (rays == 0) dirs = dq;
-            if (lane == q) o.base = rays;
-            rays += sq;
+            if (lane == q) o.base = rays | cols << 16;
+            rays += rq;
+            cols += cq;
             ++n;
         }
         close(count);
@@ -239,22 +261,27 @@ __global__ __launch_bounds__(64) void k_brick_views(const ViewConst *__restrict_
 // ---------------------------------------------------------------------------
 // Pass 1.
 //
-// Staged ray of the current footprints, relative to its brick: n counts the
-// ray's samples from the first one in the brick, N of them lie in it, and
-// q_a(n) = f_a + n D_a is sample n's coordinate in cells from the brick's
-// first cell.  inv = 1/D, off = -f inv: fma(c, inv, off) is the (real) n at
-// which the ray crosses face c.  For z, of which a brick has one layer, the
-// centred weight is fma(n, D_z, fz) itself.
+// A ray relative to a brick: n counts the ray's samples from the first one
+// in the brick, N of them lie in it, and q_a(n) = f_a + n D_a is sample n's
+// coordinate in cells from the brick's first cell.  inv = 1/D, so
+// fma(c, inv, -f inv) is the (real) n at which the ray crosses face c.  For
+// z, of which a brick has one layer, the centred weight is
+// fma(n, D_z, f_z - 1/2) itself.
 template <typename T> using vec4 = T __attribute__((ext_vector_type(4)));
 template <typename T> using vec2 = T __attribute__((ext_vector_type(2)));
 
+template <typename T> struct BrickRay {
+    T inv[3], D[3], f[3], N;
+};
+
+// As it is staged for k_cells by rays.
 template <typename T> struct StagedRay {
-    vec4<T> a;  // inv_x, off_x, inv_y, off_y
+    vec4<T> a;  // inv_x, -f_x inv_x, inv_y, -f_y inv_y
     vec4<T> b;  // D_x, D_y, D_z, f_z - 1/2
     vec2<T> c;  // N, residual
 };
 
-// The ray with increment D and its residual rv as the brick's cells use it.
+// The ray with increment D as the brick's cells use it.
 //
 // Which samples lie in the brick is decided by the ray's face crossings
 // T(c) = (c - q) / D_f counted from sample n_mid (q the float coordinate of
@@ -266,32 +293,37 @@ template <typename T> struct StagedRay {
 // its position in that cell, then differ from the exact ones by a second
 // order of that distance.
 template <typename T>
-__device__ __forceinline__ StagedRay<T> stage_ray(const double D[3], const double Qd[3], int nmid,
-                                                  const int c0[3], const int c1[3], T rv) {
-    StagedRay<T> e;
+__device__ __forceinline__ BrickRay<T> brick_ray(const double D[3], const double Qd[3], int nmid,
+                                                 const int c0[3], const int c1[3]) {
+    BrickRay<T> e;
     double qm[3];
-    T Dt[3], inv[3];
     T lo = T(-8388608), hi = T(8388608);  // 2^23: beyond every sample
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         qm[a] = __builtin_fma((double)nmid, D[a], Qd[a]);
         const T q = (T)qm[a];
-        Dt[a] = (T)D[a];
-        inv[a] = rcp(Dt[a]);
-        const T t0 = ((T)c0[a] - q) * inv[a], t1 = ((T)c1[a] - q) * inv[a];
+        e.D[a] = (T)D[a];
+        e.inv[a] = rcp(e.D[a]);
+        const T t0 = ((T)c0[a] - q) * e.inv[a], t1 = ((T)c1[a] - q) * e.inv[a];
         lo = max_t(lo, min_t(t0, t1));
         hi = min_t(hi, max_t(t0, t1));
     }
     lo = min_t(ceil_t(lo), T(8388608));
     hi = ceil_t(hi);
-    T f[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
-        f[a] = (T)(__builtin_fma((double)lo, D[a], qm[a]) - (double)c0[a]);
-    e.a = vec4<T>{inv[0], -f[0] * inv[0], inv[1], -f[1] * inv[1]};
-    e.b = vec4<T>{Dt[0], Dt[1], Dt[2], f[2] - T(0.5)};
-    e.c = vec2<T>{max_t(hi - lo, T(0)), rv};
+        e.f[a] = (T)(__builtin_fma((double)lo, D[a], qm[a]) - (double)c0[a]);
+    e.N = max_t(hi - lo, T(0));
     return e;
+}
+
+template <typename T>
+__device__ __forceinline__ StagedRay<T> stage_ray(const BrickRay<T> &e, T rv) {
+    StagedRay<T> o;
+    o.a = vec4<T>{e.inv[0], -e.f[0] * e.inv[0], e.inv[1], -e.f[1] * e.inv[1]};
+    o.b = vec4<T>{e.D[0], e.D[1], e.D[2], e.f[2] - T(0.5)};
+    o.c = vec2<T>{e.N, rv};
+    return o;
 }
 
 // A lane's cell in its brick: face coordinates for the crossings (the
@@ -359,6 +391,55 @@ __device__ __forceinline__ void crossing_sums(T m[8], const vec4<T> ra, const ve
     m[7] = fma_t(pxy, z, fma_t(bxz, y, fma_t(byz, x, m[7])));
 }
 
+// The same by pixel columns.  The rays of a column of pixels lie in one plane
+// with the z axis' direction: seen along z they are one line, y = g x + h (x
+// the main axis here; where it is y, x and y change places).  Where that line
+// enters and leaves a cell in x, and y, are found once for the column, and
+// its rays need the moments in x and z alone, sum r (1, x, x^2, z, x z,
+// x^2 z): 31 VALU instructions a ray instead of 42, and 26 a column.
+//     column: g, h, 1/g, -h/g
+//     ray a:  1/D_x, -f_x/D_x, D_x, f_x     ray b: D_z, f_z - 1/2, N, residual
+template <typename T> struct ColumnSums {
+    T s0, s1, s2, z0, z1, z2;
+    T w;  // half of what D_x D_z adds to x^2 z
+};
+
+template <typename T>
+__device__ __forceinline__ void column_ray(ColumnSums<T> &c, const vec4<T> ra, const vec4<T> rb,
+                                           T in, T out, T centre) {
+    const T n0 = ceil_t(max_t(fma_t(in, ra.x, ra.y), T(0)));
+    const T n1 = ceil_t(clamp_t(fma_t(out, ra.x, ra.y), rb.z));
+    const T k = max_t(n1 - n0, T(0));
+    const T n = fma_t(T(0.5), n0 + n1, T(-0.5));
+    const T x = fma_t(n, ra.z, ra.w) - centre;
+    const T z = fma_t(n, rb.x, rb.y);
+    const T A = mul_zero(rb.w, k);
+    const T B = A * fma_t(k * k, T(1) / T(12), T(-1) / T(12));
+    const T Bx = B * ra.z, Bxz = Bx * rb.x, Ax = A * x;
+    const T q = fma_t(Ax, x, Bx * ra.z);
+    c.s0 += A;
+    c.s1 += Ax;
+    c.s2 += q;
+    c.z0 = fma_t(A, z, c.z0);
+    c.z1 = fma_t(Ax, z, c.z1) + Bxz;
+    c.z2 = fma_t(q, z, c.z2);
+    c.w = fma_t(x, Bxz, c.w);
+}
+
+// The column's part of the moments; y = y0 + g x from the cell's centre.
+template <bool Y_MAIN, typename T>
+__device__ __forceinline__ void add_column(T m[8], const ColumnSums<T> &c, T y0, T g) {
+    constexpr int X = Y_MAIN ? 2 : 1, Y = 3 - X, XZ = Y_MAIN ? 6 : 5, YZ = 11 - XZ;
+    m[0] += c.s0;
+    m[X] += c.s1;
+    m[Y] = fma_t(y0, c.s0, fma_t(g, c.s1, m[Y]));
+    m[4] = fma_t(y0, c.s1, fma_t(g, c.s2, m[4]));
+    m[3] += c.z0;
+    m[XZ] += c.z1;
+    m[YZ] = fma_t(y0, c.z0, fma_t(g, c.z1, m[YZ]));
+    m[7] = fma_t(y0, c.z1, fma_t(g, fma_t(T(2), c.w, c.z2), m[7]));
+}
+
 // Corner sums (index ox + 2 oy + 4 oz): corner weights are the products of
 // 1/2 -+ x, 1/2 -+ y and 1/2 -+ z.
 template <typename T>
@@ -375,7 +456,7 @@ __device__ __forceinline__ void moments_to_corners(const T m[8], T c[8]) {
 // (see view_chunk).
 //
 // Bound by VALU issue: a visit of a (ray, cell) pair is 42 VALU and 3 LDS
-// instructions (40 bytes a lane), of which fused multiply-adds take about
+// instructions (40 bytes a lane; by columns 31 and 2, 32 bytes), of which fused multiply-adds take about
 // 2.8 cycles of a SIMD and min, max, ceil, compare, select and integer
 // instructions about 4.2 (measured with chains of each).  So what is not
 // arithmetic of the moments is kept out of the visits: no counters in the
@@ -386,7 +467,9 @@ __device__ __forceinline__ void moments_to_corners(const T m[8], T c[8]) {
 // the lanes' different counts): head transpose (512 x 512 x 70, 40 views)
 // 17.63 -> 8.34 ms, 256 x 256 x 64 / 60 views 3.87 -> 1.52, 128^3 / 60 views
 // 2.00 -> 0.87, 64^3 / 16 views 0.150 -> 0.081; 2.5 cycles an instruction.
-// Table of 560 rays: seven groups fill the LDS (22.4 KB) as the 68 VGPRs
+// By columns, where a cell spans three pixel rows or more, the head's goes
+// on to 7.7 ms (see by_columns).
+// Table of 560 rays: seven groups fill the LDS (22.4 KB) as the 65 to 71 VGPRs
 // allow; 480 rays 1.5% slower, 650 (six groups) 2%.  Up to six views a
 // batch: 1 to 2% over four.
 //
@@ -394,14 +477,16 @@ __device__ __forceinline__ void moments_to_corners(const T m[8], T c[8]) {
 // from the ray table; with the staged rays and the closed form a transpose
 // of 32^3 from 60 views takes 76 us instead of 213
 // (163 with one chunk of views).
-template <typename T>
-__global__ __launch_bounds__(256) void k_cells(
+template <typename T, bool COL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COL && sizeof(T) == 4 ? 7 : 2, 8))) void k_cells(
     const ViewConst *__restrict__ views, GridConst gc, int2 shape, int nu, int nv, int nviews,
     int chunk, const PixelRay *__restrict__ rays, const BrickView *__restrict__ bviews,
     const T *__restrict__ r, T *__restrict__ cells, T step) {
     __shared__ vec4<T> tab[2 * TABLE];
-    __shared__ vec2<T> tabc[TABLE];
-    __shared__ int4 slots[PARTS];  // first entry, width, first pixel of the batch's views
+    __shared__ vec2<T> tabc[COL ? 1 : TABLE];
+    __shared__ vec4<T> tabl[COL ? COLUMNS : 1];
+    __shared__ int4 slots[PARTS];   // first entry, width, first pixel of the batch's views
+    __shared__ int2 cslots[PARTS];  // and first column, whether y is the main axis
     static_assert(CB_Z == 1, "a brick is one z layer of cells");
     const int tid = threadIdx.x;
     // bricks x-fastest, then y, then z; each XCD takes one contiguous range,
@@ -427,19 +512,70 @@ __global__ __launch_bounds__(256) void k_cells(
 #pragma unroll
     for (int o = 0; o < 8; ++o) m[o] = T(0);
 
+    // The lane's cell (px, py) in the brick and its faces.  They pass through
+    // an empty asm statement, here and where rays are staged: their
+    // conversions, formed where they are used, then take no registers across
+    // the loops.
+    auto cell_faces = [&](int dirs, int &px, int &py) {
+        px = lx;
+        py = ly;
+        asm volatile("" : "+v"(px), "+v"(py));
+        const float fx = (float)px, fy = (float)py;
+        // the brick's own faces moved outward
+        const float fx0 = px == 0 ? -0.25f : fx, fy0 = py == 0 ? -0.25f : fy;
+        const float fx1 = fx + (c0[0] + px + 1 == c1[0] ? 1.25f : 1.0f);
+        const float fy1 = fy + (c0[1] + py + 1 == c1[1] ? 1.25f : 1.0f);
+        CellFaces<T> cf;
+        cf.x0 = dirs == 0 || (dirs & 1) ? fx0 : fx1;
+        cf.x1 = dirs == 0 || (dirs & 1) ? fx1 : fx0;
+        cf.y0 = dirs == 0 || (dirs & 2) ? fy0 : fy1;
+        cf.y1 = dirs == 0 || (dirs & 2) ? fy1 : fy0;
+        cf.cx = cf.x0 - fx - T(0.5);
+        cf.cy = cf.y0 - fy - T(0.5);
+        return cf;
+    };
+    // A view without a main axis, by columns: every ray set up by each lane.
+    auto direct = [&](const BrickView b, int k) {
+        int px, py;
+        const CellFaces<T> cf = cell_faces(0, px, py);
+        const int W = min(b.W, b.w), H = min(b.H, b.h);
+        const int ci = (int)__builtin_ceilf(b.a0 + b.ax * (float)px + b.ay * (float)py);
+        const int cj = (int)__builtin_ceilf(b.b0 + b.bx * (float)px + b.by * (float)py);
+        const ViewConst &vc = views[k];
+        const double Qd[3] = {vc.Qd[0], vc.Qd[1], vc.Qd[2]};
+        long long pix = ((long long)k * nv + b.j0 + max(min(cj, b.h - H), 0)) * nu + b.i0 +
+                        max(min(ci, b.w - W), 0);
+        for (int y = 0; y < H; ++y, pix += nu)
+            for (int x = 0; x < W; ++x) {
+                const StagedRay<T> e =
+                    stage_ray(brick_ray<T>(rays[pix + x].D, Qd, vc.nmid, c0, c1), r[pix + x]);
+                crossing_sums<false>(m, e.a, e.b, e.c, cf);
+            }
+    };
     const int kend = min(nviews, (int)(blockIdx.y + 1) * chunk);
     for (int k = blockIdx.y * chunk; k < kend;) {
         // the batch, or the parts of a view too large for the table: bands of
         // rows, or pieces of a row
-        int n = bv[k].batch_n, total = bv[k].batch_rays;
-        const int dirs = bv[k].dirs;
+        int n = bv[k].batch_n, total = bv[k].batch_rays, columns = 0;
+        if constexpr (COL) {
+            columns = total >> 16;
+            total &= 0xffff;
+        }
+        const int dirs = bv[k].dirs & 4 ? bv[k].dirs : 0;
         int cols = 1, pw = 0, ph = 0, parts = 1;
         if (n == 0) {
+            constexpr int WIDEST = COL ? COLUMNS : TABLE;
             n = 1;
-            cols = (bv[k].w + TABLE - 1) / TABLE;
+            cols = (bv[k].w + WIDEST - 1) / WIDEST;
             pw = (bv[k].w + cols - 1) / cols;
             ph = min(TABLE / pw, bv[k].h);
             parts = cols * ((bv[k].h + ph - 1) / ph);
+        }
+        if constexpr (COL) {
+            if (bv[k].w > 0 && !(bv[k].dirs & 16)) {
+                direct(bv[k], k);
+                parts = 0;
+            }
         }
         for (int part = 0; part < parts; ++part) {
             int oi = 0, oj = 0, w = bv[k].w, h = bv[k].h;  // the part within the view
@@ -449,20 +585,22 @@ __global__ __launch_bounds__(256) void k_cells(
                 w = max(min(pw, w - oi), 0);
                 h = min(ph, h - oj);
                 total = w * h;
+                columns = w;
             }
             if (tid < PARTS) {
                 int4 s = make_int4(0x7fffffff, 1, 0, 0);
+                int2 c = make_int2(0x7fffffff, 0);
                 if (tid < n) {
                     const BrickView &b = bv[k + tid];
-                    s = make_int4(b.base, parts > 1 ? w : b.w, b.i0 + oi, b.j0 + oj);
+                    s = make_int4(COL ? b.base & 0xffff : b.base, parts > 1 ? w : b.w, b.i0 + oi,
+                                  b.j0 + oj);
+                    c = make_int2(b.base >> 16, b.dirs & 8);
                 }
                 slots[tid] = s;
+                if constexpr (COL) cslots[tid] = c;
             }
             __syncthreads();  // readers of the table are done, the slots are there
             for (int t = tid; t < total; t += 256) {
-                // The brick's faces pass through an empty asm statement here
-                // and the lane's cell below: their conversions, formed where
-                // they are used, then take no registers across the loops.
                 int f0[3] = {c0[0], c0[1], c0[2]}, f1[3] = {c1[0], c1[1], c1[2]};
                 asm volatile("" : "+s"(f0[0]), "+s"(f0[1]), "+s"(f0[2]), "+s"(f1[0]),
                                   "+s"(f1[1]), "+s"(f1[2]));
@@ -481,26 +619,39 @@ __global__ __launch_bounds__(256) void k_cells(
                 const PixelRay g = rays[pix];
                 const ViewConst &vc = views[k + v];
                 const double Qd[3] = {vc.Qd[0], vc.Qd[1], vc.Qd[2]};
-                const StagedRay<T> ray = stage_ray(g.D, Qd, vc.nmid, f0, f1, r[pix]);
-                tab[t] = ray.a;
-                tab[t + TABLE] = ray.b;
-                tabc[t] = ray.c;
+                const BrickRay<T> ray = brick_ray<T>(g.D, Qd, vc.nmid, f0, f1);
+                if constexpr (COL) {
+                    const bool ym = cslots[v].y != 0;
+                    const T inv = ym ? ray.inv[1] : ray.inv[0], f = ym ? ray.f[1] : ray.f[0];
+                    tab[t] = vec4<T>{inv, -f * inv, ym ? ray.D[1] : ray.D[0], f};
+                    tab[t + TABLE] = vec4<T>{ray.D[2], ray.f[2] - T(0.5), ray.N, r[pix]};
+                } else {
+                    const StagedRay<T> e = stage_ray(ray, r[pix]);
+                    tab[t] = e.a;
+                    tab[t + TABLE] = e.b;
+                    tabc[t] = e.c;
+                }
+            }
+            for (int t = tid; COL && t < columns; t += 256) {
+                int v = 0;
+#pragma unroll
+                for (int q = 1; q < PARTS; ++q) v += t >= cslots[q].x;
+                const int4 sl = slots[v];
+                const int2 cs = cslots[v];
+                const PixelRay g =
+                    rays[((long long)(k + v) * nv + sl.w) * nu + (sl.z + t - cs.x)];
+                const ViewConst &vc = views[k + v];
+                const bool ym = cs.y != 0;
+                const double qx = vc.Qd[0] - c0[0], qy = vc.Qd[1] - c0[1];
+                const double gd = ym ? g.D[0] / g.D[1] : g.D[1] / g.D[0];
+                const double hd = ym ? qx - gd * qy : qy - gd * qx;
+                const double id = 1.0 / gd;
+                tabl[t] = vec4<T>{(T)gd, (T)hd, (T)id, (T)(-hd * id)};
             }
             __syncthreads();
-            int px = lx, py = ly;
-            asm volatile("" : "+v"(px), "+v"(py));
+            int px, py;
+            const CellFaces<T> cf = cell_faces(COL ? 0 : dirs, px, py);
             const float fx = (float)px, fy = (float)py;
-            // the brick's own faces moved outward
-            const float fx0 = px == 0 ? -0.25f : fx, fy0 = py == 0 ? -0.25f : fy;
-            const float fx1 = fx + (c0[0] + px + 1 == c1[0] ? 1.25f : 1.0f);
-            const float fy1 = fy + (c0[1] + py + 1 == c1[1] ? 1.25f : 1.0f);
-            CellFaces<T> cf;
-            cf.x0 = dirs == 0 || (dirs & 1) ? fx0 : fx1;
-            cf.x1 = dirs == 0 || (dirs & 1) ? fx1 : fx0;
-            cf.y0 = dirs == 0 || (dirs & 2) ? fy0 : fy1;
-            cf.y1 = dirs == 0 || (dirs & 2) ? fy1 : fy0;
-            cf.cx = cf.x0 - fx - T(0.5);
-            cf.cy = cf.y0 - fy - T(0.5);
             auto visit = [&](auto ordered) {
                 constexpr bool ORD = decltype(ordered)::value;
                 for (int v = 0; v < n; ++v) {
@@ -531,10 +682,52 @@ __global__ __launch_bounds__(256) void k_cells(
                     }
                 }
             };
-            if (dirs)
+            auto visit_columns = [&](const BrickView &b, int bw, int bh, auto y_main) {
+                constexpr bool YM = decltype(y_main)::value;
+                const int W = min(b.W, bw), H = min(b.H, bh);
+                const int ci = (int)__builtin_ceilf(b.a0 + b.ax * fx + b.ay * fy) - oi;
+                const int cj = (int)__builtin_ceilf(b.b0 + b.bx * fx + b.by * fy) - oj;
+                if (parts > 1 && !__builtin_amdgcn_ballot_w64(ci + b.W > 0 && ci < bw &&
+                                                              cj + b.H > 0 && cj < bh))
+                    return;
+                const int ec = max(min(ci, bw - W), 0), er = max(min(cj, bh - H), 0);
+                const vec4<T> *p = tab + (b.base & 0xffff) + er * bw + ec;
+                const vec4<T> *pl = tabl + (b.base >> 16) + ec;
+                const bool up = b.dirs & (YM ? 2 : 1);
+                const T x0 = YM ? cf.y0 : cf.x0, x1 = YM ? cf.y1 : cf.x1;
+                const T y0 = YM ? cf.x0 : cf.y0, y1 = YM ? cf.x1 : cf.y1;
+                const T cx = (YM ? fy : fx) + T(0.5), cy = (YM ? fx : fy) + T(0.5);
+                for (int x = 0; x < W; ++x) {
+                    const vec4<T> l = pl[x];
+                    const T t0 = fma_t(y0, l.z, l.w), t1 = fma_t(y1, l.z, l.w);
+                    const T lo = max_t(x0, min_t(t0, t1)), hi = min_t(x1, max_t(t0, t1));
+                    const T in = up ? lo : hi, out = up ? hi : lo;
+                    ColumnSums<T> c = {};
+                    const vec4<T> *q = p + x;
+                    int y = 0;
+                    for (; y + 1 < H; y += 2, q += 2 * bw) {
+                        column_ray(c, q[0], q[TABLE], in, out, cx);
+                        column_ray(c, q[bw], q[bw + TABLE], in, out, cx);
+                    }
+                    if (y < H) column_ray(c, q[0], q[TABLE], in, out, cx);
+                    add_column<YM>(m, c, fma_t(cx, l.x, l.y) - cy, l.x);
+                }
+            };
+            if constexpr (COL) {
+                for (int v = 0; v < n; ++v) {
+                    const BrickView b = bv[k + v];
+                    const int bw = parts > 1 ? w : b.w, bh = parts > 1 ? h : b.h;
+                    if (bw == 0) continue;
+                    if (b.dirs & 8)
+                        visit_columns(b, bw, bh, std::true_type());
+                    else
+                        visit_columns(b, bw, bh, std::false_type());
+                }
+            } else if (dirs) {
                 visit(std::true_type());
-            else
+            } else {
                 visit(std::false_type());
+            }
         }
         k += n;
     }
@@ -730,6 +923,15 @@ dim3 brick_grid(const cbct_geom &g) {
     return dim3((g.nx + s.x) / s.x, (g.ny + s.y) / s.y, g.nz + 1);
 }
 
+// Whether the cell pass goes by pixel columns: where a cell spans three rows of
+// them or more at the grid's centre, so that a column's own arithmetic is
+// small against its rays'.  256 x 256 x 48, 40 views, by rays / by columns
+// (us): 2 rows 677 / 728, 2.5 774 / 796, 3 906 / 896, 3.5 1017 / 976, 4
+// 1114 / 1052, 5 1278 / 1167; 512 x 512 x 70 (4.8 rows) 8790 / 7740.
+constexpr double COLUMN_ROWS = 3.0;
+
+bool by_columns(const cbct_geom &g) { return g.hz * g.sdd >= COLUMN_ROWS * g.sad * g.av; }
+
 // Views a workgroup of the cell pass takes.  A small grid has fewer bricks
 // than the chip has room for (about 1800 workgroups), and each works its way
 // through the views' loads and barriers alone; its views are then cut into
@@ -802,7 +1004,8 @@ hipError_t launch_bp_prepare(const cbct_plan &p, void *geom, hipStream_t s) {
     const dim3 b = brick_grid(p.g);
     hipLaunchKernelGGL(k_brick_views, dim3(b.x * b.y * b.z), dim3(64), 0, s, p.d_views, p.det,
                        p.grid, p.g.hx, p.g.hy, p.g.hz, p.g.nu, p.g.nv, brick_shape(p.g), (int)b.x, (int)b.y,
-                       p.g.n_views, view_chunk(p.g), (BrickView *)(base + l.bricks));
+                       p.g.n_views, view_chunk(p.g), by_columns(p.g),
+                       (BrickView *)(base + l.bricks));
     return hipGetLastError();
 }
 
@@ -815,8 +1018,9 @@ hipError_t launch_backproject_cells(const cbct_plan &p, const T *r, void *cells,
     const dim3 grid(b.x * b.y * b.z, view_chunks(p.g));
     const PixelRay *rays = (const PixelRay *)base;
     const BrickView *bv = (const BrickView *)(base + l.bricks);
-    hipLaunchKernelGGL(k_cells<T>, grid, dim3(256), 0, s, p.d_views, p.grid, brick_shape(p.g),
-                       p.g.nu, p.g.nv, p.g.n_views, view_chunk(p.g), rays, bv, r, (T *)cells, (T)p.g.step);
+    hipLaunchKernelGGL((by_columns(p.g) ? k_cells<T, true> : k_cells<T, false>), grid, dim3(256), 0,
+                       s, p.d_views, p.grid, brick_shape(p.g), p.g.nu, p.g.nv, p.g.n_views,
+                       view_chunk(p.g), rays, bv, r, (T *)cells, (T)p.g.step);
     return hipGetLastError();
 }
 

@@ -57,6 +57,39 @@ CASES = {
 }
 
 
+# Where a cell spans three detector rows or more, the cells go by columns of
+# pixels: the same cases with rows of 0.4 of the height.
+SPAN = 3.0
+for _n in sorted(set(CASES) - {"flat_voxels", "tall_footprint"}):
+    _g = CASES[_n]
+    CASES["rows_" + _n] = dataclasses.replace(_g, av=0.4 * _g.av, nv=int(2.5 * _g.nv) + 1)
+# the source 2 mm outside the grid's corner: rays over 90 degrees apart in a brick
+CASES["rows_at_the_source"] = dataclasses.replace(CASES["rows_wide_angle"], sad=60.0, n_views=9,
+                                                  angles=tuple(math.pi / 4 + 0.7 * k for k in range(9)))
+
+
+def _rows(g):
+    return g.hz * g.sdd / (g.sad * g.av)
+
+
+def test_cases_take_both_ways():
+    assert all((_rows(g) >= SPAN) == (n.startswith("rows_") or n == "tall_footprint")
+               for n, g in CASES.items())
+    # a brick that the source is so near to that no axis leads: its rays
+    # through two of the corners run along +-x and +-y, or more apart
+    g = CASES["rows_at_the_source"]
+    th = g.angles[0]
+    src = g.sad * np.array([math.sin(th), -math.cos(th)])
+    half = 0.5 * (g.nx + 1) * g.hx
+    far = []
+    for x in (half - 16 * g.hx, half):
+        for y in (-half, 16 * g.hy - half):
+            far.append(np.array([x, y]) - src)
+    ang = [math.atan2(d[1], d[0]) for d in far]
+    spread = max(abs((a - b + math.pi) % (2 * math.pi) - math.pi) for a in ang for b in ang)
+    assert spread > math.radians(60), spread
+
+
 @pytest.mark.parametrize("name", sorted(CASES))
 def test_transpose_matches_oracle(name):
     require_gpu()
@@ -100,12 +133,13 @@ def test_table_geometries_exceed_the_table():
 
 
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
-def test_a_value_that_is_not_finite_stays_on_its_ray(bad):
+@pytest.mark.parametrize("name", ["cells_31x33", "rows_cells_31x33"])
+def test_a_value_that_is_not_finite_stays_on_its_ray(name, bad):
     """Voxels whose weight for that ray is zero in the oracle keep the value
     they have without it."""
     require_gpu()
     import paper_1002_3675_amd as cb
-    g = CASES["cells_31x33"]
+    g = CASES[name]
     rng = np.random.default_rng(42)
     y = rng.uniform(0.5, 4.0, g.proj_shape).astype(np.float32)
     at = (2, 6, 33)
