@@ -234,14 +234,17 @@ __device__ __forceinline__ float staged_samples(int base, int RXr, int RXY, floa
 // tile so that they fall on different banks (best_residue).  Rows of 16 x 2
 // rays with planes packed close lost 1.4 cycles a read at the head size and
 // 3.3-3.5 at 256 x 256 x 64 and 128^3 / 60 views; now 0.6, 1.4 and 2.0:
-// P 5.60 -> 5.05 ms, 1.19 -> 1.04, 0.68 -> 0.57; 64^3 / 16 views 56 -> 44 us.
+// P 5.60 -> 5.02 ms, 1.19 -> 1.04, 0.68 -> 0.57; 64^3 / 16 views 56 -> 47 us.
 // Where a tile spans many cells (pixels near the voxel size) single pieces
 // still fit; where it spans few, runs spread the per-chunk staging and
 // segment-origin work over more samples.
 constexpr int TILE_U = 16, TILE_V = 16;
 constexpr int TILE_SUB = 16;    // samples per box
 constexpr int TILE_MERGE = 8;   // boxes per chunk at most
-constexpr int TILE_LDS = 5760;  // floats (larger boxes stage more slowly than they save)
+// Floats of a fitting box.  It decides where a ray's float sums end and go to
+// the double one, so another value moves results by a float's rounding; 5760
+// takes 44 us at 64^3 / 16 views and 1% more at the head size.
+constexpr int TILE_LDS = 5632;
 constexpr int TILE_VOL = 6016;  // floats of LDS: a fitting box, and room to space its planes
 constexpr int BOX_TAB = 128;    // boxes computed together
 static_assert(SEG % (TILE_SUB * TILE_MERGE) == 0, "a block of pieces lies inside one segment");
