@@ -453,7 +453,7 @@ __device__ __forceinline__ void moments_to_corners(const T m[8], T c[8]) {
 }
 
 // Workgroups of 256 lanes, one per brick (see brick_shape) and chunk of views
-// (see view_chunk).
+// (see cut_of).
 //
 // Bound by VALU issue: a visit of a (ray, cell) pair is 42 VALU and 3 LDS
 // instructions (40 bytes a lane; by columns 31 and 2, 32 bytes), of which fused multiply-adds take about
@@ -919,11 +919,6 @@ int2 brick_shape(const cbct_geom &g) {
     return 20 * bricks(best) <= 19 * bricks(square) ? best : square;
 }
 
-dim3 brick_grid(const cbct_geom &g) {
-    const int2 s = brick_shape(g);
-    return dim3((g.nx + s.x) / s.x, (g.ny + s.y) / s.y, g.nz + 1);
-}
-
 // Whether the cell pass goes by pixel columns: where a cell spans three rows of
 // them or more at the grid's centre, so that a column's own arithmetic is
 // small against its rays'.  256 x 256 x 48, 40 views, by rays / by columns
@@ -943,17 +938,23 @@ bool by_columns(const cbct_geom &g) { return g.hz * g.sdd >= COLUMN_ROWS * g.sad
 // 197 / 197 / 164; 80^3 and 96^3 / 16 lose 3 to 9% with two chunks.
 constexpr int SPLIT_GROUPS = 6144, SPLIT_MAX = 8, SPLIT_VIEWS = 4;
 
-int view_chunk(const cbct_geom &g) {
-    const dim3 b = brick_grid(g);
-    const long long bricks = (long long)b.x * b.y * b.z;
+// How the cell pass cuts a grid and its views.
+struct Cut {
+    int2 shape;       // cells of a brick
+    dim3 bricks;
+    int chunk, chunks;  // views of a workgroup; chunks of views
+};
+
+Cut cut_of(const cbct_geom &g) {
+    Cut c;
+    c.shape = brick_shape(g);
+    c.bricks = dim3((g.nx + c.shape.x) / c.shape.x, (g.ny + c.shape.y) / c.shape.y, g.nz + 1);
+    const long long bricks = (long long)c.bricks.x * c.bricks.y * c.bricks.z;
     const int want = (int)std::min((long long)SPLIT_MAX, SPLIT_GROUPS / bricks);
     const int n = std::max(1, std::min(want, g.n_views / SPLIT_VIEWS));
-    return (g.n_views + n - 1) / n;
-}
-
-int view_chunks(const cbct_geom &g) {
-    const int c = view_chunk(g);
-    return (g.n_views + c - 1) / c;
+    c.chunk = (g.n_views + n - 1) / n;
+    c.chunks = (g.n_views + c.chunk - 1) / c.chunk;
+    return c;
 }
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -964,21 +965,21 @@ struct GeomLayout {
     size_t bricks, total;  // byte offsets
 };
 
-GeomLayout geom_layout(const cbct_geom &g) {
-    const dim3 b = brick_grid(g);
+GeomLayout geom_layout(const cbct_geom &g, const Cut &c) {
     GeomLayout l;
     l.bricks = align256(sizeof(PixelRay) * (size_t)g.n_views * g.nu * g.nv);
-    l.total = l.bricks + sizeof(BrickView) * (size_t)b.x * b.y * b.z * g.n_views;
+    l.total = l.bricks + sizeof(BrickView) * (size_t)c.bricks.x * c.bricks.y * c.bricks.z * g.n_views;
     return l;
 }
 
 }  // namespace
 
 size_t bp_cells_bytes(const cbct_geom &g, size_t elem) {
-    return align256(elem * 8 * view_chunks(g) * (size_t)cell_pitch(g.nx) * (g.ny + 1) * (g.nz + 1));
+    return align256(elem * 8 * cut_of(g).chunks * (size_t)cell_pitch(g.nx) * (g.ny + 1) *
+                    (g.nz + 1));
 }
 
-size_t bp_geom_bytes(const cbct_geom &g) { return geom_layout(g).total; }
+size_t bp_geom_bytes(const cbct_geom &g) { return geom_layout(g, cut_of(g)).total; }
 
 size_t bp_workspace_bytes(const cbct_geom &g, size_t elem) {
     return bp_cells_bytes(g, elem) + bp_geom_bytes(g);
@@ -996,32 +997,31 @@ void cell_pass_config(int32_t out[4]) {
 }
 
 hipError_t launch_bp_prepare(const cbct_plan &p, void *geom, hipStream_t s) {
-    const GeomLayout l = geom_layout(p.g);
+    const Cut c = cut_of(p.g);
+    const GeomLayout l = geom_layout(p.g, c);
     char *base = (char *)geom;
     hipLaunchKernelGGL(k_rays, dim3((p.g.nu + 63) / 64, (p.g.nv + 3) / 4, p.g.n_views), dim3(256),
                        0, s, p.d_views, p.det, p.g.nu, p.g.nv, (PixelRay *)base);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const dim3 b = brick_grid(p.g);
+    const dim3 b = c.bricks;
     hipLaunchKernelGGL(k_brick_views, dim3(b.x * b.y * b.z), dim3(64), 0, s, p.d_views, p.det,
-                       p.grid, p.g.hx, p.g.hy, p.g.hz, p.g.nu, p.g.nv, brick_shape(p.g), (int)b.x, (int)b.y,
-                       p.g.n_views, view_chunk(p.g), by_columns(p.g),
-                       (BrickView *)(base + l.bricks));
+                       p.grid, p.g.hx, p.g.hy, p.g.hz, p.g.nu, p.g.nv, c.shape, (int)b.x, (int)b.y,
+                       p.g.n_views, c.chunk, by_columns(p.g), (BrickView *)(base + l.bricks));
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_backproject_cells(const cbct_plan &p, const T *r, void *cells,
                                     const void *geom, hipStream_t s) {
-    const GeomLayout l = geom_layout(p.g);
+    const Cut c = cut_of(p.g);
     const char *base = (const char *)geom;
-    const dim3 b = brick_grid(p.g);
-    const dim3 grid(b.x * b.y * b.z, view_chunks(p.g));
+    const dim3 grid(c.bricks.x * c.bricks.y * c.bricks.z, c.chunks);
     const PixelRay *rays = (const PixelRay *)base;
-    const BrickView *bv = (const BrickView *)(base + l.bricks);
+    const BrickView *bv = (const BrickView *)(base + geom_layout(p.g, c).bricks);
     hipLaunchKernelGGL((by_columns(p.g) ? k_cells<T, true> : k_cells<T, false>), grid, dim3(256), 0,
-                       s, p.d_views, p.grid, brick_shape(p.g), p.g.nu, p.g.nv, p.g.n_views,
-                       view_chunk(p.g), rays, bv, r, (T *)cells, (T)p.g.step);
+                       s, p.d_views, p.grid, c.shape, p.g.nu, p.g.nv, p.g.n_views, c.chunk, rays,
+                       bv, r, (T *)cells, (T)p.g.step);
     return hipGetLastError();
 }
 
@@ -1029,8 +1029,8 @@ template <typename T>
 hipError_t launch_gather_cells(const cbct_plan &p, const void *ws, const T *f, double tau,
                                T *out, hipStream_t s) {
     dim3 grid((p.g.nx + G_BX - 1) / G_BX, (p.g.ny + G_BY - 1) / G_BY, p.g.nz);
-    hipLaunchKernelGGL(k_gather<T>, grid, dim3(G_BX, G_BY), 0, s, p.grid, view_chunks(p.g),
-                       (const T *)ws, f, (T)tau, out);
+    hipLaunchKernelGGL(k_gather<T>, grid, dim3(G_BX, G_BY), 0, s, p.grid,
+                       cut_of(p.g).chunks, (const T *)ws, f, (T)tau, out);
     return hipGetLastError();
 }
 
