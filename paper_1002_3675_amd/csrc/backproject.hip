@@ -787,9 +787,9 @@ __global__ __launch_bounds__(256) void k_gather(GridConst gc, int chunks,
 // arithmetic above all, and by the gathers: about 32 instructions a voxel
 // and view with four voxels a lane, 26 / 4 of them for the view, and two
 // loads.  Head (512 x 512 x 70, 40 views) 1640 us with one voxel a lane and
-// tested taps, 825 with four and conversions of the row, 765 now.  Eight
-// voxels a lane take 140 registers and 924 us; four in the 80 registers of
-// six wavefronts spill, 1014 us.
+// tested taps, 825 with four and conversions of the row, 765 without, 726
+// with six and what all lanes share in scalar registers (96 vector registers;
+// eight voxels take 116 and 752 us).
 constexpr int Q_BX = 64, Q_BY = 4;
 
 // sqrt(x) for x > 0: the hardware's reciprocal root and a correction, within
@@ -798,6 +798,14 @@ __device__ __forceinline__ float sqrt_pos(float x) {
     const float r = __builtin_amdgcn_rsqf(x);
     const float y = x * r;
     return __builtin_fmaf(__builtin_fmaf(-y, y, x), 0.5f * r, y);
+}
+
+// The same double in every lane, in scalar registers.
+__device__ __forceinline__ double uniform(double v) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
 }
 
 template <int ZC>
@@ -811,14 +819,18 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
     const int j = blockIdx.y * Q_BY + threadIdx.y;
     const int k0 = blockIdx.z * ZC;
     if (i >= gc.nx || j >= gc.ny) return;
-    const double su = dc.sddd / dc.aud, sv = dc.sddd / dc.avd;
-    const double ci = -dc.u0d / dc.aud, cj = -dc.v0d / dc.avd;  // index of u = 0, v = 0
-    const double kz = (double)k0 - views[0].Qd[2];  // the same in every view
+    // what all lanes share, in scalar registers where vector ones are short
+    // (two voxels a lane lose 3% by it)
+    auto same = [](double v) { return ZC > 2 ? uniform(v) : v; };
+    const double su = same(dc.sddd / dc.aud), svh = same(dc.sddd / dc.avd * hz);
+    // index of u = 0, v = 0
+    const double ci = same(-dc.u0d / dc.aud), cj = same(-dc.v0d / dc.avd);
+    const double kz = same((double)k0 - views[0].Qd[2]);  // the same in every view
     double sum[ZC], wz2[ZC];
 #pragma unroll
     for (int q = 0; q < ZC; ++q) {
         sum[q] = 0.0;
-        wz2[q] = (kz + q) * hz * ((kz + q) * hz);
+        wz2[q] = same((kz + q) * hz * ((kz + q) * hz));
     }
     // 32-bit byte offsets within a view, 24-bit factors, rows below 2^20
     const bool narrow = (long long)nu * nv < (1LL << 30) && nu < (1 << 22) && nv < (1 << 20);
@@ -833,7 +845,7 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
         const double id = id0 * __builtin_fma(-d, id0, 2.0);
         // fractional pixel indices: fi, and fj = fj0 + q dj in plane k0 + q
         const double fi = __builtin_fma(n * id, su, ci);
-        const double dj = id * (sv * hz);
+        const double dj = id * svh;
         const double fj0 = __builtin_fma(kz, dj, cj);
         const double fj1 = __builtin_fma((double)(ZC - 1), dj, fj0);
         const double i0d = __builtin_floor(fi);
@@ -1046,13 +1058,16 @@ hipError_t launch_eq2(const cbct_plan &p, const float *r, const float *f, double
     };
     // Voxels a lane: more share a view's arithmetic, fewer leave more
     // wavefronts.  Measured (before the rows' conversions went, which took 4
-    // to 7%), us with 1 / 2 / 4: 4096 wavefronts of single
-    // voxels (64^3) 15 / 16 / 23, 29k (157 x 141 x 67) 101 / 84 / 91, 33k
-    // (128^3) 195 / 156 / 161, 66k (256 x 256 x 64) 407 / 309 / 289, 287k
-    // (head) 1293 / 891 / 825.
+    // to 7%), us with 1 / 2 / 4: 4096 wavefronts of single voxels (64^3)
+    // 15 / 16 / 23, 29k (157 x 141 x 67) 101 / 84 / 91, 33k (128^3)
+    // 195 / 156 / 161, 66k (256 x 256 x 64) 407 / 309 / 289, 287k (head)
+    // 1293 / 891 / 825; and since, with 4 / 6: 66k 270 / 288, 160k 209 / 214,
+    // 246k 315 / 306, 287k 757 / 726.
     const long long waves = ((p.g.nx + Q_BX - 1LL) / Q_BX) * ((p.g.ny + Q_BY - 1LL) / Q_BY) * Q_BY *
                             p.g.nz;
-    if (waves >= 49152)
+    if (waves >= 196608)
+        launch(k_eq2<6>, 6);
+    else if (waves >= 49152)
         launch(k_eq2<4>, 4);
     else if (waves >= 8192)
         launch(k_eq2<2>, 2);

@@ -1,4 +1,4 @@
-"""Eq. (2) with one, two and four voxels a lane: grids whose planes leave a
+"""Eq. (2) with one, two, four and six voxels a lane: grids whose planes leave a
 remainder, detectors that hold all, some and none of the imager points, and
 a value that is not finite beside the detector's used part, against the FP64
 oracle.
@@ -23,6 +23,7 @@ TOL = 10 * 2.0 ** -24
 ONE = Geometry(37, 29, 11, 2.0, 2.0, 2.5, 40, 18, 2.6, 2.6, 300.0, 450.0, 5)
 TWO = dataclasses.replace(ONE, nx=70, ny=66, nz=63, hx=1.0, hy=1.0, hz=0.6)
 FOUR = dataclasses.replace(ONE, nx=260, ny=158, nz=65, hx=0.4, hy=0.4, hz=0.5, n_views=3)
+SIX = dataclasses.replace(ONE, nx=260, ny=400, nz=99, hx=0.4, hy=0.25, hz=0.33, n_views=3)
 NARROW = dict(nu=17, nv=7)          # many imager points beyond the detector
 SHIFTED = dict(u_off=30.0, v_off=-9.0)
 
@@ -32,8 +33,9 @@ def _waves(g):
 
 
 @pytest.mark.parametrize("det", [{}, NARROW, SHIFTED], ids=["whole", "narrow", "shifted"])
-@pytest.mark.parametrize("g,lo,hi", [(ONE, 0, 8192), (TWO, 8192, 49152), (FOUR, 49152, 1 << 40)],
-                         ids=["one", "two", "four"])
+@pytest.mark.parametrize("g,lo,hi", [(ONE, 0, 8192), (TWO, 8192, 49152), (FOUR, 49152, 196608),
+                                     (SIX, 196608, 1 << 40)],
+                         ids=["one", "two", "four", "six"])
 def test_eq2_matches_oracle(g, lo, hi, det):
     require_gpu()
     import paper_1002_3675_amd as cb
