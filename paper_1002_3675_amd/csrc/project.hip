@@ -1,10 +1,10 @@
 // Forward cone-beam projection P (Eq. (1)): ray-driven trilinear ray march.
 //
-// One lane per ray.  The float path (k_project_tile) gives a workgroup a
+// The float path (k_project_tile), one lane per ray, gives a workgroup a
 // square tile of neighbouring rays and stages the volume boxes they cross in
-// LDS; the double path (k_project) lets a wavefront cover 64 neighbouring
-// detector columns of one row, so at equal sample index the 64 lanes touch
-// neighbouring voxels and the taps of the wave share cache lines.  The volume is
+// LDS; the double path (k_project) gives a ray one to sixteen neighbouring
+// lanes, which take its samples in turn, and a wavefront neighbouring rays of
+// one detector row, so that its taps share cache lines.  The volume is
 // read from a copy with a one-voxel zero border, so every tap of every
 // sample the ray takes is in bounds without per-sample tests: the sample
 // interval is computed exactly (cell of every sample in [-1, N-1]).  Float
@@ -135,13 +135,15 @@ __device__ __forceinline__ int wave_max(int v) {
     return v;
 }
 
-// Ray sum for double volumes: double coordinates per sample.
+// Sum of every S-th sample of a ray, n0, n0 + S, ..., for double volumes:
+// double coordinates per sample.
+template <int S>
 __device__ __forceinline__ double march_double(const double Q[3], const double D[3], int n0,
                                                int n1, const double *__restrict__ fp, int px,
                                                int pxy) {
     double acc = 0.0;
     double nf = (double)n0;
-    for (int n = n0; n <= n1; ++n, nf += 1.0) {
+    for (int n = n0; n <= n1; n += S, nf += (double)S) {
         const double q0 = sample_coord(nf, D[0], Q[0]);
         const double q1 = sample_coord(nf, D[1], Q[1]);
         const double q2 = sample_coord(nf, D[2], Q[2]);
@@ -578,13 +580,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     if (partials) block_sum_store(sq, partials, tile);
 }
 
-template <typename T>
+// Double volumes: S neighbouring lanes take every S-th sample of a ray each.
+template <int S>
 __global__ __launch_bounds__(256) void k_project(const ViewConst *__restrict__ views, DetConst dc,
                                                  GridConst gc, int nu, int nv,
-                                                 const T *__restrict__ fp,
-                                                 const T *__restrict__ Y, T *__restrict__ out,
-                                                 double *__restrict__ partials, T step) {
-    const int i = blockIdx.x * PROJ_BX + threadIdx.x;
+                                                 const double *__restrict__ fp,
+                                                 const double *__restrict__ Y,
+                                                 double *__restrict__ out, double step) {
+    const int i = blockIdx.x * (PROJ_BX / S) + threadIdx.x / S;
     const int j = blockIdx.y * PROJ_BY + threadIdx.y;
     const int k = blockIdx.z;
     const bool valid = i < nu && j < nv;
@@ -594,21 +597,17 @@ __global__ __launch_bounds__(256) void k_project(const ViewConst *__restrict__ v
     ray_setup(vc, dc, valid ? i : 0, valid ? j : 0, Q, D);
     to_float3(D, Df);
     int n0 = 1, n1 = 0;
-    if (valid) ray_interval<T>(Q, D, Df, gc, n0, n1);
+    if (valid) ray_interval<double>(Q, D, Df, gc, n0, n1);
     const int px = gc.nx + 2;
     const int pxy = px * (gc.ny + 2);
-    const double acc = march_double(Q, D, n0, n1, fp, px, pxy);
-    double sq = 0.0;
-    if (valid) {
+    double acc = march_double<S>(Q, D, n0 + (int)threadIdx.x % S, n1, fp, px, pxy);
+#pragma unroll
+    for (int d = 1; d < S; d *= 2) acc += __shfl_xor(acc, d, 64);
+    if (valid && threadIdx.x % S == 0) {
         const long long idx = ((long long)k * nv + j) * nu + i;
-        T val = (T)(acc * (double)step);
+        double val = acc * step;
         if (Y) val -= Y[idx];
         out[idx] = val;
-        sq = (double)val * (double)val;
-    }
-    if (partials) {
-        const int blin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-        block_sum_store(sq, partials, blin);
     }
 }
 
@@ -632,8 +631,28 @@ __global__ __launch_bounds__(256) void k_count(const ViewConst *__restrict__ vie
     if ((threadIdx.x & 63) == 0) atomicAdd(count, c);
 }
 
-dim3 project_grid(const cbct_plan &p) {
-    return dim3((p.g.nu + PROJ_BX - 1) / PROJ_BX, (p.g.nv + PROJ_BY - 1) / PROJ_BY, p.g.n_views);
+// Grid of blocks of 64 x 4 lanes, `per` neighbouring lanes to a ray.
+dim3 project_grid(const cbct_plan &p, int per) {
+    const int bx = PROJ_BX / per;
+    return dim3((p.g.nu + bx - 1) / bx, (p.g.nv + PROJ_BY - 1) / PROJ_BY, p.g.n_views);
+}
+
+// Lanes that share a ray of the double projector, by its samples on average
+// (rays that miss the grid counted): more of them shorten the chain of a
+// ray's loads and keep a wavefront's taps closer together, until setting the
+// ray up in each costs more.  With pixels under half a voxel at the axis
+// neighbouring rays share their taps already.  Measured, us with 1 / 2 / 4 /
+// 8 / 16 lanes: 46 samples (32^3, 60 views) 47 / 44 / 46 / 48 / 52, 74
+// (60 x 56 x 28, 10 views) 54 / 36 / 34 / 34 / 34, 115 (100 x 91 x 15, 16)
+// 85 / 68 / 51 / 48 / 44, 174 (128^3, 20) 1411 / 830 / 681 / 644 / 523, 395
+// (256 x 256 x 64, 10) 1818 / 1089 / 696 / 579 / 522, 917 (512 x 512 x 70, 4)
+// 2453 / 1858 / 1780 / 1698 / 1691; 32 lanes are slower from 115 samples up.
+// 133 samples, pixels of a fifth of a voxel: 315 / 307 / 361 / 369 / 354.
+int lanes_per_ray(const cbct_plan &p) {
+    const cbct_geom &g = p.g;
+    if (g.au * g.sad < 0.5 * g.sdd * std::min(g.hx, g.hy)) return 1;
+    const double mean = (double)p.samples / ((double)g.nu * g.nv * g.n_views);
+    return mean >= 160 ? 16 : mean >= 96 ? 8 : mean >= 64 ? 4 : mean >= 24 ? 2 : 1;
 }
 
 size_t tile_count(const cbct_geom &g) {
@@ -698,15 +717,27 @@ hipError_t launch_project(const cbct_plan &p, const T *fpad, const T *Y, T *out,
                            (float)p.g.step, tile_margin(p.g));
     } else {
         if (partials) return hipErrorInvalidValue;  // no partial sums in double
-        hipLaunchKernelGGL(k_project<T>, project_grid(p), dim3(PROJ_BX, PROJ_BY), 0, s,
-                           p.d_views, p.det, p.grid, p.g.nu, p.g.nv, fpad, Y, out, partials,
-                           (T)p.g.step);
+        auto launch = [&](auto kernel, int per) {
+            hipLaunchKernelGGL(kernel, project_grid(p, per), dim3(PROJ_BX, PROJ_BY), 0, s,
+                               p.d_views, p.det, p.grid, p.g.nu, p.g.nv, fpad, Y, out, p.g.step);
+        };
+        const int per = lanes_per_ray(p);
+        if (per == 16)
+            launch(k_project<16>, 16);
+        else if (per == 8)
+            launch(k_project<8>, 8);
+        else if (per == 4)
+            launch(k_project<4>, 4);
+        else if (per == 2)
+            launch(k_project<2>, 2);
+        else
+            launch(k_project<1>, 1);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_count_samples(const cbct_plan &p, unsigned long long *count, hipStream_t s) {
-    hipLaunchKernelGGL(k_count, project_grid(p), dim3(PROJ_BX, PROJ_BY), 0, s, p.d_views, p.det,
+    hipLaunchKernelGGL(k_count, project_grid(p, 1), dim3(PROJ_BX, PROJ_BY), 0, s, p.d_views, p.det,
                        p.grid, p.g.nu, p.g.nv, count);
     return hipGetLastError();
 }
