@@ -173,15 +173,14 @@ __device__ __forceinline__ double march_double(const double Q[3], const double D
 // cost two thirds of what the conversion and the integer adds of the same
 // sum cost: 31 -> 29 vector instructions a sample.
 template <int RXC>
-__device__ __forceinline__ float staged_samples(int base, int RXr, int RXY, float m, float mb,
-                                                const float Df[3], const float of[3]) {
+__device__ __forceinline__ float staged_samples(float seg, int base, int RXr, int RXY, float m,
+                                                float mb, const float Df[3], const float of[3]) {
     typedef const __attribute__((address_space(3))) float *lds_t;
     const int RX = RXC > 0 ? RXC : RXr;
     const float Xf = __builtin_bit_cast(float, 4);
     const float RXf = __builtin_bit_cast(float, 4 * RX);
     const float RXYf = __builtin_bit_cast(float, 4 * RXY);
     const float basef = (float)base * __builtin_bit_cast(float, 1);
-    float seg = 0.0f;
     auto sample = [&](float m) {
         const float lx = __builtin_fmaf(m, Df[0], of[0]);
         const float ly = __builtin_fmaf(m, Df[1], of[1]);
@@ -223,7 +222,9 @@ __device__ __forceinline__ float staged_samples(int base, int RXr, int RXY, floa
 // whose own boxes do not fit.  A fitting chunk's box of the zero-bordered
 // volume is loaded straight into LDS (buffer loads to LDS, one z plane at a
 // time) and the eight trilinear taps of every sample are read from LDS; an
-// unfitting chunk reads its taps from global memory.  The samples, their
+// unfitting chunk reads its taps from global memory or, with HALVES, is
+// staged piece by piece for one half of the tile after the other, if those
+// boxes fit.  The samples, their
 // cells and weights are exactly those of sample_cell and seg_axis,
 // whatever the chunking.  A square tile
 // keeps the bundle, and so the box, narrow in both detector directions.
@@ -362,10 +363,22 @@ __device__ __forceinline__ int best_residue(const uint4 *pat, int p, int lane) {
     return key & 31;
 }
 
+// Padded z indices that the samples nc .. nc + TILE_SUB - 1 of the rays
+// between four with z increments a .. d can touch.
+__device__ __forceinline__ void half_range(double Qz, double a, double b, double c, double d,
+                                           int nc, int Nz, int margin, int &z0, int &z1) {
+    const double lo = fmin(fmin(a, b), fmin(c, d)), hi = fmax(fmax(a, b), fmax(c, d));
+    const double f = (double)nc, l = (double)(nc + TILE_SUB - 1);
+    const double qmin = Qz + fmin(f * lo, l * lo), qmax = Qz + fmax(f * hi, l * hi);
+    z0 = min(max((int)floor(fmax(qmin, -4.0)) - margin + 1, 0), Nz + 2);
+    z1 = max(min((int)floor(fmin(qmax, (double)Nz + 4.0)) + margin + 2, Nz + 1), -1);
+}
+
 // At most 80 VGPRs: six wavefronts per SIMD (six groups of 27 KB of LDS per
 // CU).  Seven or eight with smaller boxes leave chunks that do not fit
 // (256 x 256 x 64: 1.04 -> 1.47 and 2.56 ms); five with larger ones are slower
 // at the head size (5.35 -> 5.46 ms) and no faster elsewhere.
+template <bool HALVES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_project_tile(
     const ViewConst *__restrict__ views, DetConst dc, GridConst gc, int nu, int nv,
     const float *__restrict__ fp, int fp_elems, const float *__restrict__ Y,
@@ -375,7 +388,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     __shared__ int4 boxes[BOX_TAB];  // piece boxes, packed b0 | b1 << 16 per axis
     __shared__ int red[2][4];
     __shared__ int pitch_max, plane_res[4];
-    __shared__ double corner[4][3];
+    __shared__ double corner[4][3], mid[4];
     const int tid = threadIdx.x;
     const int lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     // tiles u-fastest, then v, then view; contiguous per XCD, so the rays
@@ -399,6 +412,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     if ((ti == 0 || ti == TILE_U - 1) && (tj == 0 || tj == TILE_V - 1))
 #pragma unroll
         for (int a = 0; a < 3; ++a) corner[(ti != 0) + 2 * (tj != 0)][a] = D[a];
+    // and the z increments beside its middle, rows 7 and 8
+    if (HALVES && (ti == 0 || ti == TILE_U - 1) && (tj == TILE_V / 2 - 1 || tj == TILE_V / 2))
+        mid[(ti != 0) + 2 * (tj == TILE_V / 2)] = D[2];
     // union of the tile's sample intervals
     const bool any = n0 <= n1;
     int lo = wave_min(any ? n0 : 0x7fffffff), hi = wave_max(any ? n1 : -1);
@@ -460,6 +476,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
             if (lane == 0) plane_res[wid] = e;
         }
         __syncthreads();
+        float seg = 0.0f;  // of the current chunk
+        int rest = 0;      // pieces left of an unfitting chunk
+        int half = -1;     // half of the tile whose box is staged, or -1: all of it
         for (int c = cg; c < cend;) {
             const int nc = nc0 + TILE_SUB * c;
             const int4 ent = boxes[c - cg];
@@ -469,10 +488,50 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
                                  __builtin_amdgcn_readfirstlane(ent.y),
                                  __builtin_amdgcn_readfirstlane(ent.z), 0),
                        b0, b1);
-            const int run = __builtin_amdgcn_readfirstlane(ent.w);
-            const bool staged = run > 0;
-            const int len = TILE_SUB * (staged ? run : -run);
-            c += staged ? run : -run;
+            int run = 1;  // pieces of this step
+            bool staged = true;
+            if constexpr (HALVES) {
+                if (rest == 0) {  // a new chunk
+                    const int w = __builtin_amdgcn_readfirstlane(ent.w);
+                    seg = 0.0f;
+                    if (w < 0)
+                        rest = -w;
+                    else
+                        run = w;
+                }
+                staged = rest == 0;
+            } else {
+                run = __builtin_amdgcn_readfirstlane(ent.w);
+                staged = run > 0;
+                run = abs(run);
+                c += run;
+                seg = 0.0f;
+            }
+            const int len = TILE_SUB * run;
+            if (HALVES && rest) {
+                // a piece that does not fit: the halves of the tile, 8 rows of
+                // pixels each, in turn, if theirs do
+                int z0[2], z1[2];
+                bool fit = true;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    half_range(Q[2], q ? mid[2] : corner[0][2], q ? mid[3] : corner[1][2],
+                               q ? corner[2][2] : mid[0], q ? corner[3][2] : mid[1], nc, N[2],
+                               margin, z0[q], z1[q]);
+                    z0[q] = max(__builtin_amdgcn_readfirstlane(z0[q]), b0[2]);
+                    z1[q] = min(__builtin_amdgcn_readfirstlane(z1[q]), b1[2]);
+                    const int e0[3] = {b0[0], b0[1], z0[q]}, e1[3] = {b1[0], b1[1], z1[q]};
+                    fit = fit && (z0[q] > z1[q] || box_fits(e0, e1));  // or no samples
+                }
+                if (fit) {
+                    half = half < 0 ? 0 : half;
+                    b0[2] = half ? z0[1] : z0[0];
+                    b1[2] = half ? z1[1] : z1[0];
+                    staged = true;
+                } else {
+                    half = -1;
+                }
+            }
             const int RX = b1[0] - b0[0] + 1, RY = b1[1] - b0[1] + 1, RZ = b1[2] - b0[2] + 1;
             // LDS rows have an odd pitch, so rays spread across rows (views whose
             // rays run along x) do not pile onto one bank
@@ -481,12 +540,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
             // spaced planes fit; narrower rows keep close planes
             int RXY = RXP * RY;
             const int pi = (pmax - RXP) >> 1;
-            if (staged && pi < 4) {
+            if (staged && (!HALVES || pi >= 0) && pi < 4) {
                 const int padded =
                     RXY + ((__builtin_amdgcn_readfirstlane(plane_res[pi]) - RXY) & 31);
                 if (padded * RZ <= TILE_VOL) RXY = padded;
             }
-            __syncthreads();  // the previous chunk's readers are done
+            if (!HALVES || staged) __syncthreads();  // the previous chunk's readers are done
             if (staged) {
                 // Plane z of the box is RXP * RY consecutive LDS elements, x
                 // fastest; each wavefront loads 64 consecutive elements
@@ -517,13 +576,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
                 }
                 __builtin_amdgcn_s_waitcnt(0);  // the loads have landed in LDS
             }
-            __syncthreads();
+            if (!HALVES || staged) __syncthreads();
             const int na = max(n0, nc), nb = min(n1, nc + len - 1);
-            if (na > nb) continue;
+            if (!HALVES && na > nb) continue;
+            const bool mine = !HALVES || ((half < 0 || (wid >> 1) == half) && na <= nb);
             const int s = nc & ~(SEG - 1);
-            const SegOrigin o = seg_origin(Q, D, s);
-            float seg = 0.0f;
-            if (staged) {
+            SegOrigin o;
+            if (mine) o = seg_origin(Q, D, s);
+            if (mine && staged) {
                 const int base = 4 * ((o.I[2] + 1 - b0[2]) * RXY + (o.I[1] + 1 - b0[1]) * RXP +
                                       (o.I[0] + 1 - b0[0])) +
                                  (int)(size_t)(__attribute__((address_space(3))) float *)vol;
@@ -533,7 +593,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
                 switch (RXP) {
 #define CBCT_PITCH(n)                                                                   \
     case n:                                                                             \
-        seg = staged_samples<n>(base, RXP, RXY, ma, mb, Df, o.f);                   \
+        seg = staged_samples<n>(seg, base, RXP, RXY, ma, mb, Df, o.f);                   \
         break;
                     CBCT_PITCH(5) CBCT_PITCH(7) CBCT_PITCH(9) CBCT_PITCH(11) CBCT_PITCH(13)
                     CBCT_PITCH(15) CBCT_PITCH(17) CBCT_PITCH(19) CBCT_PITCH(21) CBCT_PITCH(23)
@@ -541,9 +601,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
                     CBCT_PITCH(35) CBCT_PITCH(37) CBCT_PITCH(39) CBCT_PITCH(41)
 #undef CBCT_PITCH
                     default:
-                        seg = staged_samples<0>(base, RXP, RXY, ma, mb, Df, o.f);
+                        seg = staged_samples<0>(seg, base, RXP, RXY, ma, mb, Df, o.f);
                 }
-            } else {
+            } else if (mine) {
                 const int base = (o.I[2] + 1) * pxy + (o.I[1] + 1) * px + (o.I[0] + 1);
                 const float mb = (float)(nb - s);
                 for (float m = (float)(na - s); m <= mb; m += 1.0f) {
@@ -566,7 +626,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
                     seg += c0 + wz * (c1 - c0);
                 }
             }
-            acc += (double)seg;
+            if constexpr (HALVES) {
+                if (half == 0) {  // the other half of the piece
+                    half = 1;
+                    continue;
+                }
+                half = -1;
+                c += run;
+                if (rest > 0) --rest;
+                if (rest == 0) acc += (double)seg;
+            } else {
+                acc += (double)seg;
+            }
         }
     }
     double sq = 0.0;
@@ -659,6 +730,26 @@ size_t tile_count(const cbct_geom &g) {
     return (size_t)((g.nu + TILE_U - 1) / TILE_U) * ((g.nv + TILE_V - 1) / TILE_V) * g.n_views;
 }
 
+// Whether pieces that exceed the LDS box are staged in halves of the tile
+// (k_project_tile<true>), eight rows of pixels each in turn: where the box of a
+// piece at the axis, its rays oblique or along x or y, a cell and a half
+// added on each side, exceeds it, and the tiles are two a CU or more.  (us,
+// all taps of such a piece from memory / in halves) 128^3 with pixels of a
+// voxel, 40 views 1379 / 358, 160^3 with planes of half a voxel, 30 views
+// 2925 / 856, 208 x 205 x 76, 7 views 514 / 269, 80 x 69 x 96, 10 views
+// 124 / 100; 330 tiles 80 / 88.  Where pieces fit, the code for the halves
+// costs 2 to 8%.  Sums and results are the same bit for bit either way.
+bool in_halves(const cbct_geom &g) {
+    const double m = g.sad / g.sdd, u = TILE_U * g.au * m, l = TILE_SUB * g.step;
+    const double z = std::min(TILE_V * g.av * m / g.hz + 3.5, g.nz + 2.0);
+    const double d = 0.7071 * (u + l), nx = g.nx + 2.0, ny = g.ny + 2.0;
+    auto area = [&](double x, double y) {
+        return std::min(x / g.hx + 3.5, nx) * std::min(y / g.hy + 3.5, ny);
+    };
+    return z * std::max(area(d, d), std::max(area(l, u), area(u, l))) > TILE_LDS &&
+           tile_count(g) >= 512;
+}
+
 // One-dimensional grid of all tiles of all views (see xcd_tile).
 dim3 tile_grid(const cbct_plan &p) { return dim3((unsigned)tile_count(p.g)); }
 
@@ -712,9 +803,10 @@ hipError_t launch_project(const cbct_plan &p, const T *fpad, const T *Y, T *out,
                           double *partials, hipStream_t s) {
     const long long elems = (long long)padded_count(p);
     if constexpr (sizeof(T) == 4) {
-        hipLaunchKernelGGL(k_project_tile, tile_grid(p), dim3(256), 0, s, p.d_views, p.det,
-                           p.grid, p.g.nu, p.g.nv, fpad, (int)elems, Y, out, partials,
-                           (float)p.g.step, tile_margin(p.g));
+        hipLaunchKernelGGL((in_halves(p.g) ? k_project_tile<true> : k_project_tile<false>),
+                           tile_grid(p), dim3(256), 0, s, p.d_views, p.det, p.grid, p.g.nu,
+                           p.g.nv, fpad, (int)elems, Y, out, partials, (float)p.g.step,
+                           tile_margin(p.g));
     } else {
         if (partials) return hipErrorInvalidValue;  // no partial sums in double
         auto launch = [&](auto kernel, int per) {
