@@ -392,6 +392,7 @@ extern "C" int cbct_plan_create(const cbct_geom *gin, cbct_plan **out) {
             return rc;
         }
         p->samples = (int64_t)hcount;
+        choose_cells(*p);
         *out = p.release();
         return CBCT_OK;
     } catch (const std::bad_alloc &) {

@@ -14,10 +14,11 @@
 //     about as many; of few bricks, several per brick with a share of the
 //     views each):
 //     for every view the workgroup stages the rays of its brick's footprint
-//     in LDS; each lane then visits the pixels whose rays can cross its
-//     cell and adds each ray's samples in the cell, r * (trilinear corner
-//     weight), to eight moments in registers, the samples of one crossing
-//     in closed form (see crossing_sums), in float and double alike;
+//     in LDS (unless the source is very near, see choose_cells); each lane
+//     then visits the pixels whose rays can cross its cell and adds each
+//     ray's samples in the cell, r * (trilinear corner weight), to eight
+//     moments in registers, the samples of one crossing in closed form (see
+//     crossing_sums), in float and double alike;
 //   * pass 2 (one lane per voxel): sum the matching corner of the eight
 //     cells that share the voxel, optionally fused with Step 1 of
 //     Algorithm A1, g = f - tau * P^T r.
@@ -25,6 +26,7 @@
 // Each (ray, cell) crossing is visited once, not once per trilinear tap,
 // every sum has a fixed order, and no lane writes memory another lane
 // writes.
+#include <algorithm>
 #include <type_traits>
 
 #include "ray.hpp"
@@ -58,7 +60,13 @@ struct PixelRay {
 };
 
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double rcp(double x) { return 1.0 / x; }
+// to half an ulp and 2^-100, in seven instructions for a division's eleven
+__device__ __forceinline__ double rcp(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+    return r;
+}
 
 template <typename T> __device__ __forceinline__ T fma_t(T a, T b, T c);
 template <> __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
@@ -95,13 +103,12 @@ __global__ __launch_bounds__(256) void k_rays(const ViewConst *__restrict__ view
 
 // How the rays through pixel columns i0 .. i1 of a view run in x and y, a sum
 // of these.  1: x increases along them, 2: y does.  4: for both axes they all
-// run the same way, and not too near zero to tell.  16: they have a main
-// axis, along which each advances, in cells, at least a third as fast as
-// along the other; it is y if 8 is there, else x.  Only rays more than 50
-// degrees apart in one brick, which the source is then very near to, have
-// none.
-__device__ __forceinline__ int ray_directions(const ViewConst &vc, const DetConst &dc, int i0,
-                                              int i1) {
+// run the same way, and not too near zero to tell.  8: their main axis, along
+// which each advances, in cells, at least a third as fast as along the other,
+// is y, else x.  Only rays more than 50 degrees apart in one brick (in
+// cells), which the source is then very near to, have none (see by_columns).
+__host__ __device__ __forceinline__ int ray_directions(const ViewConst &vc, const DetConst &dc,
+                                                       int i0, int i1) {
     const float ua = dc.u0 + (float)i0 * dc.au, ub = dc.u0 + (float)i1 * dc.au;
     const float tol = 1e-4f * (fabsf(vc.W[0]) + fabsf(vc.W[1]));
     float da[2], db[2];
@@ -117,10 +124,10 @@ __device__ __forceinline__ int ray_directions(const ViewConst &vc, const DetCons
         return da[a] * db[a] > 0.0f && 3.0f * fabsf(da[a]) >= fabsf(da[1 - a]) &&
                3.0f * fabsf(db[a]) >= fabsf(db[1 - a]);
     };
-    const bool x = leads(0), y = leads(1);
-    if (y && (!x || fminf(fabsf(da[1]), fabsf(db[1])) > fminf(fabsf(da[0]), fabsf(db[0]))))
+    if (leads(1) &&
+        (!leads(0) || fminf(fabsf(da[1]), fabsf(db[1])) > fminf(fabsf(da[0]), fabsf(db[0]))))
         dir |= 8;
-    return x || y ? dir | 16 : dir;
+    return dir;
 }
 
 // A brick in one view (prepared once), 64 bytes.
@@ -141,8 +148,7 @@ __device__ __forceinline__ int ray_directions(const ViewConst &vc, const DetCons
 // directions: batch_n views and batch_rays rays when a batch begins with this
 // view (batch_n = 0: the footprint alone exceeds the table and is staged in
 // parts), base this view's first table entry in its batch.  For k_cells by
-// columns both hold the pixel columns too, in the upper 16 bits, and a view
-// without a main axis stands alone with batch_n = 0.
+// columns both hold the pixel columns too, in the upper 16 bits.
 struct BrickView {
     int i0, j0, w, h;
     int W, H, dirs, base;
@@ -151,9 +157,9 @@ struct BrickView {
 };
 static_assert(sizeof(BrickView) == 64, "one 64-byte scalar load");
 
-__device__ BrickView brick_view(const ViewConst &vc, const DetConst &dc, const GridConst &gc,
-                                double hx, double hy, double hz, int nu, int nv,
-                                const int c0[3], const int c1[3]) {
+__host__ __device__ inline BrickView brick_view(const ViewConst &vc, const DetConst &dc, double hx,
+                                                double hy, double hz, int nu, int nv,
+                                                const int c0[3], const int c1[3]) {
     const double cs = vc.csd, sn = vc.snd;
     // brick centre and half extents (mm) from the source; n across the view, d its depth
     const double ex = 0.5 * (c1[0] - c0[0]) * hx, ey = 0.5 * (c1[1] - c0[1]) * hy;
@@ -218,11 +224,10 @@ __global__ __launch_bounds__(64) void k_brick_views(const ViewConst *__restrict_
     const int c1[3] = {min(c0[0] + shape.x, gc.nx), min(c0[1] + shape.y, gc.ny), c0[2] + 1};
     for (int k0 = 0; k0 < nviews; k0 += 64) {
         const int k = min(k0 + lane, nviews - 1);
-        BrickView o = brick_view(views[k], dc, gc, hx, hy, hz, nu, nv, c0, c1);
+        BrickView o = brick_view(views[k], dc, hx, hy, hz, nu, nv, c0, c1);
         // a footprint beyond the table stands alone (batch_n = 0)
         const long long pixels = (long long)o.w * o.h;
-        const bool alone = pixels > TABLE || (by_columns && pixels > 0 &&
-                                              (o.w > COLUMNS || !(o.dirs & 16)));
+        const bool alone = pixels > TABLE || (by_columns && o.w > COLUMNS);
         const int size = alone ? -1 : (int)pixels | (by_columns ? o.w << 16 : 0);
         const int dir = o.dirs & 4 ? o.dirs & 7 : 0;
         int head = 0, n = 0, rays = 0, cols = 0, dirs = 0;
@@ -344,6 +349,23 @@ __device__ __forceinline__ float mul_zero(float a, float b) {
 }
 __device__ __forceinline__ double mul_zero(double a, double b) { return b == 0.0 ? 0.0 : a * b; }
 
+// The moments' sums below, of A and B and the samples' mean position.
+template <typename T>
+__device__ __forceinline__ void add_crossing(T m[8], T A, T B, T x, T y, T z, T Dx, T Dy, T Dz) {
+    const T bx = B * Dx, by = B * Dy;
+    const T bxy = bx * Dy, bxz = bx * Dz, byz = by * Dz;
+    const T px = A * x, py = A * y;
+    const T pxy = fma_t(px, y, bxy);
+    m[0] += A;
+    m[1] += px;
+    m[2] += py;
+    m[3] = fma_t(A, z, m[3]);
+    m[4] += pxy;
+    m[5] = fma_t(px, z, m[5]) + bxz;
+    m[6] = fma_t(py, z, m[6]) + byz;
+    m[7] = fma_t(pxy, z, fma_t(bxz, y, fma_t(byz, x, m[7])));
+}
+
 // Add the ray's samples in the cell to the moments m = sum r (1, x, y, z,
 // xy, xz, yz, xyz), x, y, z the weights minus 1/2.
 //
@@ -377,18 +399,32 @@ __device__ __forceinline__ void crossing_sums(T m[8], const vec4<T> ra, const ve
     const T z = fma_t(n, rb.z, rb.w);
     const T A = mul_zero(rc.y, k);
     const T B = A * fma_t(k * k, T(1) / T(12), T(-1) / T(12));
-    const T bx = B * rb.x, by = B * rb.y;
-    const T bxy = bx * rb.y, bxz = bx * rb.z, byz = by * rb.z;
-    const T px = A * x, py = A * y;
-    const T pxy = fma_t(px, y, bxy);
-    m[0] += A;
-    m[1] += px;
-    m[2] += py;
-    m[3] = fma_t(A, z, m[3]);
-    m[4] += pxy;
-    m[5] = fma_t(px, z, m[5]) + bxz;
-    m[6] = fma_t(py, z, m[6]) + byz;
-    m[7] = fma_t(pxy, z, fma_t(bxz, y, fma_t(byz, x, m[7])));
+    add_crossing(m, A, B, x, y, z, rb.x, rb.y, rb.z);
+}
+
+// The same for a cell c .. c + 1 by itself, from the ray's increment: its face
+// crossings are brick_ray's of those faces.
+template <typename T>
+__device__ __forceinline__ void cell_sums(T m[8], const double D[3], T rv, const double Qd[3],
+                                          int nmid, const int c[3]) {
+    double qm[3];
+    T lo = T(-8388608), hi = T(8388608);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        qm[a] = __builtin_fma((double)nmid, D[a], Qd[a]);
+        const T q = (T)qm[a], inv = rcp((T)D[a]);
+        const T t0 = ((T)c[a] - q) * inv, t1 = ((T)(c[a] + 1) - q) * inv;
+        lo = max_t(lo, min_t(t0, t1));
+        hi = min_t(hi, max_t(t0, t1));
+    }
+    const T n0 = min_t(ceil_t(lo), T(8388608)), k = max_t(ceil_t(hi) - n0, T(0));
+    const double n = (double)n0 + 0.5 * ((double)k - 1.0);
+    const T x = (T)(__builtin_fma(n, D[0], qm[0]) - ((double)c[0] + 0.5));
+    const T y = (T)(__builtin_fma(n, D[1], qm[1]) - ((double)c[1] + 0.5));
+    const T z = (T)(__builtin_fma(n, D[2], qm[2]) - ((double)c[2] + 0.5));
+    const T A = mul_zero(rv, k);
+    const T B = A * fma_t(k * k, T(1) / T(12), T(-1) / T(12));
+    add_crossing(m, A, B, x, y, z, (T)D[0], (T)D[1], (T)D[2]);
 }
 
 // The same by pixel columns.  The rays of a column of pixels lie in one plane
@@ -452,6 +488,46 @@ __device__ __forceinline__ void moments_to_corners(const T m[8], T c[8]) {
     }
 }
 
+// The cells c0 .. c1 - 1 of a brick.  Bricks x-fastest, then y, then z; each
+// XCD takes one contiguous range, so the bricks resident on an XCD at a time
+// are neighbours whose footprints (ray table rows) overlap in its L2.
+__device__ __forceinline__ void brick_cells(int brick, int2 shape, const GridConst &gc, int c0[3],
+                                            int c1[3]) {
+    const int nbx = (gc.nx + shape.x) / shape.x, nby = (gc.ny + shape.y) / shape.y;
+    c0[0] = (brick % nbx) * shape.x - 1;
+    c0[1] = ((brick / nbx) % nby) * shape.y - 1;
+    c0[2] = brick / (nbx * nby) - 1;
+    c1[0] = min(c0[0] + shape.x, gc.nx);
+    c1[1] = min(c0[1] + shape.y, gc.ny);
+    c1[2] = c0[2] + 1;
+}
+
+// A lane's cell in its brick.  A wavefront of a 16 x 16 brick covers 8 x 8
+// cells, every 16 consecutive lanes 4 x 4 of them: the rays such lanes read
+// together are then few and near each other in the table, whatever the view's
+// direction.  Other bricks take their cells row by row (lanes beyond the last
+// row idle).
+__device__ __forceinline__ void lane_cell(int tid, int2 shape, int &lx, int &ly) {
+    const bool square = shape.x == 16 && shape.y == 16;
+    lx = square ? (tid & 3) | ((tid >> 2) & 4) | ((tid >> 3) & 8) : tid % shape.x;
+    ly = square ? ((tid >> 2) & 3) | ((tid >> 3) & 4) | ((tid >> 4) & 8) : tid / shape.x;
+}
+
+// The corner sums of cell (cx, cy, cz) into the workgroup's chunk of `cells`.
+template <typename T>
+__device__ __forceinline__ void store_corners(const T m[8], const GridConst &gc, int cx, int cy,
+                                              int cz, T step, T *__restrict__ cells) {
+    const long long cp = cell_pitch(gc.nx);
+    const long long ncell = cp * (gc.ny + 1) * (gc.nz + 1);
+    const long long lin =
+        (long long)(cx + 1) + cp * ((cy + 1) + (long long)(gc.ny + 1) * (cz + 1));
+    T out[8];
+    moments_to_corners(m, out);
+    cells += 8 * ncell * blockIdx.y;
+#pragma unroll
+    for (int o = 0; o < 8; ++o) cells[o * ncell + lin] = out[o] * step;
+}
+
 // Workgroups of 256 lanes, one per brick (see brick_shape) and chunk of views
 // (see cut_of).
 //
@@ -489,25 +565,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COL && size
     __shared__ int2 cslots[PARTS];  // and first column, whether y is the main axis
     static_assert(CB_Z == 1, "a brick is one z layer of cells");
     const int tid = threadIdx.x;
-    // bricks x-fastest, then y, then z; each XCD takes one contiguous range,
-    // so the bricks resident on an XCD at a time are neighbours whose
-    // footprints (ray table rows) overlap in its L2
-    // bricks x-fastest, then y, then z; each XCD takes one contiguous range,
-    // so the bricks resident on an XCD at a time are neighbours whose
-    // footprints (ray table rows) overlap in its L2
-    const int nbx = (gc.nx + shape.x) / shape.x, nby = (gc.ny + shape.y) / shape.y;
     const int brick = xcd_tile(blockIdx.x, gridDim.x);
     const BrickView *bv = bviews + (long long)brick * nviews;
-    const int c0[3] = {(brick % nbx) * shape.x - 1, ((brick / nbx) % nby) * shape.y - 1,
-                       brick / (nbx * nby) - 1};
-    const int c1[3] = {min(c0[0] + shape.x, gc.nx), min(c0[1] + shape.y, gc.ny), c0[2] + 1};
-    // A wavefront of a 16 x 16 brick covers 8 x 8 cells, every 16 consecutive
-    // lanes 4 x 4 of them: the rays such lanes read together are then few and
-    // near each other in the table, whatever the view's direction.  Other
-    // bricks take their cells row by row (lanes beyond the last row idle).
-    const bool square = shape.x == 16 && shape.y == 16;
-    const int lx = square ? (tid & 3) | ((tid >> 2) & 4) | ((tid >> 3) & 8) : tid % shape.x;
-    const int ly = square ? ((tid >> 2) & 3) | ((tid >> 3) & 4) | ((tid >> 4) & 8) : tid / shape.x;
+    int c0[3], c1[3], lx, ly;
+    brick_cells(brick, shape, gc, c0, c1);
+    lane_cell(tid, shape, lx, ly);
     T m[8];
 #pragma unroll
     for (int o = 0; o < 8; ++o) m[o] = T(0);
@@ -534,24 +596,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COL && size
         cf.cy = cf.y0 - fy - T(0.5);
         return cf;
     };
-    // A view without a main axis, by columns: every ray set up by each lane.
-    auto direct = [&](const BrickView b, int k) {
-        int px, py;
-        const CellFaces<T> cf = cell_faces(0, px, py);
-        const int W = min(b.W, b.w), H = min(b.H, b.h);
-        const int ci = (int)__builtin_ceilf(b.a0 + b.ax * (float)px + b.ay * (float)py);
-        const int cj = (int)__builtin_ceilf(b.b0 + b.bx * (float)px + b.by * (float)py);
-        const ViewConst &vc = views[k];
-        const double Qd[3] = {vc.Qd[0], vc.Qd[1], vc.Qd[2]};
-        long long pix = ((long long)k * nv + b.j0 + max(min(cj, b.h - H), 0)) * nu + b.i0 +
-                        max(min(ci, b.w - W), 0);
-        for (int y = 0; y < H; ++y, pix += nu)
-            for (int x = 0; x < W; ++x) {
-                const StagedRay<T> e =
-                    stage_ray(brick_ray<T>(rays[pix + x].D, Qd, vc.nmid, c0, c1), r[pix + x]);
-                crossing_sums<false>(m, e.a, e.b, e.c, cf);
-            }
-    };
     const int kend = min(nviews, (int)(blockIdx.y + 1) * chunk);
     for (int k = blockIdx.y * chunk; k < kend;) {
         // the batch, or the parts of a view too large for the table: bands of
@@ -570,12 +614,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COL && size
             pw = (bv[k].w + cols - 1) / cols;
             ph = min(TABLE / pw, bv[k].h);
             parts = cols * ((bv[k].h + ph - 1) / ph);
-        }
-        if constexpr (COL) {
-            if (bv[k].w > 0 && !(bv[k].dirs & 16)) {
-                direct(bv[k], k);
-                parts = 0;
-            }
         }
         for (int part = 0; part < parts; ++part) {
             int oi = 0, oj = 0, w = bv[k].w, h = bv[k].h;  // the part within the view
@@ -731,16 +769,86 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COL && size
         }
         k += n;
     }
-    if (c0[0] + lx >= c1[0] || c0[1] + ly >= c1[1]) return;
-    const long long cp = cell_pitch(gc.nx);
-    const long long ncell = cp * (gc.ny + 1) * (gc.nz + 1);
-    const long long lin = (long long)(c0[0] + 1 + lx) +
-                          cp * ((c0[1] + 1 + ly) + (long long)(gc.ny + 1) * (c0[2] + 1));
-    T out[8];
-    moments_to_corners(m, out);
-    cells += 8 * ncell * blockIdx.y;
+    if (c0[0] + lx < c1[0] && c0[1] + ly < c1[1])
+        store_corners(m, gc, c0[0] + lx, c0[1] + ly, c0[2], step, cells);
+}
+
+// The same where the source is so near that a brick's blocks of pixels are far
+// more than its cells need (see choose_cells): each lane takes the pixels of
+// its own cell, their rays from the ray table.  A visit is about 75 VALU
+// instructions, a third of them in double, and two loads, and wavefronts wait
+// for no others.
+template <typename T>
+__global__ __launch_bounds__(256) void k_cells_near(
+    const ViewConst *__restrict__ views, DetConst dc, GridConst gc, int2 shape, int nu, int nv,
+    int nviews, int chunk, const PixelRay *__restrict__ rays, const T *__restrict__ r,
+    T *__restrict__ cells, T step) {
+    int c0[3], c1[3], lx, ly;
+    brick_cells(xcd_tile(blockIdx.x, gridDim.x), shape, gc, c0, c1);
+    lane_cell(threadIdx.x, shape, lx, ly);
+    const int c[3] = {c0[0] + lx, c0[1] + ly, c0[2]};
+    if (c[0] >= c1[0] || c[1] >= c1[1]) return;
+    T m[8];
 #pragma unroll
-    for (int o = 0; o < 8; ++o) cells[o * ncell + lin] = out[o] * step;
+    for (int o = 0; o < 8; ++o) m[o] = T(0);
+    const float su = (float)(dc.sddd / dc.aud), sv = (float)(dc.sddd / dc.avd * gc.hz);
+    const float ci = (float)(-dc.u0d / dc.aud), cj = (float)(-dc.v0d / dc.avd);
+    const int kend = min(nviews, (int)(blockIdx.y + 1) * chunk);
+    for (int k = blockIdx.y * chunk; k < kend; ++k) {
+        const ViewConst &vc = views[k];
+        // the bounds of the cell's projection, from its corners' (at most
+        // 4e-7 of an index off), and 0.01 pixel more
+        const double n = __builtin_fma((double)c[0], vc.en[0],
+                                       __builtin_fma((double)c[1], vc.en[1], vc.en[2]));
+        const double d = __builtin_fma((double)c[0], vc.ew[0],
+                                       __builtin_fma((double)c[1], vc.ew[1], vc.ew[2]));
+        float umin = 3e38f, umax = -3e38f, rmin = 3e38f, rmax = 0.0f;
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+            const float id = rcp((float)(d + (o & 1 ? vc.ew[0] : 0.0) + (o & 2 ? vc.ew[1] : 0.0)));
+            const float u =
+                (float)(n + (o & 1 ? vc.en[0] : 0.0) + (o & 2 ? vc.en[1] : 0.0)) * id * su;
+            umin = fminf(umin, u);
+            umax = fmaxf(umax, u);
+            rmin = fminf(rmin, id);
+            rmax = fmaxf(rmax, id);
+        }
+        const float va = (float)(c[2] - vc.Qd[2]) * sv, vb = (float)(c[2] + 1 - vc.Qd[2]) * sv;
+        const float vmin = fminf(va * rmin, va * rmax), vmax = fmaxf(vb * rmin, vb * rmax);
+        const float mu = 0.01f + 4e-7f * fmaxf(fabsf(umin), fabsf(umax));
+        const float mv = 0.01f + 4e-7f * fmaxf(fabsf(vmin), fabsf(vmax));
+        const int i0 = max((int)__builtin_ceilf(umin - mu + ci), 0);
+        const int j0 = max((int)__builtin_ceilf(vmin - mv + cj), 0);
+        const int i1 = min((int)__builtin_floorf(umax + mu + ci), nu - 1);
+        const int j1 = min((int)__builtin_floorf(vmax + mv + cj), nv - 1);
+        const double Qd[3] = {vc.Qd[0], vc.Qd[1], vc.Qd[2]};
+        const int nmid = vc.nmid;
+        const long long view = (long long)k * nu * nv;
+        int i = i0, j = j0;
+        auto next = [&] {
+            const long long at = view + (long long)j * nu + i;
+            if (++i > i1) {
+                i = i0;
+                ++j;
+            }
+            return at;
+        };
+        // two rays at a time: a few cells next to the source have most of a
+        // view's rays, and their lanes' chains are what the chip waits for
+        int q = i0 <= i1 && j0 <= j1 ? (i1 - i0 + 1) * (j1 - j0 + 1) : 0;
+        for (; q > 1; q -= 2) {
+            const long long a = next(), b = next();
+            const PixelRay ga = rays[a], gb = rays[b];
+            const T ra = r[a], rb = r[b];
+            cell_sums(m, ga.D, ra, Qd, nmid, c);
+            cell_sums(m, gb.D, rb, Qd, nmid, c);
+        }
+        if (q > 0) {
+            const long long a = next();
+            cell_sums(m, rays[a].D, r[a], Qd, nmid, c);
+        }
+    }
+    store_corners(m, gc, c[0], c[1], c[2], step, cells);
 }
 
 // Pass 2: out = sum of corner o of cell (v - o) over o in {0,1}^3 and over the
@@ -938,7 +1046,23 @@ int2 brick_shape(const cbct_geom &g) {
 // 1114 / 1052, 5 1278 / 1167; 512 x 512 x 70 (4.8 rows) 8790 / 7740.
 constexpr double COLUMN_ROWS = 3.0;
 
-bool by_columns(const cbct_geom &g) { return g.hz * g.sdd >= COLUMN_ROWS * g.sad * g.av; }
+//
+// A view's rays through a brick then need a main axis (see ray_directions).
+// They have one if their directions in cells lie within an interval of angles
+// that reaches less than from atan(1/3) to atan(3); with cells of sides 1 and
+// a, that is from atan(1/(3a)) to atan(3/a), at the narrowest.  A brick's rays
+// spread over at most its diagonal over the nearest depth, times the length of
+// (1, u/sdd); half the angle is left unused.
+bool by_columns(const cbct_geom &g) {
+    if (!(g.hz * g.sdd >= COLUMN_ROWS * g.sad * g.av)) return false;
+    const int2 shape = brick_shape(g);
+    const double D = hypot(shape.x * g.hx, shape.y * g.hy);
+    const double depth = g.sad - hypot(0.5 * (g.nx + 1) * g.hx + fabs(g.x_off),
+                                       0.5 * (g.ny + 1) * g.hy + fabs(g.y_off));
+    const double fan = (0.5 * g.nu * g.au + fabs(g.u_off)) / g.sdd + D / depth;
+    const double a = std::max(g.hx, g.hy) / std::min(g.hx, g.hy);
+    return 2.0 * D / depth * hypot(1.0, fan) < atan(3.0 / a) - atan(1.0 / (3.0 * a));
+}
 
 // Views a workgroup of the cell pass takes.  A small grid has fewer bricks
 // than the chip has room for (about 1800 workgroups), and each works its way
@@ -1023,6 +1147,63 @@ hipError_t launch_bp_prepare(const cbct_plan &p, void *geom, hipStream_t s) {
     return hipGetLastError();
 }
 
+// What decides is how many pixels the lanes of a brick visit, on average, and
+// how many its cells have: a sample of bricks and views, the same for a
+// geometry each time.  A visit's cost is the unit; a staged ray, a share of
+// the brick's 256 lanes, and a view's own costs are fitted to measurements.
+// Near the source a brick's blocks of pixels grow with the distances and
+// sizes of its cells; where its footprint exceeds the table, whole parts are
+// visited for the few of a wavefront's cells that lie in them.  Measured over
+// 170 geometries, the source 1.15 to 10 radii of the grid from the axis: the
+// choice is the slower one by more than 7% in two of them (float, 18% at most)
+// and in four (double, 33%), and against the kernel before k_cells, which
+// tested candidate samples, none loses more than 2%.  Transposes by that
+// kernel / k_cells / this choice (us; float, double): 40 x 40 x 20 beside the
+// source 267 / 422 / 103, 266 / 647 / 119; 160 x 160 x 80 beside it 1776 /
+// 14963 / 1031, 2034 / 23747 / 1336; 64^3 at 1.3 radii 401 / 2007 / 226, 483 /
+// 3799 / 306, at 3 radii 150 / 92 / 99, 194 / 175 / 137; 64 x 64 x 20 with
+// pixels of a fifteenth of a voxel 2199 / 1858 / 1092, 2348 / 2672 / 1268.
+void choose_cells(cbct_plan &p) {
+    const cbct_geom &g = p.g;
+    const Cut c = cut_of(g);
+    const int n[4] = {(int)c.bricks.x, (int)c.bricks.y, (int)c.bricks.z, g.n_views};
+    const int most[4] = {5, 5, 3, 4};
+    int m[4], total = 1;
+    for (int a = 0; a < 4; ++a) total *= m[a] = std::min(n[a], most[a]);
+    const double column = by_columns(g) ? 0.75 : 1.0;  // a visit by columns
+    double visits = 0.0, staged = 0.0, own = 0.0, views = 0.0;
+    for (int q = 0; q < total; ++q) {
+        int at[4];
+        for (int a = 0, e = q; a < 4; e /= m[a++])
+            at[a] = (int)((2LL * (e % m[a]) + 1) * n[a] / (2 * m[a]));
+        const int c0[3] = {at[0] * c.shape.x - 1, at[1] * c.shape.y - 1, at[2] - 1};
+        const int c1[3] = {std::min(c0[0] + c.shape.x, g.nx), std::min(c0[1] + c.shape.y, g.ny),
+                           c0[2] + 1};
+        const ViewConst &vc = p.h_views[at[3]];
+        const BrickView b = brick_view(vc, p.det, g.hx, g.hy, g.hz, g.nu, g.nv, c0, c1);
+        if (b.w == 0) continue;
+        double rows = std::min(b.H, b.h);
+        if ((long long)b.w * b.h > TABLE)  // those of a wavefront's cells, rounded out to parts
+            rows = std::min(rows + 7.0 * (fabs(b.bx) + fabs(b.by)) + std::max(TABLE / b.w, 1),
+                            (double)b.h);
+        visits += std::min(b.W, b.w) * rows;
+        staged += (double)b.w * b.h / 256.0;
+        // the extents of a cell at the brick's centre
+        const double x = 0.5 * (c0[0] + c1[0]), y = 0.5 * (c0[1] + c1[1]);
+        const double z = fabs(c0[2] + 0.5 - vc.Qd[2]);
+        const double r = 1.0 / (vc.ew[0] * x + vc.ew[1] * y + vc.ew[2]);
+        const double u = (vc.en[0] * x + vc.en[1] * y + vc.en[2]) * r;
+        const double W =
+            (fabs(vc.en[0] - u * vc.ew[0]) + fabs(vc.en[1] - u * vc.ew[1])) * r * g.sdd / g.au;
+        const double H =
+            (1.0 + z * (fabs(vc.ew[0]) + fabs(vc.ew[1])) * r) * g.hz * r * g.sdd / g.av;
+        own += (W + 1.0) * (H + 1.0);
+        views += 1.0;
+    }
+    p.near32 = column * visits + staged > 1.35 * (own + views);
+    p.near64 = visits + 3.0 * staged + 4.0 * views > 1.75 * own;
+}
+
 template <typename T>
 hipError_t launch_backproject_cells(const cbct_plan &p, const T *r, void *cells,
                                     const void *geom, hipStream_t s) {
@@ -1031,9 +1212,14 @@ hipError_t launch_backproject_cells(const cbct_plan &p, const T *r, void *cells,
     const dim3 grid(c.bricks.x * c.bricks.y * c.bricks.z, c.chunks);
     const PixelRay *rays = (const PixelRay *)base;
     const BrickView *bv = (const BrickView *)(base + geom_layout(p.g, c).bricks);
-    hipLaunchKernelGGL((by_columns(p.g) ? k_cells<T, true> : k_cells<T, false>), grid, dim3(256), 0,
-                       s, p.d_views, p.grid, c.shape, p.g.nu, p.g.nv, p.g.n_views, c.chunk, rays,
-                       bv, r, (T *)cells, (T)p.g.step);
+    if (sizeof(T) == 4 ? p.near32 : p.near64)
+        hipLaunchKernelGGL(k_cells_near<T>, grid, dim3(256), 0, s, p.d_views, p.det, p.grid,
+                           c.shape, p.g.nu, p.g.nv, p.g.n_views, c.chunk, rays, r, (T *)cells,
+                           (T)p.g.step);
+    else
+        hipLaunchKernelGGL((by_columns(p.g) ? k_cells<T, true> : k_cells<T, false>), grid,
+                           dim3(256), 0, s, p.d_views, p.grid, c.shape, p.g.nu, p.g.nv,
+                           p.g.n_views, c.chunk, rays, bv, r, (T *)cells, (T)p.g.step);
     return hipGetLastError();
 }
 

@@ -73,6 +73,9 @@ struct cbct_plan {
     cbct::DetConst det;
     cbct::GridConst grid;
     int64_t samples = 0;
+    // whether the transpose's cells take their own rays (see choose_cells), in
+    // float and in double
+    bool near32 = false, near64 = false;
     int device = 0;
     mutable std::mutex lam_mu;
     mutable std::vector<std::pair<int, double>> lam_cache;
@@ -115,6 +118,7 @@ size_t bp_cells_bytes(const cbct_geom &g, size_t elem_size);
 size_t bp_geom_bytes(const cbct_geom &g);
 size_t bp_workspace_bytes(const cbct_geom &g, size_t elem_size);
 void *bp_geom_in(void *ws, const cbct_geom &g, size_t elem_size);
+void choose_cells(cbct_plan &p);
 hipError_t launch_bp_prepare(const cbct_plan &p, void *geom, hipStream_t s);
 template <typename T>
 hipError_t launch_backproject_cells(const cbct_plan &p, const T *r, void *cells,
