@@ -6,8 +6,12 @@
 // The update at v needs p = Dz/|Dz|_eps at v and at v - e_a.  One step a
 // launch moves 12 bytes per voxel (z and g in, z out) and on small grids
 // costs a launch's latency; k_tv_steps makes up to three steps of a box a
-// launch, in registers and LDS.  Rows too long for its offsets take
-// k_tv_sweep, one step a launch.
+// launch, in registers and LDS.  Grids of few planes or rows, which fill little
+// of a box, and rows too long for its offsets take one step a launch:
+// k_tv_sweep4 where rows are a multiple of four voxels and the arrays 16-byte
+// aligned, else k_tv_sweep.
+#include <algorithm>
+
 #include "cbct_internal.hpp"
 
 namespace cbct {
@@ -28,7 +32,7 @@ constexpr int SWEEP_MIN_GROUPS = 2048;
 // three 40 / 10.5 / 6.1 / 2.3; a grid of 500 000 voxels takes 3.2 either way,
 // one of a million 4.2 with two and 3.9 with three.
 constexpr int BOX_X = 32, BOX_Y = 16, BOX_Z1 = 10, BOX_Z = 12;
-constexpr int TV_MAX_NX = 1 << 24;         // rows beyond it take k_tv_sweep
+constexpr int TV_MAX_NX = 1 << 24;         // longer rows are swept
 constexpr long long TV_LARGE = 1500000;    // voxels from which two steps a launch beat three
 
 struct TvArgs {
@@ -61,9 +65,8 @@ __device__ __forceinline__ SweepTile sweep_tile(const TvArgs &a, int b) {
     return t;
 }
 
-// One projected gradient step on a 32 x 8 tile marching a chunk of planes
-// (grids of any row length, 64-bit addresses).  Plane k + 2 is fetched into
-// registers while plane k is processed.
+// One projected gradient step on a 32 x 8 tile marching a chunk of planes.
+// Plane k + 2 is fetched into registers while plane k is processed.
 __global__ __launch_bounds__(256) void k_tv_sweep(TvArgs a, const float *__restrict__ z,
                                                   const float *__restrict__ g,
                                                   float *__restrict__ out, float beta, float step,
@@ -152,6 +155,153 @@ __global__ __launch_bounds__(256) void k_tv_sweep(TvArgs a, const float *__restr
             if (nonneg) zn = fmaxf(zn, 0.0f);
             out[v] = zn;
             pz_prev = pz;
+        }
+    }
+}
+
+// The same step with 16-byte accesses: one wavefront per 32 x 8 tile, each
+// lane owning four consecutive x voxels of one row (nx a multiple of 4,
+// arrays 16-byte aligned).  z planes are staged in LDS with float4 loads
+// (plus the two x-halo columns), g is read and the result written as
+// float4, and the barriers are those of a single wavefront.  The
+// arithmetic per voxel is that of k_tv_sweep, in the same order.
+constexpr int W_X = 32, W_Y = 8;  // tile
+constexpr int W_PITCH = 40;       // LDS row: column 3 is x = i0 - 1, 4..35 the tile, 36 x = i0 + 32
+
+__global__ __launch_bounds__(64) void k_tv_sweep4(TvArgs a, const float *__restrict__ z,
+                                                  const float *__restrict__ g,
+                                                  float *__restrict__ out, float beta, float step,
+                                                  int nonneg) {
+    // z planes k and k+1: rows y = j0 - 1 .. j0 + 8
+    __shared__ __attribute__((aligned(16))) float zs[2][W_Y + 2][W_PITCH];
+    // p_x and p_y of plane k: rows y = j0 - 1 .. j0 + 7, columns as zs
+    __shared__ __attribute__((aligned(16))) float ps[2][W_Y + 1][W_PITCH];
+    const int lane = threadIdx.x;
+    const int tx = lane & 7, ty = lane >> 3;
+    const SweepTile st = sweep_tile(a, blockIdx.x);
+    const int i0 = st.i0, j0 = st.j0, k0 = st.k0, k1 = st.k1;
+    const int i = i0 + 4 * tx, j = j0 + ty;  // this lane's first voxel
+    const bool own = i < a.nx && j < a.ny;   // all four, since 4 | nx
+    const long long sy = a.nx, sz = (long long)a.nx * a.ny;
+
+    // staging work of this lane: interior float4 (row r1 = ty, and for
+    // lanes 0..15 also row 8 + lane / 8), or for lanes 16..35 one x-halo
+    // element (row (lane - 16) / 2, column low or high)
+    const int rB = lane < 16 ? 8 + (lane >> 3) : -1;           // second interior row
+    const int hrow = (lane >= 16 && lane < 36) ? (lane - 16) >> 1 : -1;
+    const int hcol = (lane & 1) ? 36 : 3;                        // LDS column of the halo
+    const int hx = (lane & 1) ? i0 + W_X : i0 - 1;               // its x
+    auto row_ok = [&](int r) {
+        const int y = j0 - 1 + r;
+        return r >= 0 && y >= 0 && y < a.ny;
+    };
+    const bool qA = i < a.nx && row_ok(ty);
+    const bool qB = rB >= 0 && i < a.nx && row_ok(rB);
+    const bool qH = hrow >= 0 && hx >= 0 && hx < a.nx && row_ok(hrow);
+    const long long oA = (long long)i + sy * (j0 - 1 + ty);
+    const long long oB = (long long)i + sy * (j0 - 1 + rB);
+    const long long oH = (long long)hx + sy * (j0 - 1 + hrow);
+    struct Plane {
+        float4 A, B;
+        float H;
+    };
+    auto fetch = [&](int k, Plane &pl) {
+        const bool kin = k < a.nz;
+        pl.A = (kin && qA) ? *(const float4 *)(z + oA + sz * k) : make_float4(0.f, 0.f, 0.f, 0.f);
+        pl.B = (kin && qB) ? *(const float4 *)(z + oB + sz * k) : make_float4(0.f, 0.f, 0.f, 0.f);
+        pl.H = (kin && qH) ? z[oH + sz * k] : 0.0f;
+    };
+    auto put = [&](int slot, const Plane &pl) {
+        *(float4 *)&zs[slot][ty][4 + 4 * tx] = pl.A;
+        if (rB >= 0) *(float4 *)&zs[slot][rB][4 + 4 * tx] = pl.B;
+        if (hrow >= 0) zs[slot][hrow][hcol] = pl.H;
+    };
+
+    // p_z of the plane below the chunk, for this lane's voxels
+    float pz_prev[4] = {0.f, 0.f, 0.f, 0.f};
+    if (own && k0 > 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const long long v = i + q + sy * j + sz * (k0 - 1);
+            const float zc = z[v];
+            const float gx = (i + q < a.nx - 1) ? (z[v + 1] - zc) * a.ihx : 0.0f;
+            const float gy = (j < a.ny - 1) ? (z[v + sy] - zc) * a.ihy : 0.0f;
+            const float gz = (z[v + sz] - zc) * a.ihz;  // k0 - 1 < nz - 1
+            pz_prev[q] = gz * __builtin_amdgcn_rsqf(gx * gx + gy * gy + gz * gz + a.eps2);
+        }
+    }
+    Plane nxt;
+    fetch(k0, nxt);
+    put(k0 & 1, nxt);
+    fetch(k0 + 1, nxt);
+    // the lane's extra p position: low x column (x = i0 - 1, 9 rows) for
+    // lanes 0..8, low y row (y = j0 - 1, 32 columns) for lanes 9..40
+    const int ex_r = lane < 9 ? lane : (lane < 41 ? 0 : -1);
+    const int ex_c = lane < 9 ? 3 : 4 + (lane - 9);
+    const int ex_x = i0 - 1 + (ex_c - 3), ex_y = j0 - 1 + ex_r;
+    for (int k = k0; k < k1; ++k) {
+        const int A = k & 1, B = A ^ 1;
+        put(B, nxt);                             // plane k + 1
+        if (k + 2 < k1 + 1) fetch(k + 2, nxt);  // in flight during this plane
+        const long long v = i + sy * j + sz * k;
+        const float4 gv = own ? *(const float4 *)(g + v) : make_float4(0.f, 0.f, 0.f, 0.f);
+        __syncthreads();
+        // p at the lane's own four positions (row ty + 1 of ps)
+        const int r = ty + 1, c = 4 + 4 * tx;
+        const float4 zc4 = *(const float4 *)&zs[A][r][c];
+        const float zr = zs[A][r][c + 4];
+        const float4 zu4 = *(const float4 *)&zs[A][r + 1][c];
+        const float4 zn4 = *(const float4 *)&zs[B][r][c];
+        const float zcv[4] = {zc4.x, zc4.y, zc4.z, zc4.w};
+        const float zxn[4] = {zc4.y, zc4.z, zc4.w, zr};
+        const float zyn[4] = {zu4.x, zu4.y, zu4.z, zu4.w};
+        const float zzn[4] = {zn4.x, zn4.y, zn4.z, zn4.w};
+        float px[4], py[4], pz[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float gx = (i + q < a.nx - 1) ? (zxn[q] - zcv[q]) * a.ihx : 0.0f;
+            const float gy = (j < a.ny - 1) ? (zyn[q] - zcv[q]) * a.ihy : 0.0f;
+            const float gz = (k < a.nz - 1) ? (zzn[q] - zcv[q]) * a.ihz : 0.0f;
+            const float inv = __builtin_amdgcn_rsqf(gx * gx + gy * gy + gz * gz + a.eps2);
+            px[q] = gx * inv;
+            py[q] = gy * inv;
+            pz[q] = gz * inv;
+        }
+        *(float4 *)&ps[0][r][c] = make_float4(px[0], px[1], px[2], px[3]);
+        *(float4 *)&ps[1][r][c] = make_float4(py[0], py[1], py[2], py[3]);
+        if (ex_r >= 0) {
+            // p at the low halo position (only p_x or p_y is read there)
+            const float zc = zs[A][ex_r][ex_c];
+            const float gx = (ex_x < a.nx - 1) ? (zs[A][ex_r][ex_c + 1] - zc) * a.ihx : 0.0f;
+            const float gy = (ex_y < a.ny - 1) ? (zs[A][ex_r + 1][ex_c] - zc) * a.ihy : 0.0f;
+            const float gz = (k < a.nz - 1) ? (zs[B][ex_r][ex_c] - zc) * a.ihz : 0.0f;
+            const float inv = __builtin_amdgcn_rsqf(gx * gx + gy * gy + gz * gz + a.eps2);
+            ps[0][ex_r][ex_c] = gx * inv;
+            ps[1][ex_r][ex_c] = gy * inv;
+        }
+        __syncthreads();
+        if (own) {
+            const float4 pl = *(const float4 *)&ps[0][r][c - 4];  // columns c - 4 .. c - 1
+            const float4 pu = *(const float4 *)&ps[1][r - 1][c];
+            const float pxm[4] = {pl.w, px[0], px[1], px[2]};
+            const float pym[4] = {pu.x, pu.y, pu.z, pu.w};
+            const float gvv[4] = {gv.x, gv.y, gv.z, gv.w};
+            float res[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float div = 0.0f;
+                if (i + q < a.nx - 1) div -= px[q] * a.ihx;
+                if (j < a.ny - 1) div -= py[q] * a.ihy;
+                if (k < a.nz - 1) div -= pz[q] * a.ihz;
+                if (i + q > 0) div += pxm[q] * a.ihx;
+                if (j > 0) div += pym[q] * a.ihy;
+                if (k > 0) div += pz_prev[q] * a.ihz;
+                float zn = zcv[q] - step * (div + beta * (zcv[q] - gvv[q]));
+                if (nonneg) zn = fmaxf(zn, 0.0f);
+                res[q] = zn;
+                pz_prev[q] = pz[q];
+            }
+            *(float4 *)(out + v) = make_float4(res[0], res[1], res[2], res[3]);
         }
     }
 }
@@ -332,42 +482,79 @@ dim3 tv_grid(const GridConst &gc) {
     return dim3((gc.nx + TV_BX - 1) / TV_BX, (gc.ny + TV_BY - 1) / TV_BY, gc.nz);
 }
 
+// Boxes of a launch of T steps.
 template <int T>
-hipError_t steps_launch(const TvArgs &a, const float *z, const float *g, float *out, float beta,
-                        float step, int nonneg, hipStream_t s) {
+long long box_count(const GridConst &gc) {
     constexpr int NZ = T == 1 ? BOX_Z1 : BOX_Z;
     auto boxes = [](int n, int side) { return ((long long)n + side - 2 * T - 1) / (side - 2 * T); };
-    const long long n = boxes(a.nx, BOX_X) * boxes(a.ny, BOX_Y) * boxes(a.nz, NZ);
+    return boxes(gc.nx, BOX_X) * boxes(gc.ny, BOX_Y) * boxes(gc.nz, NZ);
+}
+
+int steps_of_boxes(const GridConst &gc) {
+    return (long long)gc.nx * gc.ny * gc.nz < TV_LARGE ? 3 : 2;
+}
+
+// Whether the grid is swept, one step a launch: where rows or boxes are too many
+// for a launch of boxes, or where that takes longer than as many sweeps.  Both
+// in us, fitted to 150 grids: a launch of boxes by their number; a sweep by
+// the planes its tiles march, the voxels of the tiles (their rows and columns
+// of 8 x 32 full or not), the planes read again where chunks are short, and the
+// memory's rate beyond what the last cache holds.  Sweep / boxes, us a step:
+// 4096 x 4096 x 1 36 / 175, 2048^2 x 2 18 / 46, 1024^2 x 4 10.8 / 13.7, x 5
+// 12.6 / 13.8, x 6 14.9 / 13.9, x 8 18.5 / 14.3; 300000 x 1 x 1 7.2 / 35;
+// 512^2 x 1 3.6 / 4.9, x 3 5.5 / 5.1; 2047^2 x 1 25 / 45.
+bool swept(const GridConst &gc) {
+    const int T = steps_of_boxes(gc);
+    const long long boxes = std::max(box_count<1>(gc), T == 3 ? box_count<3>(gc) : box_count<2>(gc));
+    if (gc.nx > TV_MAX_NX || boxes * (BOX_X * BOX_Y) > 0xffffffffLL) return true;
+    const TvArgs a = args_of(gc, 1.0);
+    const double tiles = (double)((gc.nx + ST_X - 1) / ST_X) * ((gc.ny + ST_Y - 1) / ST_Y);
+    const double layer = tiles * (ST_X * ST_Y) * 1e-6, zc = std::min(a.zc, gc.nz);
+    const bool wide = gc.nx % 4 == 0;
+    const double voxels = (double)gc.nx * gc.ny * gc.nz * 1e-6;
+    double sweep = wide ? (voxels > 21.0 ? 2.9 : 1.8) * layer * gc.nz : layer * (2.9 * gc.nz + 2.3);
+    if (a.zc < gc.nz) sweep *= (zc + 1.0) / zc;
+    const long long n = T == 3 ? box_count<3>(gc) : box_count<2>(gc);
+    return T * (3.0 + 0.25 * zc + sweep) < 5.0 + (T == 3 ? 9.5e-3 : 7.3e-3) * n;
+}
+
+template <int T>
+hipError_t steps_launch(const GridConst &gc, const TvArgs &a, const float *z, const float *g, float *out, float beta,
+                        float step, int nonneg, hipStream_t s) {
+    constexpr int NZ = T == 1 ? BOX_Z1 : BOX_Z;
     const auto kernel = nonneg ? k_tv_steps<BOX_X, BOX_Y, NZ, T, true>
                                : k_tv_steps<BOX_X, BOX_Y, NZ, T, false>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(BOX_X * BOX_Y), 0, s, a, z, g, out, beta,
-                       step);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)box_count<T>(gc)), dim3(BOX_X * BOX_Y), 0, s, a, z,
+                       g, out, beta, step);
     return hipGetLastError();
 }
 
 }  // namespace
 
-int tv_steps_per_launch(const GridConst &gc) {
-    if (gc.nx > TV_MAX_NX) return 1;
-    return (long long)gc.nx * gc.ny * gc.nz < TV_LARGE ? 3 : 2;
-}
+int tv_steps_per_launch(const GridConst &gc) { return swept(gc) ? 1 : steps_of_boxes(gc); }
 
 hipError_t launch_tv_steps(const GridConst &gc, const float *z, const float *g, float *out,
                            float beta, float eps, float step, int nonneg, int steps,
                            hipStream_t s) {
     const TvArgs a = args_of(gc, eps);
-    if (gc.nx > TV_MAX_NX) {
+    if (swept(gc)) {
         if (steps != 1) return hipErrorInvalidValue;
         const int grid = ((gc.nx + ST_X - 1) / ST_X) * ((gc.ny + ST_Y - 1) / ST_Y) *
                          ((gc.nz + a.zc - 1) / a.zc);
-        hipLaunchKernelGGL(k_tv_sweep, dim3(grid), dim3(256), 0, s, a, z, g, out, beta, step,
-                           nonneg);
+        static_assert(W_X == ST_X && W_Y == ST_Y, "both sweeps use the same tiles");
+        const bool wide = gc.nx % 4 == 0 && !(((uintptr_t)z | (uintptr_t)g | (uintptr_t)out) & 15);
+        if (wide)
+            hipLaunchKernelGGL(k_tv_sweep4, dim3(grid), dim3(64), 0, s, a, z, g, out, beta, step,
+                               nonneg);
+        else
+            hipLaunchKernelGGL(k_tv_sweep, dim3(grid), dim3(256), 0, s, a, z, g, out, beta, step,
+                               nonneg);
         return hipGetLastError();
     }
     switch (steps) {
-        case 1: return steps_launch<1>(a, z, g, out, beta, step, nonneg, s);
-        case 2: return steps_launch<2>(a, z, g, out, beta, step, nonneg, s);
-        case 3: return steps_launch<3>(a, z, g, out, beta, step, nonneg, s);
+        case 1: return steps_launch<1>(gc, a, z, g, out, beta, step, nonneg, s);
+        case 2: return steps_launch<2>(gc, a, z, g, out, beta, step, nonneg, s);
+        case 3: return steps_launch<3>(gc, a, z, g, out, beta, step, nonneg, s);
         default: return hipErrorInvalidValue;
     }
 }
