@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) void k_tv_sweep(TvArgs a, const float *__restr
     // plane elements of this lane: t = tid and t = tid + 256 of the
     // (ST_Y + 2) x (ST_X + 2) halo tile
     constexpr int NP = (ST_Y + 2) * (ST_X + 2);
-    int off[2];
+    long long off[2];
     bool inb[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void k_tv_sweep(TvArgs a, const float *__restr
         const int jj = t / (ST_X + 2), ii = t % (ST_X + 2);
         const int gi = i0 - 1 + ii, gj = j0 - 1 + jj;
         inb[e] = t < NP && gi >= 0 && gi < a.nx && gj >= 0 && gj < a.ny;
-        off[e] = inb[e] ? gi + a.nx * gj : 0;
+        off[e] = inb[e] ? gi + sy * gj : 0;
     }
     auto fetch = [&](int k, float r[2]) {
 #pragma unroll
@@ -500,9 +500,9 @@ int steps_of_boxes(const GridConst &gc) {
 // the planes its tiles march, the voxels of the tiles (their rows and columns
 // of 8 x 32 full or not), the planes read again where chunks are short, and the
 // memory's rate beyond what the last cache holds.  Sweep / boxes, us a step:
-// 4096 x 4096 x 1 36 / 175, 2048^2 x 2 18 / 46, 1024^2 x 4 10.8 / 13.7, x 5
-// 12.6 / 13.8, x 6 14.9 / 13.9, x 8 18.5 / 14.3; 300000 x 1 x 1 7.2 / 35;
-// 512^2 x 1 3.6 / 4.9, x 3 5.5 / 5.1; 2047^2 x 1 25 / 45.
+// 4096 x 4096 x 1 36 / 175, 2048^2 x 2 18 / 46, 1024^2 x 4 10.9 / 13.9, x 5
+// 12.8 / 13.9, x 6 14.6 / 14.0, x 8 18.7 / 14.2; 300000 x 1 x 1 7.5 / 35;
+// 512^2 x 1 3.5 / 5.0, x 3 5.5 / 5.1; 2047^2 x 1 26 / 46.
 bool swept(const GridConst &gc) {
     const int T = steps_of_boxes(gc);
     const long long boxes = std::max(box_count<1>(gc), T == 3 ? box_count<3>(gc) : box_count<2>(gc));

@@ -64,3 +64,58 @@ def test_a_single_plane_takes_a_few_copies_time():
 
     t = ms(copies)
     assert ms(lambda: cb.tv_prox(z, out, H, 600.0, 1e-3, n, out=out)) <= 5 * t
+
+
+def _steps64(g, z, k, cut):
+    """k steps in float64 of a box cut out of a grid; cut[a] = (low, high): whether
+    that side of axis a is a cut, k voxels from which the values are not the
+    grid's own."""
+    import torch
+    eps, beta = 1e-3, 600.0
+    step = 1.0 / (beta + 4.0 * float(np.sum(H ** -2)) / eps)
+    g, z = g.double(), z.double()
+    for _ in range(k):
+        p = []
+        for a, h in ((2, H[0]), (1, H[1]), (0, H[2])):
+            d = torch.zeros_like(z)
+            m = z.shape[a] - 1
+            d.narrow(a, 0, m).copy_((z.narrow(a, 1, m) - z.narrow(a, 0, m)) / h)
+            p.append(d)
+        norm = torch.sqrt(p[0] ** 2 + p[1] ** 2 + p[2] ** 2 + eps * eps)
+        grad = beta * (z - g)
+        for (a, h), d in zip(((2, H[0]), (1, H[1]), (0, H[2])), p):
+            d = d / norm / h
+            m = z.shape[a] - 1
+            grad = grad - d
+            grad.narrow(a, 1, m).add_(d.narrow(a, 0, m))
+        z = (z - step * grad).clamp(min=0.0)
+    for a, (low, high) in enumerate(cut):
+        z = z.narrow(a, k * low, z.shape[a] - k * (low + high))
+    return z
+
+
+@pytest.mark.parametrize("shape,boxes", [
+    # rows beyond the boxes' offsets, planes in two chunks
+    ((17, 2, 2 ** 24 + 5), [((12, 17), (0, 2), (0, 300)), ((0, 17), (0, 2), (2 ** 24 - 200, 2 ** 24 + 5))]),
+    # and rows that begin beyond 2^31 voxels
+    ((1, 129, 2 ** 24 + 1), [((0, 1), (118, 129), (0, 300)),
+                             ((0, 1), (118, 129), (2 ** 24 - 200, 2 ** 24 + 1))]),
+])
+def test_long_rows(shape, boxes):
+    """Boxes cut out of the volume at its sides, in float64."""
+    torch = require_gpu()
+    import paper_1002_3675_amd as cb
+    torch.manual_seed(62)
+    g, z = (torch.rand(shape, device="cuda").mul_(0.02) for _ in range(2))
+    k = 3
+
+    def cut(x, box):
+        return x[tuple(slice(*s) for s in box)]
+
+    want = [_steps64(cut(g, b), cut(z, b), k,
+                     [(s[0] > 0, s[1] < n) for s, n in zip(b, shape)]) for b in boxes]
+    print("tv sweep of long rows %s" % (shape,), flush=True)
+    cb.tv_prox(g, z, H, 600.0, 1e-3, k, out=z)
+    for b, w in zip(boxes, want):
+        inner = tuple(slice(s[0] + k * (s[0] > 0), s[1] - k * (s[1] < n)) for s, n in zip(b, shape))
+        assert rel_l2(to_np(z[inner]), to_np(w)) <= 20 * k * 2.0 ** -24
