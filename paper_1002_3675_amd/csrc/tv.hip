@@ -10,6 +10,8 @@
 // of a box, and rows too long for its offsets take one step a launch:
 // k_tv_sweep4 where rows are a multiple of four voxels and the arrays 16-byte
 // aligned, else k_tv_sweep.
+#include <float.h>
+
 #include <algorithm>
 
 #include "cbct_internal.hpp"
@@ -324,7 +326,9 @@ __device__ __forceinline__ float from_prev(float v) {
 // of a row by DPP, so a step has two barriers for all of its planes.
 //
 // At the grid's sides D_a = 0 follows from a zero 1/h (mx, my, mz); voxels
-// outside the grid read as zero and stay zero.
+// outside the grid read as zero and stay zero while their neighbours are
+// finite.  eps^2 is a normal number, so that p is zero at them and not zero
+// times the infinite reciprocal root of zero.
 //
 // What bounds it at 512 x 512 x 70 and two steps: about 500 VALU instructions
 // a lane for 16 voxel-steps, two thirds of the lanes' work kept (28 x 12 of
@@ -519,9 +523,10 @@ bool swept(const GridConst &gc) {
 }
 
 template <int T>
-hipError_t steps_launch(const GridConst &gc, const TvArgs &a, const float *z, const float *g, float *out, float beta,
+hipError_t steps_launch(const GridConst &gc, TvArgs a, const float *z, const float *g, float *out, float beta,
                         float step, int nonneg, hipStream_t s) {
     constexpr int NZ = T == 1 ? BOX_Z1 : BOX_Z;
+    a.eps2 = std::max(a.eps2, FLT_MIN);
     const auto kernel = nonneg ? k_tv_steps<BOX_X, BOX_Y, NZ, T, true>
                                : k_tv_steps<BOX_X, BOX_Y, NZ, T, false>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)box_count<T>(gc)), dim3(BOX_X * BOX_Y), 0, s, a, z,
