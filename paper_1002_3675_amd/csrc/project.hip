@@ -168,11 +168,12 @@ __device__ __forceinline__ double march_double(const double Q[3], const double D
 // float (exact below 2^24); two samples per loop step, summed in order.
 // RXC > 0 fixes the row pitch at compile time.  The LDS address is formed in
 // subnormal floats, whose bits are the integer itself: every product and sum
-// below is a multiple of 4 * 2^-149 smaller than 2^26 of these, so exact, and
-// no zero among them is negative (base is +0 or not zero).  Multiply-adds
-// cost two thirds of what the conversion and the integer adds of the same
-// sum cost: 31 -> 29 vector instructions a sample.
-template <int RXC>
+// below is a multiple of 4 * 2^-149 smaller than 2^26 * 2^-149 (see
+// small_offsets), so exact, and no zero among them is negative (base is +0 or
+// not zero).  Multiply-adds cost two thirds of what the conversion and the
+// integer adds of the same sum cost: 31 -> 29 vector instructions a sample.
+// With WIDE it is formed in integers, whatever the size of the terms.
+template <int RXC, bool WIDE = false>
 __device__ __forceinline__ float staged_samples(float seg, int base, int RXr, int RXY, float m,
                                                 float mb, const float Df[3], const float of[3]) {
     typedef const __attribute__((address_space(3))) float *lds_t;
@@ -188,10 +189,19 @@ __device__ __forceinline__ float staged_samples(float seg, int base, int RXr, in
         const float fx = __builtin_floorf(lx), fy = __builtin_floorf(ly),
                     fz = __builtin_floorf(lz);
         const float wx = lx - fx, wy = ly - fy, wz = lz - fz;
-        const float at = __builtin_fmaf(
-            fz, RXYf, __builtin_fmaf(fy, RXf, __builtin_fmaf(fx, Xf, basef)));
-        const lds_t p = (lds_t)(size_t)__builtin_bit_cast(unsigned, at);
-        const lds_t q = (lds_t)(size_t)__builtin_bit_cast(unsigned, at + RXYf);
+        unsigned pa, qa;
+        if constexpr (WIDE) {
+            pa = (unsigned)base + 4u * ((unsigned)(int)fz * (unsigned)RXY +
+                                        (unsigned)(int)fy * (unsigned)RX + (unsigned)(int)fx);
+            qa = pa + 4u * (unsigned)RXY;
+        } else {
+            const float at = __builtin_fmaf(
+                fz, RXYf, __builtin_fmaf(fy, RXf, __builtin_fmaf(fx, Xf, basef)));
+            pa = __builtin_bit_cast(unsigned, at);
+            qa = __builtin_bit_cast(unsigned, at + RXYf);
+        }
+        const lds_t p = (lds_t)(size_t)pa;
+        const lds_t q = (lds_t)(size_t)qa;
         const float c00 = p[0] + wx * (p[1] - p[0]);
         const float c10 = p[RX] + wx * (p[RX + 1] - p[RX]);
         const float c01 = q[0] + wx * (q[1] - q[0]);
@@ -378,7 +388,7 @@ __device__ __forceinline__ void half_range(double Qz, double a, double b, double
 // CU).  Seven or eight with smaller boxes leave chunks that do not fit
 // (256 x 256 x 64: 1.04 -> 1.47 and 2.56 ms); five with larger ones are slower
 // at the head size (5.35 -> 5.46 ms) and no faster elsewhere.
-template <bool HALVES>
+template <bool HALVES, bool WIDE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_project_tile(
     const ViewConst *__restrict__ views, DetConst dc, GridConst gc, int nu, int nv,
     const float *__restrict__ fp, int fp_elems, const float *__restrict__ Y,
@@ -590,7 +600,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
                 const float ma = (float)(na - s), mb = (float)(nb - s);
                 // common row pitches as constants: the row offsets then sit in
                 // the LDS instructions' immediates
-                switch (RXP) {
+                switch (WIDE ? 0 : RXP) {
 #define CBCT_PITCH(n)                                                                   \
     case n:                                                                             \
         seg = staged_samples<n>(seg, base, RXP, RXY, ma, mb, Df, o.f);                   \
@@ -601,7 +611,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
                     CBCT_PITCH(35) CBCT_PITCH(37) CBCT_PITCH(39) CBCT_PITCH(41)
 #undef CBCT_PITCH
                     default:
-                        seg = staged_samples<0>(seg, base, RXP, RXY, ma, mb, Df, o.f);
+                        seg = staged_samples<0, WIDE>(seg, base, RXP, RXY, ma, mb, Df, o.f);
                 }
             } else if (mine) {
                 const int base = (o.I[2] + 1) * pxy + (o.I[1] + 1) * px + (o.I[0] + 1);
@@ -750,6 +760,20 @@ bool in_halves(const cbct_geom &g) {
            tile_count(g) >= 512;
 }
 
+// Whether the terms of a staged sample's LDS address, in bytes, stay below 2^26
+// (staged_samples).  A sample is at most SEG increments and a cell from its
+// segment's origin; a box is two cells or more in y and z, so its planes are
+// at most TILE_VOL / 2 floats apart and its rows TILE_LDS / 4.  A ray's
+// increment is at most the step over the spacing, in z times the steepest
+// ray's slope.  Steps of less than ten spacings always are small enough.
+bool small_offsets(const cbct_geom &g) {
+    const double v = 0.5 * (g.nv - 1) * g.av + fabs(g.v_off);
+    auto cells = [](double d) { return SEG * d + 2.0; };
+    const double sum = 0.5 * TILE_VOL * cells(g.step / g.hz * v / hypot(g.sdd, v)) +
+                       0.25 * TILE_LDS * cells(g.step / g.hy) + cells(g.step / g.hx) + TILE_VOL;
+    return 4.0 * sum < 67108864.0;
+}
+
 // One-dimensional grid of all tiles of all views (see xcd_tile).
 dim3 tile_grid(const cbct_plan &p) { return dim3((unsigned)tile_count(p.g)); }
 
@@ -803,8 +827,10 @@ hipError_t launch_project(const cbct_plan &p, const T *fpad, const T *Y, T *out,
                           double *partials, hipStream_t s) {
     const long long elems = (long long)padded_count(p);
     if constexpr (sizeof(T) == 4) {
-        hipLaunchKernelGGL((in_halves(p.g) ? k_project_tile<true> : k_project_tile<false>),
-                           tile_grid(p), dim3(256), 0, s, p.d_views, p.det, p.grid, p.g.nu,
+        const auto kernel = !small_offsets(p.g) ? k_project_tile<false, true>
+                            : in_halves(p.g)    ? k_project_tile<true, false>
+                                                : k_project_tile<false, false>;
+        hipLaunchKernelGGL(kernel, tile_grid(p), dim3(256), 0, s, p.d_views, p.det, p.grid, p.g.nu,
                            p.g.nv, fpad, (int)elems, Y, out, partials, (float)p.g.step,
                            tile_margin(p.g));
     } else {
