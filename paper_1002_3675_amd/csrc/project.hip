@@ -741,23 +741,33 @@ size_t tile_count(const cbct_geom &g) {
 }
 
 // Whether pieces that exceed the LDS box are staged in halves of the tile
-// (k_project_tile<true>), eight rows of pixels each in turn: where the box of a
-// piece at the axis, its rays oblique or along x or y, a cell and a half
-// added on each side, exceeds it, and the tiles are two a CU or more.  (us,
-// all taps of such a piece from memory / in halves) 128^3 with pixels of a
-// voxel, 40 views 1379 / 358, 160^3 with planes of half a voxel, 30 views
-// 2925 / 856, 208 x 205 x 76, 7 views 514 / 269, 80 x 69 x 96, 10 views
-// 124 / 100; 330 tiles 80 / 88.  Where pieces fit, the code for the halves
-// costs 2 to 8%.  Sums and results are the same bit for bit either way.
+// (k_project_tile<true, false>), eight rows of pixels each in turn: where the
+// box of a piece at the axis, its rays oblique or along x or y, a cell and a
+// half added on each side, exceeds it, and half a tile's box, which is then
+// smaller than so estimated, does not by much (with long steps, by less).  The
+// tiles have to be two a CU or more; volumes of under 400000 voxels, whose
+// taps the L2 holds, also need 900 tiles and a box well beyond LDS.  (us, all taps of such a piece from memory /
+// in halves) 128^3 with pixels of a voxel, 40 views 1379 / 358; 160^3 with
+// planes of half a voxel, 30 views 2925 / 856; half a box 0.67 of LDS 261 /
+// 226, 0.83 440 / 283, 1.04 420 / 303, 1.5 437 / 351, 1.7 421 / 359, 1.9 254 /
+// 219, 2.0 178 / 190, above 2.4 the same or 5% worse; 100 x 100 x 50 with steps
+// of two voxels (1.73) 70 / 75; 72 x 72 x 29, 1008 tiles, box 1.05 of LDS 68 /
+// 86; 69 x 69 x 25, 636 tiles, 1.9 62 / 85; 330 tiles 80 / 88.  Where pieces
+// fit, the code for the halves costs 2 to 8%.  Sums and results are the same
+// bit for bit either way.
 bool in_halves(const cbct_geom &g) {
     const double m = g.sad / g.sdd, u = TILE_U * g.au * m, l = TILE_SUB * g.step;
-    const double z = std::min(TILE_V * g.av * m / g.hz + 3.5, g.nz + 2.0);
+    const double v = TILE_V * g.av * m / g.hz, planes = g.nz + 2.0;
     const double d = 0.7071 * (u + l), nx = g.nx + 2.0, ny = g.ny + 2.0;
     auto area = [&](double x, double y) {
         return std::min(x / g.hx + 3.5, nx) * std::min(y / g.hy + 3.5, ny);
     };
-    return z * std::max(area(d, d), std::max(area(l, u), area(u, l))) > TILE_LDS &&
-           tile_count(g) >= 512;
+    const double most = std::max(area(d, d), std::max(area(l, u), area(u, l))) / TILE_LDS;
+    const double box = std::min(v + 3.5, planes) * most;
+    const double half = std::min(0.5 * v + 3.5, planes) * most;
+    const bool long_steps = g.step > 0.75 * std::min(g.hx, std::min(g.hy, g.hz));
+    if (!(box > 1.0 && half <= (long_steps ? 1.6 : 1.95)) || tile_count(g) < 512) return false;
+    return (double)g.nx * g.ny * g.nz >= 4e5 || (box > 1.3 && tile_count(g) >= 900);
 }
 
 // Whether the terms of a staged sample's LDS address, in bytes, stay below 2^26
