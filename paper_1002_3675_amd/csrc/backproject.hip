@@ -889,19 +889,20 @@ __global__ __launch_bounds__(256) void k_gather(GridConst gc, int chunks,
 //
 // Everything of a view but the row coordinate and l is the same along a
 // column.  Where all the wavefront's imager points have their four taps on
-// the detector, their tests go too, and the row coordinate's whole part and
-// fraction are read from the bits of a double: 2^-32 of a row, where the
-// weight formed of it is rounded to 2^-25.  Bound by VALU issue, the double
-// arithmetic above all, and by the gathers: about 32 instructions a voxel
+// the detector, their tests go too.  Bound by VALU issue, the double
+// arithmetic above all, and by the gathers: about 33 instructions a voxel
 // and view with four voxels a lane, 26 / 4 of them for the view, and two
 // loads.  Head (512 x 512 x 70, 40 views) 1640 us with one voxel a lane and
-// tested taps, 825 with four and conversions of the row, 765 without, 726
-// with six and what all lanes share in scalar registers (96 vector registers;
-// eight voxels take 116 and 752 us).
+// tested taps, 825 with four, 780 with six and what all lanes share in scalar
+// registers (96 vector registers; eight voxels take 116 and 4% longer).  The
+// row's fraction read from the low word of a double 2^20 above it took 724,
+// but is then cut at 2^-32 of a row: further from the exact values than before
+// in 22 of 40 geometries, by up to 0.2% of their error.
 constexpr int Q_BX = 64, Q_BY = 4;
 
-// sqrt(x) for x > 0: the hardware's reciprocal root and a correction, within
-// an ulp of the correctly rounded value.
+// sqrt(x) for x > 0: the hardware's reciprocal root and a correction, which
+// gives the correctly rounded value (checked for every mantissa of both
+// parities of the exponent, at five exponents).
 __device__ __forceinline__ float sqrt_pos(float x) {
     const float r = __builtin_amdgcn_rsqf(x);
     const float y = x * r;
@@ -962,23 +963,17 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
         const double lxy2 = __builtin_fma(n, n, d * d);
         auto weight = [&](int q) { return w0 * (double)sqrt_pos((float)(wz2[q] + lxy2)); };
         const float *rt = r + (long long)t * nu * nv;
-        // rows less than 1e-6 below the last are left out: 2^20 + fj may round up to it
         const bool inside = narrow && fi >= 0.0 && fi < nu - 1.0 && fmin(fj0, fj1) >= 0.0 &&
-                            fmax(fj0, fj1) < nv - 1.0 - 1e-6;
+                            fmax(fj0, fj1) < nv - 1.0;
         if (!__builtin_amdgcn_ballot_w64(!inside)) {
             const float *rt1 = rt + nu;
-            // 2^20 + fj has fj's whole part in the low 20 bits of its upper
-            // word (0x41300000 above them) and 32 bits of its fraction in the
-            // lower: they need no conversions
             const unsigned nu4 = 4u * (unsigned)nu;
-            const unsigned i4 = 4u * (unsigned)(int)i0d - 0x300000u * nu4;
-            const double fjm = fj0 + 1048576.0;
+            const unsigned i4 = 4u * (unsigned)(int)i0d;
 #pragma unroll
             for (int q = 0; q < ZC; ++q) {
-                const unsigned long long x =
-                    __builtin_bit_cast(unsigned long long, __builtin_fma((double)q, dj, fjm));
-                const unsigned o = __umul24((unsigned)(x >> 32), nu4) + i4;
-                const float b = (float)(unsigned)x * 0x1p-32f;
+                const double fj = __builtin_fma((double)q, dj, fj0);
+                const unsigned o = __umul24((unsigned)(int)fj, nu4) + i4;
+                const float b = (float)__builtin_amdgcn_fract(fj);
                 const float *p = (const float *)((const char *)rt + o);
                 const float *p1 = (const float *)((const char *)rt1 + o);
                 const float v0 = p[0] + a * (p[1] - p[0]), v1 = p1[0] + a * (p1[1] - p1[0]);
@@ -1243,12 +1238,11 @@ hipError_t launch_eq2(const cbct_plan &p, const float *r, const float *f, double
                            out);
     };
     // Voxels a lane: more share a view's arithmetic, fewer leave more
-    // wavefronts.  Measured (before the rows' conversions went, which took 4
-    // to 7%), us with 1 / 2 / 4: 4096 wavefronts of single voxels (64^3)
-    // 15 / 16 / 23, 29k (157 x 141 x 67) 101 / 84 / 91, 33k (128^3)
+    // wavefronts.  Measured, us with 1 / 2 / 4: 4096 wavefronts of single voxels
+    // (64^3) 15 / 16 / 23, 29k (157 x 141 x 67) 101 / 84 / 91, 33k (128^3)
     // 195 / 156 / 161, 66k (256 x 256 x 64) 407 / 309 / 289, 287k (head)
-    // 1293 / 891 / 825; and since, with 4 / 6: 66k 270 / 288, 160k 209 / 214,
-    // 246k 315 / 306, 287k 757 / 726.
+    // 1293 / 891 / 825; with 4 / 6: 66k 270 / 288, 160k 209 / 214, 246k 315 /
+    // 306, 287k 757 / 726.
     const long long waves = ((p.g.nx + Q_BX - 1LL) / Q_BX) * ((p.g.ny + Q_BY - 1LL) / Q_BY) * Q_BY *
                             p.g.nz;
     if (waves >= 196608)
