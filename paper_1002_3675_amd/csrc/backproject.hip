@@ -897,7 +897,10 @@ __global__ __launch_bounds__(256) void k_gather(GridConst gc, int chunks,
 // registers (96 vector registers; eight voxels take 116 and 4% longer).  The
 // row's fraction read from the low word of a double 2^20 above it took 724,
 // but is then cut at 2^-32 of a row: further from the exact values than before
-// in 22 of 40 geometries, by up to 0.2% of their error.
+// in 22 of 40 geometries, by up to 0.2% of their error.  With one voxel a
+// lane, where few wavefronts wait for a view's latencies, a view has no
+// branch and its taps no tests: 64^3 from 16 views 14.5 -> 10.1 us (14.8 with
+// the first kernel), 14 x 14 x 25 from 21 views 15.0 -> 9.5 (14.1).
 constexpr int Q_BX = 64, Q_BY = 4;
 
 // sqrt(x) for x > 0: the hardware's reciprocal root and a correction, which
@@ -915,6 +918,32 @@ __device__ __forceinline__ double uniform(double v) {
     const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
     const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
     return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+
+// What a view is to a column of voxels (i, j): the fractional pixel indices fi,
+// and fj + q dj in plane q of the column, w0 = weight / l and the square of l's
+// part in the xy plane.
+struct Eq2View {
+    double fi, fj, dj, w0, lxy2;
+};
+
+__device__ __forceinline__ Eq2View eq2_view(const ViewConst &vc, const DetConst &dc, int i, int j,
+                                            double kz, double su, double svh, double ci,
+                                            double cj) {
+    // source-to-voxel vector (mm): n along e_u, d along e_w (depth)
+    const double n = __builtin_fma((double)i, vc.en[0], __builtin_fma((double)j, vc.en[1], vc.en[2]));
+    const double d = __builtin_fma((double)i, vc.ew[0], __builtin_fma((double)j, vc.ew[1], vc.ew[2]));
+    // 1/d from the float reciprocal and one Newton step in double: the
+    // relative error squares, from ~2e-7 to ~4e-14
+    const double id0 = (double)__builtin_amdgcn_rcpf((float)d);
+    const double id = id0 * __builtin_fma(-d, id0, 2.0);
+    Eq2View v;
+    v.fi = __builtin_fma(n * id, su, ci);
+    v.dj = id * svh;
+    v.fj = __builtin_fma(kz, v.dj, cj);
+    v.w0 = dc.sdd2d * (id * id * id);
+    v.lxy2 = __builtin_fma(n, n, d * d);
+    return v;
 }
 
 template <int ZC>
@@ -943,41 +972,58 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
     }
     // 32-bit byte offsets within a view, 24-bit factors, rows below 2^20
     const bool narrow = (long long)nu * nv < (1LL << 30) && nu < (1 << 22) && nv < (1 << 20);
-    for (int t = 0; t < nviews; ++t) {
-        const ViewConst &vc = views[t];
-        // source-to-voxel vector (mm): n along e_u, d along e_w (depth)
-        const double n = __builtin_fma((double)i, vc.en[0], __builtin_fma((double)j, vc.en[1], vc.en[2]));
-        const double d = __builtin_fma((double)i, vc.ew[0], __builtin_fma((double)j, vc.ew[1], vc.ew[2]));
-        // 1/d from the float reciprocal and one Newton step in double: the
-        // relative error squares, from ~2e-7 to ~4e-14
-        const double id0 = (double)__builtin_amdgcn_rcpf((float)d);
-        const double id = id0 * __builtin_fma(-d, id0, 2.0);
-        // fractional pixel indices: fi, and fj = fj0 + q dj in plane k0 + q
-        const double fi = __builtin_fma(n * id, su, ci);
-        const double dj = id * svh;
-        const double fj0 = __builtin_fma(kz, dj, cj);
-        const double fj1 = __builtin_fma((double)(ZC - 1), dj, fj0);
-        const double i0d = __builtin_floor(fi);
-        const float a = (float)(fi - i0d);
-        const double w0 = dc.sdd2d * (id * id * id);     // weight / l
-        const double lxy2 = __builtin_fma(n, n, d * d);
-        auto weight = [&](int q) { return w0 * (double)sqrt_pos((float)(wz2[q] + lxy2)); };
+    auto weight = [&](const Eq2View &v, int q) {
+        return v.w0 * (double)sqrt_pos((float)(wz2[q] + v.lxy2));
+    };
+    int t0 = 0;
+    if (ZC == 1 && (long long)nu * nv < (1LL << 28) && nu < (1 << 21) && nv < (1 << 20)) {
+        // Few wavefronts: a view takes its chain of latencies, shorter without
+        // branches and with the next view's beside it.  A view is a buffer that
+        // reads zero beyond its ends, and so 2^31 bytes on.
+#pragma unroll 2
+        for (int t = 0; t < nviews; ++t) {
+            const Eq2View v = eq2_view(views[t], dc, i, j, kz, su, svh, ci, cj);
+            const double i0d = __builtin_floor(v.fi), j0d = __builtin_floor(v.fj);
+            const float a = (float)(v.fi - i0d), b = (float)(v.fj - j0d);
+            const int i0 = (int)fmax(fmin(i0d, (double)nu), -2.0);
+            const int j0 = (int)fmax(fmin(j0d, (double)nv), -2.0);
+            const unsigned nu4 = 4u * (unsigned)nu, o = (unsigned)__mul24(j0, 4 * nu);
+            const unsigned o0 = o + (i0 >= 0 && i0 < nu ? 4u * (unsigned)i0 : 0x80000000u);
+            const unsigned o1 =
+                o + (i0 >= -1 && i0 < nu - 1 ? 4u * (unsigned)(i0 + 1) : 0x80000000u);
+            const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(r + (long long)t * nu * nv), (short)0, 4 * nu * nv, 0x00020000);
+            auto tap = [&](unsigned at) {
+                return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rt, at, 0, 0));
+            };
+            const float r00 = tap(o0), r10 = tap(o1);
+            const float r01 = tap(o0 + nu4), r11 = tap(o1 + nu4);
+            const float v0 = r00 + a * (r10 - r00), v1 = r01 + a * (r11 - r01);
+            sum[0] = __builtin_fma(weight(v, 0), (double)(v0 + b * (v1 - v0)), sum[0]);
+        }
+        t0 = nviews;
+    }
+    for (int t = t0; t < nviews; ++t) {
+        const Eq2View v = eq2_view(views[t], dc, i, j, kz, su, svh, ci, cj);
+        const double fj1 = __builtin_fma((double)(ZC - 1), v.dj, v.fj);
+        const double i0d = __builtin_floor(v.fi);
+        const float a = (float)(v.fi - i0d);
         const float *rt = r + (long long)t * nu * nv;
-        const bool inside = narrow && fi >= 0.0 && fi < nu - 1.0 && fmin(fj0, fj1) >= 0.0 &&
-                            fmax(fj0, fj1) < nv - 1.0;
+        const bool inside = narrow && v.fi >= 0.0 && v.fi < nu - 1.0 && fmin(v.fj, fj1) >= 0.0 &&
+                            fmax(v.fj, fj1) < nv - 1.0;
         if (!__builtin_amdgcn_ballot_w64(!inside)) {
             const float *rt1 = rt + nu;
             const unsigned nu4 = 4u * (unsigned)nu;
             const unsigned i4 = 4u * (unsigned)(int)i0d;
 #pragma unroll
             for (int q = 0; q < ZC; ++q) {
-                const double fj = __builtin_fma((double)q, dj, fj0);
+                const double fj = __builtin_fma((double)q, v.dj, v.fj);
                 const unsigned o = __umul24((unsigned)(int)fj, nu4) + i4;
                 const float b = (float)__builtin_amdgcn_fract(fj);
                 const float *p = (const float *)((const char *)rt + o);
                 const float *p1 = (const float *)((const char *)rt1 + o);
                 const float v0 = p[0] + a * (p[1] - p[0]), v1 = p1[0] + a * (p1[1] - p1[0]);
-                sum[q] = __builtin_fma(weight(q), (double)(v0 + b * (v1 - v0)), sum[q]);
+                sum[q] = __builtin_fma(weight(v, q), (double)(v0 + b * (v1 - v0)), sum[q]);
             }
             continue;
         }
@@ -985,7 +1031,7 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
         const bool in0 = i0 >= 0 && i0 < nu, in1 = i0 + 1 >= 0 && i0 + 1 < nu;
 #pragma unroll
         for (int q = 0; q < ZC; ++q) {
-            const double fj = __builtin_fma((double)q, dj, fj0);
+            const double fj = __builtin_fma((double)q, v.dj, v.fj);
             const double j0d = __builtin_floor(fj);
             const float b = (float)(fj - j0d);
             const int j0 = (int)fmax(fmin(j0d, (double)nv), -2.0);
@@ -995,7 +1041,7 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
             const float r01 = (in0 && jn1) ? rt[(long long)(j0 + 1) * nu + i0] : 0.0f;
             const float r11 = (in1 && jn1) ? rt[(long long)(j0 + 1) * nu + i0 + 1] : 0.0f;
             const float v0 = r00 + a * (r10 - r00), v1 = r01 + a * (r11 - r01);
-            sum[q] = __builtin_fma(weight(q), (double)(v0 + b * (v1 - v0)), sum[q]);
+            sum[q] = __builtin_fma(weight(v, q), (double)(v0 + b * (v1 - v0)), sum[q]);
         }
     }
 #pragma unroll
@@ -1239,8 +1285,8 @@ hipError_t launch_eq2(const cbct_plan &p, const float *r, const float *f, double
     };
     // Voxels a lane: more share a view's arithmetic, fewer leave more
     // wavefronts.  Measured, us with 1 / 2 / 4: 4096 wavefronts of single voxels
-    // (64^3) 15 / 16 / 23, 29k (157 x 141 x 67) 101 / 84 / 91, 33k (128^3)
-    // 195 / 156 / 161, 66k (256 x 256 x 64) 407 / 309 / 289, 287k (head)
+    // (64^3) 10 / 16 / 23, 13k (80^3) 27 / 27, 29k (157 x 141 x 67) 91 / 76 /
+    // 91, 33k (128^3) 216 / 150 / 161, 66k (256 x 256 x 64) 407 / 309 / 289, 287k (head)
     // 1293 / 891 / 825; with 4 / 6: 66k 270 / 288, 160k 209 / 214, 246k 315 /
     // 306, 287k 757 / 726.
     const long long waves = ((p.g.nx + Q_BX - 1LL) / Q_BX) * ((p.g.ny + Q_BY - 1LL) / Q_BY) * Q_BY *

@@ -1,0 +1,75 @@
+"""Eq. (2) operator on grids of few wavefronts, whose taps are read from a view as
+a buffer without tests: voxels whose imager points lie left and right of the
+detector, above and below it, on its outermost pixels, and far off; one row or
+column of pixels.  Against the FP64 oracle; tolerance: weights and
+interpolation in a few 2^-24, sums in double, 1e-6."""
+
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+from workloads import Geometry
+
+from gpu_util import require_gpu, rel_l2, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    "all_sides": Geometry(30, 27, 25, 2.0, 2.0, 2.0, 14, 11, 2.5, 2.5, 200.0, 300.0, 7),
+    "off_the_detector": Geometry(30, 27, 25, 2.0, 2.0, 2.0, 14, 11, 2.5, 2.5, 200.0, 300.0, 7,
+                                 u_off=60.0, v_off=-45.0),
+    "one_row": Geometry(20, 21, 6, 2.0, 2.0, 2.0, 40, 1, 2.0, 9.0, 200.0, 300.0, 5),
+    "one_column": Geometry(20, 21, 6, 2.0, 2.0, 2.0, 1, 20, 30.0, 1.5, 200.0, 300.0, 5),
+    "one_pixel": Geometry(9, 9, 9, 2.0, 2.0, 2.0, 1, 1, 20.0, 20.0, 200.0, 300.0, 4),
+    # points exactly on the outermost pixel centres
+    "on_the_edges": Geometry(9, 9, 9, 2.0, 2.0, 2.0, 3, 3, 6.0, 6.0, 200.0, 400.0, 4),
+    "beside_the_source": Geometry(30, 30, 20, 2.0, 2.0, 2.0, 40, 30, 4.0, 4.0, 45.0, 90.0, 9,
+                                  angles=tuple(math.pi / 4 + 0.7 * k for k in range(9))),
+    "odd_views": Geometry(14, 14, 25, 2.0, 2.0, 2.0, 5, 23, 3.6, 3.6, 300.0, 450.0, 21),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_small_grids_match_oracle(name):
+    require_gpu()
+    import paper_1002_3675_amd as cb
+    g = CASES[name]
+    assert -(-g.nx // 64) * -(-g.ny // 4) * 4 * g.nz < 8192
+    # the first and last views' neighbours in memory are no values of theirs
+    y = np.random.default_rng(97).uniform(0.5, 4.0, g.proj_shape).astype(np.float32)
+    y[1::2] *= 1e6
+    want = oracle.eq2_backproject(g, y.astype(np.float64))
+    assert np.count_nonzero(want) > 0
+    print("eq2 small %s" % name, flush=True)
+    f = to_np(cb.Plan(g).backproject_eq2(to_dev(y)))
+    assert rel_l2(f, want) <= 1e-6, rel_l2(f, want)
+    # the even views alone
+    y[1::2] = 0.0
+    want = oracle.eq2_backproject(g, y.astype(np.float64))
+    f = to_np(cb.Plan(g).backproject_eq2(to_dev(y)))
+    assert rel_l2(f, want) <= 1e-6, rel_l2(f, want)
+
+
+def test_many_views_of_a_small_grid_take_no_branches():
+    """460 views of 11 x 18 x 76 voxels: 135 us a call, 228 with a branch a tap and
+    243 with a branch a view."""
+    torch = require_gpu()
+    import paper_1002_3675_amd as cb
+    g = Geometry(11, 18, 76, 1.0, 1.0, 1.0, 5, 140, 1.8, 1.8, 300.0, 450.0, 460)
+    plan, y = cb.Plan(g), torch.rand((460, 140, 5), device="cuda")
+    out = torch.empty(g.vol_shape, device="cuda")
+
+    def us():
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(20):
+            plan.backproject_eq2(y, out=out)
+        b.record()
+        torch.cuda.synchronize()
+        return a.elapsed_time(b) * 50
+
+    us()
+    print("460 views: %.1f us" % us(), flush=True)
+    assert us() <= 190
