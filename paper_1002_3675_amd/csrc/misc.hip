@@ -216,10 +216,12 @@ hipError_t launch_probe_fma(bool fp64, void *out, int blocks, int iters, hipStre
 // ln(ref / c) of finite positive numbers whose exponents differ by at most
 // 1000.  With ref / c = 2^e m, m in [1/sqrt 2, sqrt 2], and
 // s = (m - 1) / (m + 1), ln m = 2 atanh s = 2 s (1 + t/3 + t^2 (1/5 + t/7 +
-// ...)), t = s^2 <= 0.0295.  The bracket's polynomial is worth at most 2^-12
-// of the sum and is formed in float, the rest in double: the result is
-// within 2^-35 of the logarithm, relative, and so within half a unit of the
-// last place of a float and a thousandth of it.
+// ...)), t = s^2 <= 0.0295; terms from t^10/21 on, 2^-55 of the sum, are left
+// out.  s is a product with the hardware's reciprocal after one Newton step,
+// and one correction.  The terms t^5/11 ... t^9/19, at most 2^-28 of the sum,
+// are formed in float: with its 24 bits they err by 2^-53 of the sum, as the
+// double they are added to.  Within 5e-16 of the logarithm, relative (log()
+// of the rounded quotient errs by more where that is near one).
 __device__ __forceinline__ double log_ratio(double ref, double c) {
     double a = __builtin_amdgcn_frexp_mant(ref), b = __builtin_amdgcn_frexp_mant(c);
     int e = __builtin_amdgcn_frexp_exp(ref) - __builtin_amdgcn_frexp_exp(c);
@@ -228,15 +230,20 @@ __device__ __forceinline__ double log_ratio(double ref, double c) {
     b = lo ? 0.5 * b : b;
     e += (hi ? 1 : 0) - (lo ? 1 : 0);
     const double num = a - b, den = a + b;
-    const double r = __builtin_amdgcn_rcp(den), s0 = num * r;
+    double r = __builtin_amdgcn_rcp(den);
+    r = __builtin_fma(__builtin_fma(-den, r, 1.0), r, r);
+    const double s0 = num * r;
     const double s = __builtin_fma(__builtin_fma(-den, s0, num), r, s0);
     const double t = s * s;
     const float tf = (float)t;
-    float p = __builtin_fmaf(tf, 1.0f / 13.0f, 1.0f / 11.0f);
-    p = __builtin_fmaf(tf, p, 1.0f / 9.0f);
-    p = __builtin_fmaf(tf, p, 1.0f / 7.0f);
-    p = __builtin_fmaf(tf, p, 1.0f / 5.0f);
-    const double q = t * __builtin_fma(t, (double)p, 1.0 / 3.0), s2 = s + s;
+    float pf = __builtin_fmaf(tf, 1.0f / 19.0f, 1.0f / 17.0f);
+    pf = __builtin_fmaf(tf, pf, 1.0f / 15.0f);
+    pf = __builtin_fmaf(tf, pf, 1.0f / 13.0f);
+    pf = __builtin_fmaf(tf, pf, 1.0f / 11.0f);
+    double p = __builtin_fma(t, (double)pf, 1.0 / 9.0);
+    p = __builtin_fma(t, p, 1.0 / 7.0);
+    p = __builtin_fma(t, p, 1.0 / 5.0);
+    const double q = t * __builtin_fma(t, p, 1.0 / 3.0), s2 = s + s;
     return __builtin_fma((double)e, 0.6931471805599453, __builtin_fma(s2, q, s2));
 }
 
@@ -249,9 +256,10 @@ __device__ __forceinline__ float log_count(float count, double ref, double min_c
 
 // y = ln(ref / max(c, min_count)), ref = flat[i] or i0; double arithmetic.
 // log() and a full division, 140 vector instructions an element, bounded it;
-// log_ratio's 47 leave it near its memory traffic: 512 x 384 x 40 projections
-// 28.8 -> 16.2 us, 12 bytes an element at 5.8 TB/s.  Four elements a lane
-// where all arrays are 16-byte aligned.
+// log_ratio's 53 leave it near its memory traffic: 512 x 384 x 40 projections
+// 28.8 -> 16.7 us, 12 bytes an element at 5.65 TB/s (17.2 us with all terms in
+// double; 16.4 with those from t^2/5 on in float, within 8e-12 only).  Four
+// elements a lane where all arrays are 16-byte aligned.
 template <int V>
 __global__ __launch_bounds__(256) void k_log_counts(const float *__restrict__ counts,
                                                     const float *__restrict__ flat, double i0,
