@@ -1108,12 +1108,19 @@ bool by_columns(const cbct_geom &g) {
 // Views a workgroup of the cell pass takes.  A small grid has fewer bricks
 // than the chip has room for (about 1800 workgroups), and each works its way
 // through the views' loads and barriers alone; its views are then cut into
-// up to eight chunks of four or more, with cell sums of their own, as long
-// as no more than SPLIT_GROUPS workgroups result.  Transposes with 1 chunk,
-// with up to 3072 workgroups and with up to 6144 (us): 32^3 / 60 views
-// 115 / 50 / 50, 48^3 / 16 47 / 38 / 39, 64^3 / 16 79 / 79 / 67, 64^3 / 60
-// 197 / 197 / 164; 80^3 and 96^3 / 16 lose 3 to 9% with two chunks.
-constexpr int SPLIT_GROUPS = 6144, SPLIT_MAX = 8, SPLIT_VIEWS = 4;
+// up to eight chunks, with cell sums of their own, as long as no more than
+// SPLIT_GROUPS workgroups result and each keeps enough views to fill its
+// batches: the more, the better the bricks fill the chip by themselves.
+// Transposes (us) with 1 chunk / up to 3072 workgroups / up to 6144: 32^3 / 60
+// views 115 / 50 / 50, 48^3 / 16 47 / 38 / 39.  With 1 / 2 chunks, and as
+// chunks of 4 views, float: 1170 bricks (64^3), 16 views 59 / 57, 59 (and 2%
+// for 4 with finer pixels); 1380 (68^3), 16 66 / 63, 69; 1470 (128 x 128 x 20), 16 54 / 54, 60; 2268 (80^3), 8
+// 57 / -, 60, 16 88 / 87, 32 157 / 146, 60 279 / 248; double: 2268, 8 95 / -,
+// 103, 16 155 / 160, 32 283 / 278; 2704 (200 x 200 x 15), 16 136 / 144, 32 246 /
+// 249.
+constexpr int SPLIT_GROUPS = 6144, SPLIT_MAX = 8;
+
+int least_views(long long bricks) { return bricks < 1300 ? 4 : bricks < 2048 ? 8 : 16; }
 
 // How the cell pass cuts a grid and its views.
 struct Cut {
@@ -1128,7 +1135,7 @@ Cut cut_of(const cbct_geom &g) {
     c.bricks = dim3((g.nx + c.shape.x) / c.shape.x, (g.ny + c.shape.y) / c.shape.y, g.nz + 1);
     const long long bricks = (long long)c.bricks.x * c.bricks.y * c.bricks.z;
     const int want = (int)std::min((long long)SPLIT_MAX, SPLIT_GROUPS / bricks);
-    const int n = std::max(1, std::min(want, g.n_views / SPLIT_VIEWS));
+    const int n = std::max(1, std::min(want, g.n_views / least_views(bricks)));
     c.chunk = (g.n_views + n - 1) / n;
     c.chunks = (g.n_views + c.chunk - 1) / c.chunk;
     return c;
