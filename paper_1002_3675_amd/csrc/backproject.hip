@@ -513,10 +513,11 @@ __device__ __forceinline__ void lane_cell(int tid, int2 shape, int &lx, int &ly)
     ly = square ? ((tid >> 2) & 3) | ((tid >> 3) & 4) | ((tid >> 4) & 8) : tid / shape.x;
 }
 
-// The corner sums of cell (cx, cy, cz) into the workgroup's chunk of `cells`.
+// The corner sums of cell (cx, cy, cz) into the workgroup's chunk of `cells`, or
+// added to what is there.
 template <typename T>
 __device__ __forceinline__ void store_corners(const T m[8], const GridConst &gc, int cx, int cy,
-                                              int cz, T step, T *__restrict__ cells) {
+                                              int cz, T step, bool add, T *__restrict__ cells) {
     const long long cp = cell_pitch(gc.nx);
     const long long ncell = cp * (gc.ny + 1) * (gc.nz + 1);
     const long long lin =
@@ -524,8 +525,14 @@ __device__ __forceinline__ void store_corners(const T m[8], const GridConst &gc,
     T out[8];
     moments_to_corners(m, out);
     cells += 8 * ncell * blockIdx.y;
+    cells += lin;
+    if (add) {
 #pragma unroll
-    for (int o = 0; o < 8; ++o) cells[o * ncell + lin] = out[o] * step;
+        for (int o = 0; o < 8; ++o) cells[o * ncell] += out[o] * step;
+    } else {
+#pragma unroll
+        for (int o = 0; o < 8; ++o) cells[o * ncell] = out[o] * step;
+    }
 }
 
 // Workgroups of 256 lanes, one per brick (see brick_shape) and chunk of views
@@ -557,7 +564,7 @@ template <typename T, bool COL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COL && sizeof(T) == 4 ? 7 : 2, 8))) void k_cells(
     const ViewConst *__restrict__ views, GridConst gc, int2 shape, int nu, int nv, int nviews,
     int chunk, const PixelRay *__restrict__ rays, const BrickView *__restrict__ bviews,
-    const T *__restrict__ r, T *__restrict__ cells, T step) {
+    const T *__restrict__ r, T *__restrict__ cells, T step, bool add) {
     __shared__ vec4<T> tab[2 * TABLE];
     __shared__ vec2<T> tabc[COL ? 1 : TABLE];
     __shared__ vec4<T> tabl[COL ? COLUMNS : 1];
@@ -770,7 +777,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COL && size
         k += n;
     }
     if (c0[0] + lx < c1[0] && c0[1] + ly < c1[1])
-        store_corners(m, gc, c0[0] + lx, c0[1] + ly, c0[2], step, cells);
+        store_corners(m, gc, c0[0] + lx, c0[1] + ly, c0[2], step, add, cells);
 }
 
 // The same where the source is so near that a brick's blocks of pixels are far
@@ -782,7 +789,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_cells_near(
     const ViewConst *__restrict__ views, DetConst dc, GridConst gc, int2 shape, int nu, int nv,
     int nviews, int chunk, const PixelRay *__restrict__ rays, const T *__restrict__ r,
-    T *__restrict__ cells, T step) {
+    T *__restrict__ cells, T step, bool add) {
     int c0[3], c1[3], lx, ly;
     brick_cells(xcd_tile(blockIdx.x, gridDim.x), shape, gc, c0, c1);
     lane_cell(threadIdx.x, shape, lx, ly);
@@ -848,7 +855,7 @@ __global__ __launch_bounds__(256) void k_cells_near(
             cell_sums(m, rays[a].D, r[a], Qd, nmid, c);
         }
     }
-    store_corners(m, gc, c[0], c[1], c[2], step, cells);
+    store_corners(m, gc, c[0], c[1], c[2], step, add, cells);
 }
 
 // Pass 2: out = sum of corner o of cell (v - o) over o in {0,1}^3 and over the
@@ -1126,44 +1133,71 @@ int least_views(long long bricks) { return bricks < 1300 ? 4 : bricks < 2048 ? 8
 struct Cut {
     int2 shape;       // cells of a brick
     dim3 bricks;
-    int chunk, chunks;  // views of a workgroup; chunks of views
+    int slab;           // views of a launch
+    int chunk, chunks;  // views of a workgroup; chunks of a launch's views
 };
+
+// Bricks' views are kept for all views where they take no more than TABLE_BYTES.
+// Beyond that they take a quarter, or TABLE_BYTES where that is more: a launch
+// then goes through a slab of the views, prepared anew for each call, and adds
+// its cell sums to the slabs' before.  512^3 voxels from 720 views: 8.6 GB
+// instead of 25.7, in a call or a solve.  Preparing and adding take
+// a tenth of the transpose's time (320^3, 480 views in four slabs 89.4 -> 98.8
+// ms), so tables that the card easily holds are kept.
+constexpr long long TABLE_BYTES = 8LL << 30;
 
 Cut cut_of(const cbct_geom &g) {
     Cut c;
     c.shape = brick_shape(g);
     c.bricks = dim3((g.nx + c.shape.x) / c.shape.x, (g.ny + c.shape.y) / c.shape.y, g.nz + 1);
     const long long bricks = (long long)c.bricks.x * c.bricks.y * c.bricks.z;
+    const long long view = (long long)sizeof(BrickView) * bricks;
+    const long long most = std::max(TABLE_BYTES / view, (g.n_views + 3LL) / 4);
+    const int slabs = (int)((g.n_views + most - 1) / most);
+    c.slab = (g.n_views + slabs - 1) / slabs;
     const int want = (int)std::min((long long)SPLIT_MAX, SPLIT_GROUPS / bricks);
-    const int n = std::max(1, std::min(want, g.n_views / least_views(bricks)));
-    c.chunk = (g.n_views + n - 1) / n;
-    c.chunks = (g.n_views + c.chunk - 1) / c.chunk;
+    const int n = std::max(1, std::min(want, c.slab / least_views(bricks)));
+    c.chunk = (c.slab + n - 1) / n;
+    c.chunks = (c.slab + c.chunk - 1) / c.chunk;
     return c;
 }
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Geometry tables of the transpose: the ray table at offset 0, then the
-// bricks' views.
-struct GeomLayout {
-    size_t bricks, total;  // byte offsets
-};
+size_t table_bytes(const Cut &c) {
+    return sizeof(BrickView) * (size_t)c.bricks.x * c.bricks.y * c.bricks.z * c.slab;
+}
 
-GeomLayout geom_layout(const cbct_geom &g, const Cut &c) {
-    GeomLayout l;
-    l.bricks = align256(sizeof(PixelRay) * (size_t)g.n_views * g.nu * g.nv);
-    l.total = l.bricks + sizeof(BrickView) * (size_t)c.bricks.x * c.bricks.y * c.bricks.z * g.n_views;
-    return l;
+size_t ray_bytes(const cbct_geom &g) {
+    return align256(sizeof(PixelRay) * (size_t)g.n_views * g.nu * g.nv);
+}
+
+size_t sums_bytes(const cbct_geom &g, const Cut &c, size_t elem) {
+    return align256(elem * 8 * c.chunks * (size_t)cell_pitch(g.nx) * (g.ny + 1) * (g.nz + 1));
+}
+
+hipError_t launch_brick_views(const cbct_plan &p, const Cut &c, int k, int views, BrickView *out,
+                              hipStream_t s) {
+    const dim3 b = c.bricks;
+    hipLaunchKernelGGL(k_brick_views, dim3(b.x * b.y * b.z), dim3(64), 0, s, p.d_views + k, p.det,
+                       p.grid, p.g.hx, p.g.hy, p.g.hz, p.g.nu, p.g.nv, c.shape, (int)b.x, (int)b.y,
+                       views, c.chunk, by_columns(p.g), out);
+    return hipGetLastError();
 }
 
 }  // namespace
 
+// The cell sums, and after them a slab's bricks' views.
 size_t bp_cells_bytes(const cbct_geom &g, size_t elem) {
-    return align256(elem * 8 * cut_of(g).chunks * (size_t)cell_pitch(g.nx) * (g.ny + 1) *
-                    (g.nz + 1));
+    const Cut c = cut_of(g);
+    return sums_bytes(g, c, elem) + (c.slab < g.n_views ? align256(table_bytes(c)) : 0);
 }
 
-size_t bp_geom_bytes(const cbct_geom &g) { return geom_layout(g, cut_of(g)).total; }
+// The ray table, and after it the bricks' views if all are kept.
+size_t bp_geom_bytes(const cbct_geom &g) {
+    const Cut c = cut_of(g);
+    return ray_bytes(g) + (c.slab < g.n_views ? 0 : table_bytes(c));
+}
 
 size_t bp_workspace_bytes(const cbct_geom &g, size_t elem) {
     return bp_cells_bytes(g, elem) + bp_geom_bytes(g);
@@ -1182,17 +1216,12 @@ void cell_pass_config(int32_t out[4]) {
 
 hipError_t launch_bp_prepare(const cbct_plan &p, void *geom, hipStream_t s) {
     const Cut c = cut_of(p.g);
-    const GeomLayout l = geom_layout(p.g, c);
     char *base = (char *)geom;
     hipLaunchKernelGGL(k_rays, dim3((p.g.nu + 63) / 64, (p.g.nv + 3) / 4, p.g.n_views), dim3(256),
                        0, s, p.d_views, p.det, p.g.nu, p.g.nv, (PixelRay *)base);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const dim3 b = c.bricks;
-    hipLaunchKernelGGL(k_brick_views, dim3(b.x * b.y * b.z), dim3(64), 0, s, p.d_views, p.det,
-                       p.grid, p.g.hx, p.g.hy, p.g.hz, p.g.nu, p.g.nv, c.shape, (int)b.x, (int)b.y,
-                       p.g.n_views, c.chunk, by_columns(p.g), (BrickView *)(base + l.bricks));
-    return hipGetLastError();
+    if (e != hipSuccess || c.slab < p.g.n_views) return e;
+    return launch_brick_views(p, c, 0, p.g.n_views, (BrickView *)(base + ray_bytes(p.g)), s);
 }
 
 // What decides is how many pixels the lanes of a brick visit, on average, and
@@ -1256,19 +1285,32 @@ template <typename T>
 hipError_t launch_backproject_cells(const cbct_plan &p, const T *r, void *cells,
                                     const void *geom, hipStream_t s) {
     const Cut c = cut_of(p.g);
-    const char *base = (const char *)geom;
     const dim3 grid(c.bricks.x * c.bricks.y * c.bricks.z, c.chunks);
-    const PixelRay *rays = (const PixelRay *)base;
-    const BrickView *bv = (const BrickView *)(base + geom_layout(p.g, c).bricks);
-    if (sizeof(T) == 4 ? p.near32 : p.near64)
-        hipLaunchKernelGGL(k_cells_near<T>, grid, dim3(256), 0, s, p.d_views, p.det, p.grid,
-                           c.shape, p.g.nu, p.g.nv, p.g.n_views, c.chunk, rays, r, (T *)cells,
-                           (T)p.g.step);
-    else
-        hipLaunchKernelGGL((by_columns(p.g) ? k_cells<T, true> : k_cells<T, false>), grid,
-                           dim3(256), 0, s, p.d_views, p.grid, c.shape, p.g.nu, p.g.nv,
-                           p.g.n_views, c.chunk, rays, bv, r, (T *)cells, (T)p.g.step);
-    return hipGetLastError();
+    const bool near = sizeof(T) == 4 ? p.near32 : p.near64, kept = c.slab == p.g.n_views;
+    BrickView *bv = kept ? (BrickView *)((char *)geom + ray_bytes(p.g))
+                         : (BrickView *)((char *)cells + sums_bytes(p.g, c, sizeof(T)));
+    for (int k = 0; k < p.g.n_views; k += c.slab) {
+        const int views = std::min(c.slab, p.g.n_views - k);
+        const long long first = (long long)k * p.g.nu * p.g.nv;
+        const PixelRay *rays = (const PixelRay *)geom + first;
+        if (near) {
+            hipLaunchKernelGGL(k_cells_near<T>, grid, dim3(256), 0, s, p.d_views + k, p.det,
+                               p.grid, c.shape, p.g.nu, p.g.nv, views, c.chunk, rays, r + first,
+                               (T *)cells, (T)p.g.step, k > 0);
+        } else {
+            if (!kept) {
+                const hipError_t e = launch_brick_views(p, c, k, views, bv, s);
+                if (e != hipSuccess) return e;
+            }
+            hipLaunchKernelGGL((by_columns(p.g) ? k_cells<T, true> : k_cells<T, false>), grid,
+                               dim3(256), 0, s, p.d_views + k, p.grid, c.shape, p.g.nu, p.g.nv,
+                               views, c.chunk, rays, bv, r + first, (T *)cells, (T)p.g.step,
+                               k > 0);
+        }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <typename T>
