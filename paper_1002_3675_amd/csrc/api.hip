@@ -80,9 +80,6 @@ GridConst grid_of(const cbct_geom &g) {
     c.hx = (float)g.hx;
     c.hy = (float)g.hy;
     c.hz = (float)g.hz;
-    c.x0 = (float)(-0.5 * (g.nx - 1) * g.hx + g.x_off);
-    c.y0 = (float)(-0.5 * (g.ny - 1) * g.hy + g.y_off);
-    c.z0 = (float)(-0.5 * (g.nz - 1) * g.hz + g.z_off);
     return c;
 }
 
@@ -325,19 +322,14 @@ extern "C" int cbct_plan_create(const cbct_geom *gin, cbct_plan **out) {
             memset(&v, 0, sizeof(v));
             for (int a = 0; a < 3; ++a) {
                 v.Qd[a] = (src[a] - x0[a]) / h[a];
-                v.Q[a] = (float)v.Qd[a];
             }
             for (int a = 0; a < 2; ++a) {
                 v.Wd[a] = step / h[a] * g.sdd * ew[a];
                 v.Ud[a] = step / h[a] * eu[a];
                 v.W[a] = (float)v.Wd[a];
                 v.U[a] = (float)v.Ud[a];
-                v.src[a] = (float)src[a];
             }
             v.Vzd = step / h[2];
-            v.Vz = (float)v.Vzd;
-            v.cs = (float)cs;
-            v.sn = (float)sn;
             v.csd = cs;
             v.snd = sn;
             v.en[0] = h[0] * cs;
@@ -357,11 +349,7 @@ extern "C" int cbct_plan_create(const cbct_geom *gin, cbct_plan **out) {
         d.sdd2d = g.sdd * g.sdd;
         d.sddd = g.sdd;
         d.u0 = (float)d.u0d;
-        d.v0 = (float)d.v0d;
         d.au = (float)g.au;
-        d.av = (float)g.av;
-        d.sdd2 = (float)d.sdd2d;
-        d.sdd = (float)g.sdd;
         p->grid = grid_of(g);
         (void)hipGetDevice(&p->device);
         rc = check_hip(hipMalloc((void **)&p->d_views, sizeof(ViewConst) * g.n_views),

@@ -294,9 +294,10 @@ template <typename T> struct StagedRay {
 // float for the face they share, so every sample is in exactly one brick,
 // and inside a brick in exactly one cell (crossing_sums), whatever the
 // rounding.  A sample within rounding of a face (6e-5 of a step at 512
-// voxels) may get the cell beside the exact one; its weights, formed from
-// its position in that cell, then differ from the exact ones by a second
-// order of that distance.
+// voxels) may get the cell beside the exact one; its weights, formed from its
+// position in that cell, then are off by twice its distance from the face at
+// the face's voxels and by minus that distance at their neighbours on both
+// sides: second differences, to which smooth data are blind.
 template <typename T>
 __device__ __forceinline__ BrickRay<T> brick_ray(const double D[3], const double Qd[3], int nmid,
                                                  const int c0[3], const int c1[3]) {

@@ -22,15 +22,10 @@ namespace cbct {
 // position in index coordinates, (s_a - x_a(0)) / h_a, and W, U, V are
 // step/h_a times sdd*e_w, e_u and e_v.
 struct ViewConst {
-    float Q[3];
-    float W[2];    // W_z = 0 (e_w lies in the xy plane)
-    float U[2];    // U_z = 0
-    float Vz;      // V_x = V_y = 0
-    float src[2];  // source (mm), x and y; z = 0
-    float cs, sn;  // cos(theta), sin(theta)
-    double Qd[3];  // the same constants in double for the FP64 kernels
-    double Wd[2], Ud[2], Vzd;
-    double csd, snd;  // cos(theta), sin(theta) in double
+    double Qd[3];
+    double Wd[2], Ud[2], Vzd;  // W_z = U_z = V_x = V_y = 0 (e_w and e_u lie in the xy plane)
+    float W[2], U[2];          // in float, for the rays' directions
+    double csd, snd;           // cos(theta), sin(theta)
     // source-to-voxel (i, j) vector (mm) along e_u and along e_w (the depth):
     // en[0] i + en[1] j + en[2], ew alike
     double en[3], ew[3];
@@ -51,16 +46,14 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
 }
 
 struct DetConst {
-    float u0, au, v0, av;  // pixel centre u = u0 + i*au, v = v0 + j*av (mm)
-    float sdd2;            // sdd^2
-    float sdd;
-    double u0d, aud, v0d, avd, sdd2d, sddd;
+    double u0d, aud, v0d, avd;  // pixel centre u = u0 + i*au, v = v0 + j*av (mm)
+    double sdd2d, sddd;         // sdd^2, sdd
+    float u0, au;               // in float, for the rays' directions
 };
 
 struct GridConst {
     int nx, ny, nz;
     float hx, hy, hz;
-    float x0, y0, z0;      // centre of voxel 0 (mm)
 };
 
 }  // namespace cbct
@@ -110,10 +103,11 @@ hipError_t launch_project(const cbct_plan &p, const T *fpad, const T *Y, T *out,
                           double *partials, hipStream_t s);
 // The transpose needs the cell corner sums (bp_cells_bytes, written by
 // launch_backproject_cells, read by launch_gather_cells) and the geometry
-// tables (bp_geom_bytes: a per-pixel ray table and per-brick pixel
-// rectangles), which depend on the plan only and are filled by
-// launch_bp_prepare.  A combined workspace of bp_workspace_bytes holds the
-// corner sums at offset 0 and the geometry tables at bp_geom_in.
+// tables (bp_geom_bytes: the ray table, a ray a pixel, and every brick's
+// record of every view), which depend on the plan only and are filled by
+// launch_bp_prepare; of very large scans the records lie with the corner sums
+// and are filled by each call.  A combined workspace of bp_workspace_bytes
+// holds the corner sums at offset 0 and the geometry tables at bp_geom_in.
 size_t bp_cells_bytes(const cbct_geom &g, size_t elem_size);
 size_t bp_geom_bytes(const cbct_geom &g);
 size_t bp_workspace_bytes(const cbct_geom &g, size_t elem_size);

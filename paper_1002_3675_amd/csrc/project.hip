@@ -54,7 +54,7 @@ __device__ __forceinline__ void sample_cell(const double Q[3], const double D[3]
     } else {
 #pragma unroll
         for (int a = 0; a < 3; ++a)
-            c[a] = (int)floor_t(sample_coord((double)n, D[a], Q[a]));
+            c[a] = (int)__builtin_floor(sample_coord((double)n, D[a], Q[a]));
     }
 }
 
@@ -91,8 +91,8 @@ __device__ __forceinline__ void ray_interval(const double Q[3], const double D[3
         n1 = 0;
         return;
     }
-    n0 = clamp_to_int(floor_t(lo));
-    n1 = clamp_to_int(floor_t(hi)) + 1;
+    n0 = clamp_to_int(__builtin_floor(lo));
+    n1 = clamp_to_int(__builtin_floor(hi)) + 1;
     if (n0 < 0) n0 = 0;
     while (n0 <= n1 && !in_box<T>(n0, Q, D, Df, gc)) ++n0;
     while (n1 >= n0 && !in_box<T>(n1, Q, D, Df, gc)) --n1;
@@ -147,7 +147,7 @@ __device__ __forceinline__ double march_double(const double Q[3], const double D
         const double q0 = sample_coord(nf, D[0], Q[0]);
         const double q1 = sample_coord(nf, D[1], Q[1]);
         const double q2 = sample_coord(nf, D[2], Q[2]);
-        const double f0 = floor_t(q0), f1 = floor_t(q1), f2 = floor_t(q2);
+        const double f0 = __builtin_floor(q0), f1 = __builtin_floor(q1), f2 = __builtin_floor(q2);
         const double wx = q0 - f0, wy = q1 - f1, wz = q2 - f2;
         const int base = ((int)f2 + 1) * pxy + ((int)f1 + 1) * px + ((int)f0 + 1);
         const double *p = fp + base;

@@ -90,46 +90,32 @@ __device__ __forceinline__ double sample_coord(double n, double D, double Q) {
     return __builtin_fma(n, D, Q);
 }
 
-template <typename T>
-__device__ __forceinline__ T floor_t(T x);
-template <>
-__device__ __forceinline__ float floor_t<float>(float x) { return __builtin_floorf(x); }
-template <>
-__device__ __forceinline__ double floor_t<double>(double x) { return __builtin_floor(x); }
-
 // Interval [lo, hi] (real-valued, unrounded) of sample indices whose
 // coordinate along one axis lies in [a, b); returns false if none can.
-template <typename T>
-__device__ __forceinline__ bool axis_interval(T Q, T D, T a, T b, T &lo, T &hi) {
-    if (D > T(0)) {
-        T inv = T(1) / D;
+__device__ __forceinline__ bool axis_interval(double Q, double D, double a, double b, double &lo,
+                                              double &hi) {
+    if (D > 0.0) {
+        const double inv = 1.0 / D;
         lo = (a - Q) * inv;
         hi = (b - Q) * inv;
         return true;
     }
-    if (D < T(0)) {
-        T inv = T(1) / D;
+    if (D < 0.0) {
+        const double inv = 1.0 / D;
         lo = (b - Q) * inv;
         hi = (a - Q) * inv;
         return true;
     }
-    lo = T(-1e30);
-    hi = T(1e30);
+    lo = -1e30;
+    hi = 1e30;
     return Q >= a && Q < b;
 }
 
 // Clamp a real sample index into a range safe for int conversion.
-template <typename T>
-__device__ __forceinline__ int clamp_to_int(T x) {
-    x = x < T(-4) ? T(-4) : x;
-    x = x > T(1 << 24) ? T(1 << 24) : x;
+__device__ __forceinline__ int clamp_to_int(double x) {
+    x = x < -4.0 ? -4.0 : x;
+    x = x > (double)(1 << 24) ? (double)(1 << 24) : x;
     return (int)x;
-}
-
-// Same for float with one median-of-three (finite inputs).
-template <>
-__device__ __forceinline__ int clamp_to_int<float>(float x) {
-    return (int)__builtin_amdgcn_fmed3f(x, -4.0f, (float)(1 << 24));
 }
 
 }  // namespace cbct
