@@ -37,7 +37,7 @@ namespace {
 
 constexpr int CB_X = 16, CB_Y = 16, CB_Z = 1;  // cells per workgroup: one z layer (see brick_shape)
 constexpr int TABLE = 560;                     // rays staged at a time (at most 40 B each, 80 in double)
-constexpr int COLUMNS = 256;                   // and pixel columns (k_cells by columns; 16 B, 32)
+constexpr int COLUMNS = 256;                   // and pixel columns (k_cells by columns; 16 B)
 constexpr int PARTS = 6;                       // views staged at a time, at most
 constexpr int G_BX = 64, G_BY = 4;            // pass-2 block
 
@@ -317,8 +317,12 @@ __device__ __forceinline__ BrickRay<T> brick_ray(const double D[3], const double
     lo = min_t(ceil_t(lo), T(8388608));
     hi = ceil_t(hi);
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-        e.f[a] = (T)(__builtin_fma((double)lo, D[a], qm[a]) - (double)c0[a]);
+    for (int a = 0; a < 3; ++a) {
+        // in double the sample's own coordinate, rounded once
+        const double q = sizeof(T) == 8 ? __builtin_fma(nmid + (double)lo, D[a], Qd[a])
+                                        : __builtin_fma((double)lo, D[a], qm[a]);
+        e.f[a] = (T)(q - (double)c0[a]);
+    }
     e.N = max_t(hi - lo, T(0));
     return e;
 }
@@ -407,12 +411,12 @@ __device__ __forceinline__ void crossing_sums(T m[8], const vec4<T> ra, const ve
 // crossings are brick_ray's of those faces.
 template <typename T>
 __device__ __forceinline__ void cell_sums(T m[8], const double D[3], T rv, const double Qd[3],
-                                          int nmid, const int c[3]) {
+                                          double nmid, const int c[3]) {
     double qm[3];
     T lo = T(-8388608), hi = T(8388608);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        qm[a] = __builtin_fma((double)nmid, D[a], Qd[a]);
+        qm[a] = __builtin_fma(nmid, D[a], Qd[a]);
         const T q = (T)qm[a], inv = rcp((T)D[a]);
         const T t0 = ((T)c[a] - q) * inv, t1 = ((T)(c[a] + 1) - q) * inv;
         lo = max_t(lo, min_t(t0, t1));
@@ -420,9 +424,12 @@ __device__ __forceinline__ void cell_sums(T m[8], const double D[3], T rv, const
     }
     const T n0 = min_t(ceil_t(lo), T(8388608)), k = max_t(ceil_t(hi) - n0, T(0));
     const double n = (double)n0 + 0.5 * ((double)k - 1.0);
-    const T x = (T)(__builtin_fma(n, D[0], qm[0]) - ((double)c[0] + 0.5));
-    const T y = (T)(__builtin_fma(n, D[1], qm[1]) - ((double)c[1] + 0.5));
-    const T z = (T)(__builtin_fma(n, D[2], qm[2]) - ((double)c[2] + 0.5));
+    auto at = [&](int a) {
+        const double q = sizeof(T) == 8 ? __builtin_fma(nmid + n, D[a], Qd[a])
+                                        : __builtin_fma(n, D[a], qm[a]);
+        return (T)(q - ((double)c[a] + 0.5));
+    };
+    const T x = at(0), y = at(1), z = at(2);
     const T A = mul_zero(rv, k);
     const T B = A * fma_t(k * k, T(1) / T(12), T(-1) / T(12));
     add_crossing(m, A, B, x, y, z, (T)D[0], (T)D[1], (T)D[2]);
@@ -560,12 +567,15 @@ __device__ __forceinline__ void store_corners(const T m[8], const GridConst &gc,
 // Double data (derivative checks) took every candidate sample of every pixel
 // from the ray table; with the staged rays and the closed form a transpose
 // of 32^3 from 60 views takes 76 us instead of 213
-// (163 with one chunk of views).
+// (163 with one chunk of views).  It goes by rays always: a column's line, the
+// same for all its rays, carries the rounding of one ray's increment, some
+// hundred cells from the source, into all of them, and the transpose was up
+// to 15% further from 80-bit sums than with each ray's own; 3 to 12% faster.
 template <typename T, bool COL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COL && sizeof(T) == 4 ? 7 : 2, 8))) void k_cells(
     const ViewConst *__restrict__ views, GridConst gc, int2 shape, int nu, int nv, int nviews,
     int chunk, const PixelRay *__restrict__ rays, const BrickView *__restrict__ bviews,
-    const T *__restrict__ r, T *__restrict__ cells, T step, bool add) {
+    const T *__restrict__ r, T *__restrict__ cells, T step, bool add, bool alike) {
     __shared__ vec4<T> tab[2 * TABLE];
     __shared__ vec2<T> tabc[COL ? 1 : TABLE];
     __shared__ vec4<T> tabl[COL ? COLUMNS : 1];
@@ -608,12 +618,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COL && size
     for (int k = blockIdx.y * chunk; k < kend;) {
         // the batch, or the parts of a view too large for the table: bands of
         // rows, or pieces of a row
-        int n = bv[k].batch_n, total = bv[k].batch_rays, columns = 0;
-        if constexpr (COL) {
-            columns = total >> 16;
-            total &= 0xffff;
-        }
-        const int dirs = bv[k].dirs & 4 ? bv[k].dirs : 0;
+        int n = bv[k].batch_n, total = bv[k].batch_rays & 0xffff;
+        int columns = bv[k].batch_rays >> 16;
+        // (batches formed for columns mix directions)
+        const int dirs = alike && bv[k].dirs & 4 ? bv[k].dirs : 0;
         int cols = 1, pw = 0, ph = 0, parts = 1;
         if (n == 0) {
             constexpr int WIDEST = COL ? COLUMNS : TABLE;
@@ -638,7 +646,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COL && size
                 int2 c = make_int2(0x7fffffff, 0);
                 if (tid < n) {
                     const BrickView &b = bv[k + tid];
-                    s = make_int4(COL ? b.base & 0xffff : b.base, parts > 1 ? w : b.w, b.i0 + oi,
+                    s = make_int4(b.base & 0xffff, parts > 1 ? w : b.w, b.i0 + oi,
                                   b.j0 + oj);
                     c = make_int2(b.base >> 16, b.dirs & 8);
                 }
@@ -715,7 +723,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COL && size
                                                                   cj + b.H > 0 && cj < bh))
                         continue;
                     const int e =
-                        b.base + max(min(cj, bh - H), 0) * bw + max(min(ci, bw - W), 0);
+                        (b.base & 0xffff) + max(min(cj, bh - H), 0) * bw + max(min(ci, bw - W), 0);
                     const vec4<T> *p = tab + e;
                     const vec2<T> *pc = tabc + e;
                     for (int y = 0; y < H; ++y, p += bw, pc += bw) {
@@ -830,7 +838,7 @@ __global__ __launch_bounds__(256) void k_cells_near(
         const int i1 = min((int)__builtin_floorf(umax + mu + ci), nu - 1);
         const int j1 = min((int)__builtin_floorf(vmax + mv + cj), nv - 1);
         const double Qd[3] = {vc.Qd[0], vc.Qd[1], vc.Qd[2]};
-        const int nmid = vc.nmid;
+        const double nmid = vc.nmid;
         const long long view = (long long)k * nu * nv;
         int i = i0, j = j0;
         auto next = [&] {
@@ -1235,12 +1243,13 @@ hipError_t launch_bp_prepare(const cbct_plan &p, void *geom, hipStream_t s) {
 // 170 geometries, the source 1.15 to 10 radii of the grid from the axis: the
 // choice is the slower one by more than 7% in two of them (float, 18% at most)
 // and in four (double, 33%), and against the kernel before k_cells, which
-// tested candidate samples, none loses more than 2%.  Transposes by that
+// tested candidate samples, none loses more than 2% but one, 100 x 100 x 50 in
+// double with steps of two voxels (250 -> 282 us).  Transposes by that
 // kernel / k_cells / this choice (us; float, double): 40 x 40 x 20 beside the
-// source 267 / 422 / 103, 266 / 647 / 119; 160 x 160 x 80 beside it 1776 /
-// 14963 / 1031, 2034 / 23747 / 1336; 64^3 at 1.3 radii 401 / 2007 / 226, 483 /
-// 3799 / 306, at 3 radii 150 / 92 / 99, 194 / 175 / 137; 64 x 64 x 20 with
-// pixels of a fifteenth of a voxel 2199 / 1858 / 1092, 2348 / 2672 / 1268.
+// source 267 / 422 / 103, 266 / 647 / 118; 160 x 160 x 80 beside it 1776 /
+// 14963 / 1031, 2034 / 23747 / 1357; 64^3 at 1.3 radii 401 / 2007 / 226, 483 /
+// 3799 / 311, at 3 radii 150 / 92 / 99, 194 / 175 / 138; 64 x 64 x 20 with
+// pixels of a fifteenth of a voxel 2199 / 1858 / 1092, 2348 / 2672 / 1388.
 void choose_cells(cbct_plan &p) {
     const cbct_geom &g = p.g;
     const Cut c = cut_of(g);
@@ -1303,10 +1312,13 @@ hipError_t launch_backproject_cells(const cbct_plan &p, const T *r, void *cells,
                 const hipError_t e = launch_brick_views(p, c, k, views, bv, s);
                 if (e != hipSuccess) return e;
             }
-            hipLaunchKernelGGL((by_columns(p.g) ? k_cells<T, true> : k_cells<T, false>), grid,
-                               dim3(256), 0, s, p.d_views + k, p.grid, c.shape, p.g.nu, p.g.nv,
-                               views, c.chunk, rays, bv, r + first, (T *)cells, (T)p.g.step,
-                               k > 0);
+            auto kernel = k_cells<T, false>;
+            if constexpr (sizeof(T) == 4) {
+                if (by_columns(p.g)) kernel = k_cells<T, true>;
+            }
+            hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, p.d_views + k, p.grid, c.shape,
+                               p.g.nu, p.g.nv, views, c.chunk, rays, bv, r + first, (T *)cells,
+                               (T)p.g.step, k > 0, !by_columns(p.g));
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
