@@ -909,12 +909,14 @@ __global__ __launch_bounds__(256) void k_gather(GridConst gc, int chunks,
 // arithmetic above all, and by the gathers: about 33 instructions a voxel
 // and view with four voxels a lane, 26 / 4 of them for the view, and two
 // loads.  Head (512 x 512 x 70, 40 views) 1640 us with one voxel a lane and
-// tested taps, 825 with four, 780 with six and what all lanes share in scalar
+// tested taps, 825 with four, 786 with six and what all lanes share in scalar
 // registers (96 vector registers; eight voxels take 116 and 4% longer).  The
 // row's fraction read from the low word of a double 2^20 above it took 724,
 // but is then cut at 2^-32 of a row: further from the exact values than before
-// in 22 of 40 geometries, by up to 0.2% of their error.  With one voxel a
-// lane, where few wavefronts wait for a view's latencies, a view has no
+// in 22 of 40 geometries, by up to 0.2% of their error.  A view's loads are
+// issued before its sums by a barrier to the scheduler: left to itself it
+// orders them so or not, 780 or 875 us, by what changes elsewhere.  With one
+// voxel a lane, where few wavefronts wait for a view's latencies, a view has no
 // branch and its taps no tests: 64^3 from 16 views 14.5 -> 10.1 us (14.8 with
 // the first kernel), 14 x 14 x 25 from 21 views 15.0 -> 9.5 (14.1).
 constexpr int Q_BX = 64, Q_BY = 4;
@@ -1031,15 +1033,23 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
             const float *rt1 = rt + nu;
             const unsigned nu4 = 4u * (unsigned)nu;
             const unsigned i4 = 4u * (unsigned)(int)i0d;
+            float r00[ZC], r10[ZC], r01[ZC], r11[ZC], b[ZC];
 #pragma unroll
             for (int q = 0; q < ZC; ++q) {
                 const double fj = __builtin_fma((double)q, v.dj, v.fj);
                 const unsigned o = __umul24((unsigned)(int)fj, nu4) + i4;
-                const float b = (float)__builtin_amdgcn_fract(fj);
+                b[q] = (float)__builtin_amdgcn_fract(fj);
                 const float *p = (const float *)((const char *)rt + o);
                 const float *p1 = (const float *)((const char *)rt1 + o);
-                const float v0 = p[0] + a * (p[1] - p[0]), v1 = p1[0] + a * (p1[1] - p1[0]);
-                sum[q] = __builtin_fma(weight(v, q), (double)(v0 + b * (v1 - v0)), sum[q]);
+                r00[q] = p[0], r10[q] = p[1], r01[q] = p1[0], r11[q] = p1[1];
+            }
+            // all loads go out before the first is waited for
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < ZC; ++q) {
+                const float v0 = r00[q] + a * (r10[q] - r00[q]);
+                const float v1 = r01[q] + a * (r11[q] - r01[q]);
+                sum[q] = __builtin_fma(weight(v, q), (double)(v0 + b[q] * (v1 - v0)), sum[q]);
             }
             continue;
         }
