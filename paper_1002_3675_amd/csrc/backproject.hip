@@ -1140,13 +1140,14 @@ bool by_columns(const cbct_geom &g) {
 // Transposes (us) with 1 chunk / up to 3072 workgroups / up to 6144: 32^3 / 60
 // views 115 / 50 / 50, 48^3 / 16 47 / 38 / 39.  With 1 / 2 chunks, and as
 // chunks of 4 views, float: 1170 bricks (64^3), 16 views 59 / 57, 59 (and 2%
-// for 4 with finer pixels); 1380 (68^3), 16 66 / 63, 69; 1470 (128 x 128 x 20), 16 54 / 54, 60; 2268 (80^3), 8
-// 57 / -, 60, 16 88 / 87, 32 157 / 146, 60 279 / 248; double: 2268, 8 95 / -,
-// 103, 16 155 / 160, 32 283 / 278; 2704 (200 x 200 x 15), 16 136 / 144, 32 246 /
-// 249.
+// for 4 with finer pixels); 1340 (66^3), 16 66 / 61, 65; 1470 (128 x 128 x 20),
+// 16 54 / 54, 60; 2072 (109 x 115 x 36), 16 177 / 166, 24 260 / 240; 2268 (80^3),
+// 8 57 / -, 60, 16 88 / 87; 2324 (82^3), 16 95 / 94, 24 135 / 129; 2784 (86^3), 16
+// 108 / 113, 24 155 / 159, 40 242 / 246; double: 2072, 16 359 / 349; 2268, 8 95 /
+// -, 103, 16 155 / 160; 2324, 24 257 / 243; 2784, 16 206 / 234.
 constexpr int SPLIT_GROUPS = 6144, SPLIT_MAX = 8;
 
-int least_views(long long bricks) { return bricks < 1300 ? 4 : bricks < 2048 ? 8 : 16; }
+int least_views(long long bricks) { return bricks < 1300 ? 4 : bricks < 2500 ? 8 : 16; }
 
 // How the cell pass cuts a grid and its views.
 struct Cut {
