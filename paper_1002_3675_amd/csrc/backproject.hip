@@ -917,8 +917,10 @@ __global__ __launch_bounds__(256) void k_gather(GridConst gc, int chunks,
 // issued before its sums by a barrier to the scheduler: left to itself it
 // orders them so or not, 780 or 875 us, by what changes elsewhere.  With one
 // voxel a lane, where few wavefronts wait for a view's latencies, a view has no
-// branch and its taps no tests: 64^3 from 16 views 14.5 -> 10.1 us (14.8 with
-// the first kernel), 14 x 14 x 25 from 21 views 15.0 -> 9.5 (14.1).
+// branch and its taps no tests, and the two pixels of a row are one load: 64^3
+// from 16 views 14.5 -> 10.5 us (14.8 with the first kernel), 14 x 14 x 25 from
+// 21 views 15.0 -> 10.3 (14.1), 64^3 from 20 views with the source at 1.3 radii
+// 14.0 -> 12.2 (18.6; a load for each pixel 16.2).
 constexpr int Q_BX = 64, Q_BY = 4;
 
 // sqrt(x) for x > 0: the hardware's reciprocal root and a correction, which
@@ -994,10 +996,10 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
         return v.w0 * (double)sqrt_pos((float)(wz2[q] + v.lxy2));
     };
     int t0 = 0;
-    if (ZC == 1 && (long long)nu * nv < (1LL << 28) && nu < (1 << 21) && nv < (1 << 20)) {
+    if (ZC == 1 && nu > 1 && (long long)nu * nv < (1LL << 28) && nu < (1 << 21) && nv < (1 << 20)) {
         // Few wavefronts: a view takes its chain of latencies, shorter without
         // branches and with the next view's beside it.  A view is a buffer that
-        // reads zero beyond its ends, and so 2^31 bytes on.
+        // reads zero beyond its ends.
 #pragma unroll 2
         for (int t = 0; t < nviews; ++t) {
             const Eq2View v = eq2_view(views[t], dc, i, j, kz, su, svh, ci, cj);
@@ -1005,17 +1007,24 @@ __global__ __launch_bounds__(256) void k_eq2(const ViewConst *__restrict__ views
             const float a = (float)(v.fi - i0d), b = (float)(v.fj - j0d);
             const int i0 = (int)fmax(fmin(i0d, (double)nu), -2.0);
             const int j0 = (int)fmax(fmin(j0d, (double)nv), -2.0);
-            const unsigned nu4 = 4u * (unsigned)nu, o = (unsigned)__mul24(j0, 4 * nu);
-            const unsigned o0 = o + (i0 >= 0 && i0 < nu ? 4u * (unsigned)i0 : 0x80000000u);
-            const unsigned o1 =
-                o + (i0 >= -1 && i0 < nu - 1 ? 4u * (unsigned)(i0 + 1) : 0x80000000u);
+            // the pair of a row's pixels that holds those of the two that are there
+            const int ip = max(min(i0, nu - 2), 0);
+            const unsigned nu4 = 4u * (unsigned)nu;
+            const unsigned o = (unsigned)__mul24(j0, 4 * nu) + 4u * (unsigned)ip;
             const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(
                 (void *)(r + (long long)t * nu * nv), (short)0, 4 * nu * nv, 0x00020000);
-            auto tap = [&](unsigned at) {
-                return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rt, at, 0, 0));
+            using pair = unsigned __attribute__((ext_vector_type(2)));
+            const pair p0 = __builtin_amdgcn_raw_buffer_load_b64(rt, o, 0, 0);
+            const pair p1 = __builtin_amdgcn_raw_buffer_load_b64(rt, o + nu4, 0, 0);
+            const bool left = i0 < 0, right = i0 > nu - 2;
+            const bool in0 = i0 >= 0 && i0 < nu, in1 = i0 >= -1 && i0 < nu - 1;
+            auto first = [&](pair p) {
+                return in0 ? __builtin_bit_cast(float, right ? p[1] : p[0]) : 0.0f;
             };
-            const float r00 = tap(o0), r10 = tap(o1);
-            const float r01 = tap(o0 + nu4), r11 = tap(o1 + nu4);
+            auto second = [&](pair p) {
+                return in1 ? __builtin_bit_cast(float, left ? p[0] : p[1]) : 0.0f;
+            };
+            const float r00 = first(p0), r10 = second(p0), r01 = first(p1), r11 = second(p1);
             const float v0 = r00 + a * (r10 - r00), v1 = r01 + a * (r11 - r01);
             sum[0] = __builtin_fma(weight(v, 0), (double)(v0 + b * (v1 - v0)), sum[0]);
         }
