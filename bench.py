@@ -36,7 +36,7 @@ PEAK_ALU_TFLOPS = 78.6      # 256 CU x 64 lanes x 2 flop (FMA) x 2.4 GHz, non-pa
 # fractions (3), and the 8 trilinear corner weights times the residual with
 # their accumulation (22)
 FLOPS_PER_SAMPLE = 34.0
-TV_BYTES_PER_VOXEL = 12.0   # per sweep: read z and g, write z
+TV_BYTES_PER_VOXEL = 12.0   # per launch (one to three steps): read z and g, write z
 
 
 TRAFFIC_FILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles",
@@ -70,6 +70,16 @@ def measured_traffic(kernel, mix):
                 n_c, n_f = mix
                 return (n_c * coarse + n_f * fine) / max(n_c + n_f, 1)
     return None
+
+
+def tv_launches(torch, cb, geom, n_inner):
+    """Launches that `n_inner` TV steps take on this level's grid, counted."""
+    z = torch.zeros(geom.vol_shape, device="cuda")
+    cb.kernel_timing(True, kernels=["tv_sweep"])
+    cb.tv_prox(z, z, (geom.hx, geom.hy, geom.hz), 1.0, 1e-3, n_inner)
+    torch.cuda.synchronize()
+    cb.kernel_timing(False)
+    return cb.kernel_times()["tv_sweep"][0]
 
 
 def eq2_comparison(torch, cb, plan, Y, params, f_matched, rep_matched, yr, fb, ms_pt, reps):
@@ -540,6 +550,9 @@ def main():
     kall = cb.kernel_times()
     dom = max(kall, key=lambda k: kall[k][1])
     log("breakdown solve done; dominant kernel %s" % dom)
+    n_inner = list(rep.n_inner_used)
+    tv = [tv_launches(torch, cb, lv, n) * it
+          for lv, n, it in zip((plan_c.geom, g), n_inner, iters)]
 
     cb.kernel_timing(True, kernels=[dom])
     torch.cuda.synchronize()
@@ -556,19 +569,17 @@ def main():
 
     # per-kernel algorithmic work over the timed region
     nvox_f, nvox_c = g.n_vox, plan_c.geom.nx * plan_c.geom.ny * plan_c.geom.nz
-    n_inner = list(rep.n_inner_used)
-    sweeps = n_inner[0] * iters[0] * nvox_c + n_inner[1] * iters[1] * nvox_f
     work = {
         "project": ("alu", FLOPS_PER_SAMPLE * (iters[0] * s_c + (iters[1] + 1) * s_f)),
         "cells": ("alu", FLOPS_PER_SAMPLE * (iters[0] * s_c + iters[1] * s_f)),
-        "tv_sweep": ("hbm", TV_BYTES_PER_VOXEL * sweeps),
+        "tv_sweep": ("hbm", TV_BYTES_PER_VOXEL * (tv[0] * nvox_c + tv[1] * nvox_f)),
         "gather": ("hbm", 4.0 * (8 + 1 + 1) * (iters[0] * nvox_c + iters[1] * nvox_f)),
     }
-    # launches per level (coarse, fine) of each kernel in one solve (a TV
-    # launch makes one to three steps)
+    # launches per level (coarse, fine) of each kernel in one solve
     mix = {
         "project": (iters[0], iters[1] + 1),
         "cells": (iters[0], iters[1]),
+        "tv_sweep": tuple(tv),
         "gather": (iters[0], iters[1]),
     }
     per_kernel = {k: {"launches": n, "ms_per_step": tot} for k, (n, tot) in kall.items()}
