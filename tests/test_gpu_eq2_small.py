@@ -53,7 +53,7 @@ def test_small_grids_match_oracle(name):
 
 
 def test_many_views_of_a_small_grid_take_no_branches():
-    """460 views of 11 x 18 x 76 voxels: 135 us a call, 228 with a branch a tap and
+    """460 views of 11 x 18 x 76 voxels: 150 us a call, 228 with a branch a tap and
     243 with a branch a view."""
     torch = require_gpu()
     import paper_1002_3675_amd as cb
